@@ -242,7 +242,7 @@ fused_stage_kernel(Consts c, StageArgs s)
     }
 
     auto load_plane = [&](int zp, TIN (&dst)[NLOAD][5][PW]) {
-        // zp is in [-2, nz + 6] (march padding): at most two wraps
+        // zp is in [-2, nz + 3]: at most two wraps
         int zw = zp < 0 ? zp + c.nz : zp;
         zw = zw >= c.nz ? zw - c.nz : zw;
         zw = zw >= c.nz ? zw - c.nz : zw;
@@ -627,16 +627,19 @@ fused_stage_kernel(Consts c, StageArgs s)
     if constexpr (AHEAD2) load_plane(z0 - 1, pf);
     lds_barrier();
 
-    // The march covers planes z0-2 .. z1+1, padded to a multiple of 5;
-    // padding planes are loaded (wrapped, valid memory) but never output.
-    const int L = z1 - z0 + 4;
-    for (int it = 0; it < L; it += 5) {
-        const int zp = z0 - 2 + it;
+    // The march covers planes z0-2 .. z1+1 and is left at the last of them.
+    const int zlast = z1 + 1;
+    for (int zp = z0 - 2;;) {
         step(IC<0>{}, zp);
-        step(IC<1>{}, zp + 1);
-        step(IC<2>{}, zp + 2);
-        step(IC<3>{}, zp + 3);
-        step(IC<4>{}, zp + 4);
+        if (++zp > zlast) break;
+        step(IC<1>{}, zp);
+        if (++zp > zlast) break;
+        step(IC<2>{}, zp);
+        if (++zp > zlast) break;
+        step(IC<3>{}, zp);
+        if (++zp > zlast) break;
+        step(IC<4>{}, zp);
+        if (++zp > zlast) break;
     }
 
     if constexpr (DIAG) {
@@ -786,7 +789,7 @@ int fused_resident_blocks(ns_precision prec, int tile)
     int r = cache[dev][q][tile].load();
     if (r == 0) {
         if (split_tile(tile))
-            r = split_resident_blocks(prec, tile);
+            r = prec == NS_FP64 ? trio_resident_blocks(tile) : split_resident_blocks(tile);
         else
             r = prec == NS_FP64 ? resident_tile<double, double, double>(tile)
                                 : resident_tile<float, float, float>(tile);
@@ -812,7 +815,8 @@ int64_t fused_num_blocks(const Consts &c, int tile, int zchunk)
 hipError_t launch_fused_stage(const Consts &c, const StageArgs &s, ns_precision prec,
                               int tile, hipStream_t st)
 {
-    if (split_tile(tile)) return launch_split_stage(c, s, prec, tile, st);
+    if (split_tile(tile))
+        return prec == NS_FP64 ? launch_trio_stage(c, s, tile, st) : launch_split_stage(c, s, tile, st);
     if (prec == NS_FP64)
         return launch_tile<double, double, double>(tile, c, s, st);
     // FP32 storage: stage 1 reads the double state, stage 3 writes it.

@@ -6,11 +6,10 @@
 namespace ns {
 
 // Column-tile shapes of the fused kernel.  Tiles 0-7: threads = BX * BY,
-// one z column each (ns_fused.hip).  Tiles 8-10 (_2G): 2 * BX * BY
-// threads, two per column: the momentum equations in one wave group, the
-// mass and energy equations and the viscous terms in the other
-// (ns_split.hip).  Chosen per problem by the
-// autotuner or by the default rule.
+// one z column each (ns_fused.hip).  Tiles 8-10 (_2G) split each column over
+// groups of waves: FP64 over three (ns_trio.hip), FP32 storage over two
+// (ns_split.hip).  Chosen per problem by the autotuner or by the default
+// rule.
 enum {
     TILE_32x8 = 0, TILE_16x16 = 1, TILE_64x4 = 2, TILE_32x16 = 3,
     TILE_16x8 = 4, TILE_32x4 = 5, TILE_16x4 = 6, TILE_8x8 = 7,
@@ -39,11 +38,13 @@ bool fused_order_supported(int tile, int order);
 int fused_resident_blocks(ns_precision prec, int tile);
 hipError_t launch_fused_stage(const Consts &c, const StageArgs &s, ns_precision prec,
                               int tile, hipStream_t st);
-// The two-group kernel (tiles 8-10): stage launch and resident blocks.
+// The split-column kernels (tiles 8-10; split_: FP32 storage, trio_: FP64):
+// stage launch and resident blocks.
 bool split_tile(int tile);
-int split_resident_blocks(ns_precision prec, int tile);
-hipError_t launch_split_stage(const Consts &c, const StageArgs &s, ns_precision prec, int tile,
-                              hipStream_t st);
+int split_resident_blocks(int tile);
+hipError_t launch_split_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st);
+int trio_resident_blocks(int tile);
+hipError_t launch_trio_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st);
 // Planes a block marches beyond its chunk (halo and pipeline depth).
 int fused_extra_planes(int tile);
 

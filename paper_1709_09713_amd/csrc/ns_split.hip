@@ -1,5 +1,6 @@
-// ns_split.hip -- the fused on-the-fly stage kernel with the work of each
-// grid point split between two groups of waves.
+// ns_split.hip -- the fused on-the-fly stage kernel of FP32 storage with the
+// work of each grid point split between two groups of waves (tiles 8-10;
+// ns_trio.hip is their FP64 form).
 //
 // Same algorithm class and arithmetic as the one-thread-per-column kernel of
 // ns_fused.hip (minimal storage: every derivative of the governing-equations
@@ -41,9 +42,7 @@ namespace {
 template <typename TIN, typename CT>
 __device__ __forceinline__ CT sp_to_ct(TIN v, double ref)
 {
-    if constexpr (std::is_same<CT, double>::value)
-        return v;
-    else if constexpr (std::is_same<TIN, double>::value)
+    if constexpr (std::is_same<TIN, double>::value)
         return (float)(v - ref);
     else
         return v;
@@ -61,17 +60,8 @@ __device__ __forceinline__ void sp_store(void *q, int64_t i, double v, double re
         __builtin_nontemporal_store((float)(v - ref), (float *)q + i);
 }
 
-// 1/x: hardware estimate and Newton steps r <- r + r (1 - x r); two steps
-// reach double rounding error, one single.  x (a density) is positive and
-// normal.
-__device__ __forceinline__ double sp_recip(double x)
-{
-    double r = __builtin_amdgcn_rcp(x);
-    double e = __builtin_fma(-x, r, 1.0);
-    r = __builtin_fma(r, e, r);
-    e = __builtin_fma(-x, r, 1.0);
-    return __builtin_fma(r, e, r);
-}
+// 1/x: hardware estimate and one Newton step r <- r + r (1 - x r), which
+// reaches single rounding error.  x (a density) is positive and normal.
 __device__ __forceinline__ float sp_recip(float x)
 {
     float r = __builtin_amdgcn_rcpf(x);
@@ -84,7 +74,7 @@ using SIC = std::integral_constant<int, V>;
 
 }  // namespace
 
-// MODE: 0 = residual only (R to s.rout), 1..3 = RK stage.
+// MODE: RK stage 1..3.
 // PAIR (even nx): group M loads the halo plane two
 // x-neighbours per lane with one 2-wide load and stages them with one
 // 2-wide LDS store per field; pairs start at even x, so with nx even they
@@ -110,7 +100,7 @@ split_stage_kernel(Consts c, StageArgs s)
     static_assert(MODE != 1 || std::is_same<TIN, double>::value, "stage 1 reads the double state");
     static_assert(!DIAG || MODE == 1, "diagnostics of the step's input state are taken in stage 1");
     static_assert(BX % 2 == 0, "pairs need an even tile width");
-    constexpr bool DEV = std::is_same<CT, float>::value;
+    static_assert(std::is_same<CT, float>::value, "deviation form in float");
     constexpr int HX = BX + 4, HY = BY + 4, HP = HX * HY, NT = BX * BY;
     static_assert(HP % 2 == 0, "pair cells start at even LDS offsets");
     constexpr int PW = PAIR ? 2 : 1;                        // points per load slot
@@ -155,9 +145,9 @@ split_stage_kernel(Consts c, StageArgs s)
     double dr[4] = {0.0, 0.0, 0.0, 0.0};
 
     // The march covers planes z0-2 .. z1+2 (M finishes a plane three steps
-    // after loading it), padded to a multiple of 5; padding planes are
-    // loaded (wrapped, valid memory) but never output.
-    const int L = z1 - z0 + 5;
+    // after loading it); planes beyond the halo are loaded (wrapped, valid
+    // memory) but never output.
+    const int zlast = z1 + 2;
 
 #define LV(f, dy, dx) lds[b][f][own + (dy) * HX + (dx)]
 #define DX1(f) d1u(LV(f, 0, -2), LV(f, 0, -1), LV(f, 0, 1), LV(f, 0, 2))
@@ -173,6 +163,20 @@ split_stage_kernel(Consts c, StageArgs s)
 #define DY1H() d1u(HF(-2, 0, L_V), HF(-1, 0, L_V), HF(1, 0, L_V), HF(2, 0, L_V))
 #define DX2(f) d2u(LV(f, 0, -2), LV(f, 0, -1), LV(f, 0, 0), LV(f, 0, 1), LV(f, 0, 2))
 #define DY2(f) d2u(LV(f, -2, 0), LV(f, -1, 0), LV(f, 0, 0), LV(f, 1, 0), LV(f, 2, 0))
+// the five phases of the ring, left at the last plane of the march
+#define MARCH(step)                                       \
+    for (int zp = z0 - 2;;) {                             \
+        step(SIC<0>{}, zp);                               \
+        if (++zp > zlast) break;                          \
+        step(SIC<1>{}, zp);                               \
+        if (++zp > zlast) break;                          \
+        step(SIC<2>{}, zp);                               \
+        if (++zp > zlast) break;                          \
+        step(SIC<3>{}, zp);                               \
+        if (++zp > zlast) break;                          \
+        step(SIC<4>{}, zp);                               \
+        if (++zp > zlast) break;                          \
+    }
 
     if (!grp_e) {
         // ------------------------------------------------------------ group M
@@ -260,11 +264,11 @@ split_stage_kernel(Consts c, StageArgs s)
                     const CT m1 = sp_to_ct<TIN, CT>(pf[r][2][j], 0.0);
                     const CT m2 = sp_to_ct<TIN, CT>(pf[r][3][j], 0.0);
                     const CT E = sp_to_ct<TIN, CT>(pf[r][4][j], c.rhoE_ref);
-                    const CT rhof = DEV ? CT(1) + rho : rho;
+                    const CT rhof = CT(1) + rho;
                     const CT inv = sp_recip(rhof);
                     const CT u = m0 * inv, v = m1 * inv, w = m2 * inv;
                     const CT p = gm1 * (E - half * (m0 * u + m1 * v + m2 * w));
-                    const CT T = DEV ? (gM2 * p - rho) * inv : gM2 * p * inv;
+                    const CT T = (gM2 * p - rho) * inv;
                     val[L_RHO][j] = rho;
                     val[L_M0][j] = m0;
                     val[L_M1][j] = m1;
@@ -316,7 +320,7 @@ split_stage_kernel(Consts c, StageArgs s)
             // zp + 2, finishing plane zf + 1) never include this step's
             // stores.  Idle lanes read a valid address they ignore.
             load_plane(zp + 2, pg);
-            if constexpr (MODE >= 1) {
+            {
                 // stages 2 and 3 read the accumulator, stage 1 the state
                 const double *src = (MODE >= 2) ? s.acc_in : (const double *)s.qin;
                 const int zn = zf + 1;
@@ -380,20 +384,15 @@ split_stage_kernel(Consts c, StageArgs s)
 #pragma unroll
                 for (int k = 0; k < 3; ++k) Rd[k] = (double)(rp[k] + inv_re * vbuf[b ^ 1][3 + k][pt]);
                 if (active) {
-                    if constexpr (MODE == 0) {
+                    if constexpr (DIAG) {
 #pragma unroll
-                        for (int f = 0; f < 3; ++f) s.rout[(1 + f) * N + pidx] = Rd[f];
-                    } else {
-                        if constexpr (DIAG) {
+                        for (int f = 0; f < 3; ++f) dr[f] += acc[f];
+                    }
 #pragma unroll
-                            for (int f = 0; f < 3; ++f) dr[f] += acc[f];
-                        }
-#pragma unroll
-                        for (int f = 0; f < 3; ++f) {
-                            sp_store<TOUT>(s.qout, (1 + f) * N + pidx, acc[f] + s.a_dt * Rd[f], 0.0);
-                            if constexpr (MODE < 3)
-                                __builtin_nontemporal_store(acc[f] + s.b_dt * Rd[f], s.acc_out + (1 + f) * N + pidx);
-                        }
+                    for (int f = 0; f < 3; ++f) {
+                        sp_store<TOUT>(s.qout, (1 + f) * N + pidx, acc[f] + s.a_dt * Rd[f], 0.0);
+                        if constexpr (MODE < 3)
+                            __builtin_nontemporal_store(acc[f] + s.b_dt * Rd[f], s.acc_out + (1 + f) * N + pidx);
                     }
                 }
             }
@@ -422,15 +421,7 @@ split_stage_kernel(Consts c, StageArgs s)
         stage_plane(0);
         load_plane(z0 - 1, pf);
         lds_barrier();
-        auto chunk = [&](int it) {
-            const int zp = z0 - 2 + it;
-            step(SIC<0>{}, zp);
-            step(SIC<1>{}, zp + 1);
-            step(SIC<2>{}, zp + 2);
-            step(SIC<3>{}, zp + 3);
-            step(SIC<4>{}, zp + 4);
-        };
-        for (int it = 0; it < L; it += 5) chunk(it);
+        MARCH(step)
     } else {
         // ------------------------------------------------------------ group E
         enum { Z_E, Z_U, Z_V, Z_W, Z_RHO, NZ };
@@ -460,7 +451,7 @@ split_stage_kernel(Consts c, StageArgs s)
             const bool do_fin = (zf >= z0 && zf < z1);
             const bool do_plane = (zp >= z0 && zp < z1);
             const int64_t pidx = (int64_t)(do_fin ? zf : z0) * c.nxy + col;
-            if constexpr (MODE >= 1) {
+            {
                 // one step ahead, as in group M
                 const double *src = (MODE >= 2) ? s.acc_in : (const double *)s.qin;
                 const int zn = zf + 1;
@@ -536,17 +527,9 @@ split_stage_kernel(Consts c, StageArgs s)
                     // tau_ij du_i/dx_j restricted to terms without a z derivative
                     const CT phi = CT(2) * (Gxx * Gxx + Gyy * Gyy) + Gxy * Gxy + Gyx * Gyx
                                    + CT(2) * Gxy * Gyx + Gzx * Gzx + Gzy * Gzy;
-                    const CT rhof = DEV ? CT(1) + rho : rho;
-                    if constexpr (DEV) {
-                        ra[S0][R_MASS] -= half * (c1x * DX1(L_M0) + c1y * DY1(L_M1) + rhof * a
-                                                  + uc * DX1(L_RHO) + vc * DY1(L_RHO));
-                    } else {
-                        // rho u and rho v at the taps, from the rho and
-                        // velocity taps this group reads anyway (equal to
-                        // the staged momenta up to rounding)
-                        ra[S0][R_MASS] -= half * (c1x * DX1P(L_RHO, L_U) + c1y * DY1P(L_RHO, L_V)
-                                                  + rhof * a + uc * DX1(L_RHO) + vc * DY1(L_RHO));
-                    }
+                    const CT rhof = CT(1) + rho;
+                    ra[S0][R_MASS] -= half * (c1x * DX1(L_M0) + c1y * DY1(L_M1) + rhof * a
+                                              + uc * DX1(L_RHO) + vc * DY1(L_RHO));
                     if constexpr (DIAG) {
                         // the kinetic energy and the omega_z part of the
                         // enstrophy are complete in the plane; the vorticity
@@ -573,7 +556,7 @@ split_stage_kernel(Consts c, StageArgs s)
 #define DZ2(f) d2u(qz[SM4][f], qz[SM3][f], qz[SM2][f], qz[SM1][f], qz[S0][f])
                 const CT E = qz[SM2][Z_E], rho = qz[SM2][Z_RHO];
                 const CT u = qz[SM2][Z_U], v = qz[SM2][Z_V], w = qz[SM2][Z_W];
-                const CT rhof = DEV ? CT(1) + rho : rho;
+                const CT rhof = CT(1) + rho;
                 const CT a = qa[SM2], bb = qb[SM2], cc = qc[SM2];
                 const CT wc = w * c1z;
                 const CT Gxz = c1z * DZ1(Z_U), Gyz = c1z * DZ1(Z_V), Gzz = c1z * DZ1(Z_W);
@@ -593,25 +576,20 @@ split_stage_kernel(Consts c, StageArgs s)
                               + inv_re * (u * Vx + v * Vy + w * Vz + phi);
                 const CT R0 = ra[SM2][R_MASS] - half * (rhof * Gzz + wc * DZ1(Z_RHO));
                 double Rd4 = (double)R4;
-                if constexpr (DEV) Rd4 -= c.H_ref * ((double)a + (double)Gzz);
+                Rd4 -= c.H_ref * ((double)a + (double)Gzz);
                 const double Rd0 = (double)R0;
                 if (active) {
-                    if constexpr (MODE == 0) {
-                        s.rout[pidx] = Rd0;
-                        s.rout[4 * N + pidx] = Rd4;
-                    } else {
-                        if constexpr (DIAG) {
-                            const CT ox = cc - Gyz, oy = Gxz - bb;
-                            dr[0] += acc0;
-                            dr[1] += acc4;
-                            dr[3] += 0.5 * (double)rhof * ((double)ox * (double)ox + (double)oy * (double)oy);
-                        }
-                        sp_store<TOUT>(s.qout, pidx, acc0 + s.a_dt * Rd0, c.rho_ref);
-                        sp_store<TOUT>(s.qout, 4 * N + pidx, acc4 + s.a_dt * Rd4, c.rhoE_ref);
-                        if constexpr (MODE < 3) {
-                            __builtin_nontemporal_store(acc0 + s.b_dt * Rd0, s.acc_out + pidx);
-                            __builtin_nontemporal_store(acc4 + s.b_dt * Rd4, s.acc_out + 4 * N + pidx);
-                        }
+                    if constexpr (DIAG) {
+                        const CT ox = cc - Gyz, oy = Gxz - bb;
+                        dr[0] += acc0;
+                        dr[1] += acc4;
+                        dr[3] += 0.5 * (double)rhof * ((double)ox * (double)ox + (double)oy * (double)oy);
+                    }
+                    sp_store<TOUT>(s.qout, pidx, acc0 + s.a_dt * Rd0, c.rho_ref);
+                    sp_store<TOUT>(s.qout, 4 * N + pidx, acc4 + s.a_dt * Rd4, c.rhoE_ref);
+                    if constexpr (MODE < 3) {
+                        __builtin_nontemporal_store(acc0 + s.b_dt * Rd0, s.acc_out + pidx);
+                        __builtin_nontemporal_store(acc4 + s.b_dt * Rd4, s.acc_out + 4 * N + pidx);
                     }
                 }
 #undef DZ1
@@ -622,15 +600,7 @@ split_stage_kernel(Consts c, StageArgs s)
 
         // prologue: matches group M's barrier
         lds_barrier();
-        auto chunk = [&](int it) {
-            const int zp = z0 - 2 + it;
-            step(SIC<0>{}, zp);
-            step(SIC<1>{}, zp + 1);
-            step(SIC<2>{}, zp + 2);
-            step(SIC<3>{}, zp + 3);
-            step(SIC<4>{}, zp + 4);
-        };
-        for (int it = 0; it < L; it += 5) chunk(it);
+        MARCH(step)
     }
 #undef LV
 #undef DX1
@@ -642,6 +612,7 @@ split_stage_kernel(Consts c, StageArgs s)
 #undef DY1H
 #undef DX2
 #undef DY2
+#undef MARCH
 
     if constexpr (DIAG) {
         // block reduction of the diagnostic partial sums, fixed order: each
@@ -742,30 +713,19 @@ int resident_sp()
 
 bool split_tile(int tile) { return tile == TILE_16x8_2G || tile == TILE_32x8_2G || tile == TILE_16x4_2G; }
 
-int split_resident_blocks(ns_precision prec, int tile)
+int split_resident_blocks(int tile)
 {
-    const bool d = prec == NS_FP64;
     switch (tile) {
-    case TILE_16x8_2G: return d ? resident_sp<16, 8, double>() : resident_sp<16, 8, float>();
-    case TILE_32x8_2G: return d ? resident_sp<32, 8, double>() : resident_sp<32, 8, float>();
-    case TILE_16x4_2G: return d ? resident_sp<16, 4, double>() : resident_sp<16, 4, float>();
+    case TILE_16x8_2G: return resident_sp<16, 8, float>();
+    case TILE_32x8_2G: return resident_sp<32, 8, float>();
+    case TILE_16x4_2G: return resident_sp<16, 4, float>();
     default: return 0;
     }
 }
 
-hipError_t launch_split_stage(const Consts &c, const StageArgs &s, ns_precision prec, int tile,
-                              hipStream_t st)
+// Stage 1 reads the double state, stage 3 writes it.
+hipError_t launch_split_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st)
 {
-    if (prec == NS_FP64) {
-        switch (s.mode) {
-        case 0: return launch_sp_tile<double, double, double, 0>(tile, c, s, st);
-        case 1: return launch_sp_tile<double, double, double, 1>(tile, c, s, st);
-        case 2: return launch_sp_tile<double, double, double, 2>(tile, c, s, st);
-        case 3: return launch_sp_tile<double, double, double, 3>(tile, c, s, st);
-        default: return hipErrorInvalidValue;
-        }
-    }
-    // FP32 storage: stage 1 reads the double state, stage 3 writes it.
     switch (s.mode) {
     case 1: return launch_sp_tile<double, float, float, 1>(tile, c, s, st);
     case 2: return launch_sp_tile<float, float, float, 2>(tile, c, s, st);

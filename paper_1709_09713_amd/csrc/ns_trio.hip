@@ -1,0 +1,819 @@
+// ns_trio.hip -- the fused on-the-fly FP64 stage kernel with the work of each
+// grid point split between three groups of waves (tiles 8-10; tile 9, 32x8,
+// is the FP64 default).
+//
+// Same algorithm class as the one-thread-per-column kernel of ns_fused.hip
+// (minimal storage: every derivative of the governing-equations section is
+// evaluated on the fly from an LDS-staged (x, y) tile marching along z, the
+// low-storage RK3 update of the generic-algorithm figure in the same pass),
+// but a block holds three threads per column of its tile:
+//  * group A (threads [0, NT)) loads and stages each plane and evaluates the
+//    mass and energy equations and the in-plane pressure gradient;
+//  * group B evaluates the three momentum equations and heat conduction;
+//  * group C evaluates div u, the viscous vector V_i = lap u_i + (1/3) d_i
+//    div u and the viscous work and dissipation.
+// The groups hand values over through vbuf, double buffered like the planes:
+// what one writes in the step of plane zp another reads in the next step,
+// after the plane barrier.  C finishes plane zp - 2 in that step, A and B
+// finish plane zp - 3.
+//
+// Arithmetic.  The skew-symmetric convective terms are taken pair by pair:
+// with the first-derivative weights c_k (odd in k, so they sum to zero)
+//   1/2 [D(f u) + f D u + u D f] = sum_k c_k (f_0 + f_k) (u_0 + u_k) / 2,
+// one addition and one multiply-add per tap where the three stencils of the
+// left side take about twice that; along z the term of a pair of planes is
+// formed once and added to one plane and taken from the other, so a residual
+// is complete two planes on and no ring of five planes is needed (the viscous
+// vector and the velocity gradient still gather from one).  Density, energy,
+// pressure and temperature are staged as deviations from the uniform
+// reference state (rho = 1, p = 1 / (gamma M^2)), whose share of the mass
+// and energy equations is -div u and -H_ref div u: the sums of a pair then
+// lose nothing to the large means.  Relative rms error of the residual
+// against 80-bit arithmetic (64^3, M = 0.1; stencils of the full fields ->
+// here): mass 3.7e-15 -> 3.6e-15, momentum 5.4e-13 .. 7.3e-13 -> 2.5e-15 ..
+// 5.7e-15, energy 4.9e-15 -> 3.6e-15; the same order of gains for M = 0.05
+// to 0.4 and on 161x97x31 and 20x17x24.
+//
+// What bounds it: at 512^3 a stage moves 19-26 GB (4.3 ms at the rate of a
+// plain kernel of the same access pattern for stage 2, 3.1 ms for stages 1
+// and 3) and needs about 3.2 ms of LDS and vector issue when its planes come
+// from L2; a step takes 4.0-4.6 ms because one barrier per plane keeps the
+// groups in step, so the three do not overlap fully.  Two groups (momentum |
+// the rest) at two waves per SIMD had 30 dependent LDS waits per plane in the
+// longer group; three groups of about equal length fit 168 registers, three
+// waves per SIMD, and hide them better.  Measured (ms per step without
+// diagnostics, two groups -> three): 512^3 13.99 -> 12.72, 256^3 1.739 ->
+// 1.595, 192^3 0.843 -> 0.754, 101x77x53 0.0884 -> 0.0774, 64^3 0.0552 ->
+// 0.0500, 32^3 0.0495 -> 0.0285 (there also because the march ends at its
+// last plane instead of at a multiple of five).
+#include <type_traits>
+
+#include "ns_common.hpp"
+#include "ns_kernels.hpp"
+
+namespace ns {
+
+namespace {
+
+// Coefficients of the stencils with their weights and physical constants
+// folded in on the host: uniform double products formed in the kernel would
+// be held in two vector registers each for the whole march.
+struct TrioK {
+    double x4, xh, y4, yh, z4, zh;   // 4 c1 and c1 / 2 of each direction
+    double z8;                       // 8 c1_z
+    double kx, ky, kz, kz16;         // kappa c2 of each direction, 16 kappa c2_z
+    double vx, vy, vz;               // 4/3 c2 of each direction
+    double mxy, mz;                  // c1_x c1_y / 3, c1_z / 3
+};
+
+TrioK make_k(const Consts &c)
+{
+    TrioK k;
+    k.x4 = 4.0 * c.c1[0];
+    k.xh = 0.5 * c.c1[0];
+    k.y4 = 4.0 * c.c1[1];
+    k.yh = 0.5 * c.c1[1];
+    k.z4 = 4.0 * c.c1[2];
+    k.zh = 0.5 * c.c1[2];
+    k.z8 = 8.0 * c.c1[2];
+    k.kx = c.kappa * c.c2[0];
+    k.ky = c.kappa * c.c2[1];
+    k.kz = c.kappa * c.c2[2];
+    k.kz16 = 16.0 * k.kz;
+    k.vx = 4.0 * c.c2[0] / 3.0;
+    k.vy = 4.0 * c.c2[1] / 3.0;
+    k.vz = 4.0 * c.c2[2] / 3.0;
+    k.mxy = c.c1[0] * c.c1[1] / 3.0;
+    k.mz = c.c1[2] / 3.0;
+    return k;
+}
+
+typedef double d2_t __attribute__((ext_vector_type(2)));
+
+template <int V>
+using TIC = std::integral_constant<int, V>;
+
+// 1/x: hardware estimate and two Newton steps r <- r + r (1 - x r), which
+// reach double rounding error.  x (a density) is positive and normal.
+__device__ __forceinline__ double tr_recip(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    double e = __builtin_fma(-x, r, 1.0);
+    r = __builtin_fma(r, e, r);
+    e = __builtin_fma(-x, r, 1.0);
+    return __builtin_fma(r, e, r);
+}
+
+// Unscaled first- and second-derivative stencils with the multiply-adds
+// written out: a product left to the compiler (30 f_0, say) can be shared
+// with another plane's step, fused in one phase of the march and not in
+// another, and a point's rounding would depend on its place in a z-chunk.
+__device__ __forceinline__ double d1(double fm2, double fm1, double fp1, double fp2)
+{
+    return __builtin_fma(8.0, fp1 - fm1, fm2 - fp2);
+}
+__device__ __forceinline__ double d2(double fm2, double fm1, double f0, double fp1, double fp2)
+{
+    return __builtin_fma(-30.0, f0, __builtin_fma(16.0, fm1 + fp1, -(fm2 + fp2)));
+}
+
+// acc - sum_k c_k (f_0 + f_k) (u_0 + u_k) / 2 over the taps k = -2, -1, 1, 2
+// in t[0..3], with the weighted velocity sums s[k] = |c_k| (u_0 + u_k) / 2.
+__device__ __forceinline__ double conv(double acc, double f0, const double (&t)[4], const double (&s)[4])
+{
+    acc = __builtin_fma(-(f0 + t[0]), s[0], acc);
+    acc = __builtin_fma(f0 + t[1], s[1], acc);
+    acc = __builtin_fma(-(f0 + t[2]), s[2], acc);
+    return __builtin_fma(f0 + t[3], s[3], acc);
+}
+
+// unscaled first derivative of the product of two fields at the taps
+__device__ __forceinline__ double d1_prod(const double (&f)[4], const double (&g)[4])
+{
+    const double far = __builtin_fma(f[0], g[0], -(f[3] * g[3]));
+    const double near = __builtin_fma(f[2], g[2], -(f[1] * g[1]));
+    return __builtin_fma(8.0, near, far);
+}
+
+}  // namespace
+
+// MODE: 0 = residual only (R to s.rout), 1..3 = RK stage.
+template <int BX, int BY, int MODE, bool DIAG, bool PAIR>
+__global__ void __launch_bounds__(3 * BX * BY) __attribute__((amdgpu_waves_per_eu(BX * BY >= 128 ? 3 : 2)))
+trio_stage_kernel(Consts c, TrioK k, StageArgs s)
+{
+    // Multiply-adds are fused only within one expression, never across
+    // statements: the march's five phases are compiled separately, and
+    // fusion across statements can differ between them, which would make a
+    // point's rounding depend on where its plane falls in a z-chunk.
+#pragma clang fp contract(on)
+    static_assert(!DIAG || MODE == 1, "diagnostics of the step's input state are taken in stage 1");
+    constexpr int HX = BX + 4, HY = BY + 4, HP = HX * HY, NT = BX * BY;
+    static_assert(BX % 2 == 0 && HP % 2 == 0, "pairs need an even tile width and even LDS offsets");
+    constexpr int PW = PAIR ? 2 : 1;                      // points per load slot
+    constexpr int NLOAD = (HP + PW * NT - 1) / (PW * NT);
+    constexpr int NW = 3 * NT / 64;
+    static_assert(NT % 64 == 0, "each group must be whole waves");
+    // staged fields: rho - 1, rho u_i, E - E_ref, u, v, w, p - p_ref, T - 1
+    enum { L_R, L_M0, L_M1, L_M2, L_E, L_U, L_V, L_W, L_P, L_T, NF };
+    // handed over: V, dissipative energy terms and div u of plane zp - 2 (C),
+    // heat conduction of plane zp - 2 (B), in-plane pressure gradient of
+    // plane zp (A); with diagnostics omega_z of plane zp and omega_x, omega_y
+    // of plane zp - 2 (C)
+    enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_HEAT, H_PX, H_PY, H_OZ, H_OX, H_OY };
+    __shared__ __attribute__((aligned(16))) double lds[2][NF][HP];
+    __shared__ double vbuf[2][DIAG ? 11 : 8][NT];
+    __shared__ double red[NW][kDiag];
+
+    // The group is a property of the wave; reading it through a scalar
+    // register makes the branches below scalar branches, so each wave runs
+    // exactly one group's march (and its barriers).
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int grp = wave / (NT / 64);
+    const int pt = (int)threadIdx.x - grp * NT;
+    const int tx = pt % BX, ty = pt / BX;
+    int tbx, tby, tbz;
+    xcd_tile(&tbx, &tby, &tbz);
+    const int x0 = tbx * BX, y0 = tby * BY;
+    const int z0 = tbz * s.zchunk;
+    const int z1 = min(z0 + s.zchunk, c.nz);
+    const int gx = x0 + tx, gy = y0 + ty;
+    const bool active = (gx < c.nx) && (gy < c.ny);
+    const int own = (ty + 2) * HX + tx + 2;
+    const int64_t N = c.N;
+    const int64_t col = active ? (int64_t)gy * c.nx + gx : 0;
+
+    const double c1x = c.c1[0], c1y = c.c1[1], c1z = c.c1[2];
+    const double c2x = c.c2[0], c2y = c.c2[1], c2z = c.c2[2];
+    const double inv_re = c.inv_re;
+
+    // per-column diagnostic sums of stage 1, added in program order
+    // (deterministic): group A mass, energy and enstrophy, group B the
+    // momenta and kinetic energy
+    double dr[4] = {0.0, 0.0, 0.0, 0.0};
+
+    // The march covers planes z0-2 .. z1+2 (A and B finish a plane three
+    // steps after it was staged); planes beyond the halo are loaded (wrapped,
+    // valid memory) but never output.
+    const int zlast = z1 + 2;
+    const double *qin = (const double *)s.qin;
+    // stages 2 and 3 read the accumulator, stage 1 the state
+    const double *accsrc = (MODE >= 2) ? s.acc_in : qin;
+
+#define LV(f, dy, dx) lds[b][f][own + (dy) * HX + (dx)]
+#define TAPS_X(t, f) const double t[4] = {LV(f, 0, -2), LV(f, 0, -1), LV(f, 0, 1), LV(f, 0, 2)}
+#define TAPS_Y(t, f) const double t[4] = {LV(f, -2, 0), LV(f, -1, 0), LV(f, 1, 0), LV(f, 2, 0)}
+#define D1T(t) d1(t[0], t[1], t[2], t[3])
+#define D2T(t, t0) d2(t[0], t[1], t0, t[2], t[3])
+// Makes a value be computed here.  Left alone, the compiler moves arithmetic
+// whose result is used in a later plane's step into that step and keeps its
+// operands, many more, in registers: up to 445 spilled registers in group C,
+// none with this.
+#define KEEP(x) asm volatile("" : "+v"(x))
+// Scheduling fence of the narrow tiles' group C: without it their reads run
+// ahead until registers spill (16x8: 2.00 -> 1.76 ms per step at 256^3); the
+// 32-wide tile does not spill and is 1% faster without.
+#define SB() do { if constexpr (BX < 32) __builtin_amdgcn_sched_barrier(0); } while (0)
+// |c_k| (u_0 + u_k) / 2 with the first-derivative weights c_k
+#define HALF_SUMS(s, u0, t, w4, wh)                                                               \
+    const double s[4] = {(wh) * ((u0) + t[0]), (w4) * ((u0) + t[1]), (w4) * ((u0) + t[2]), (wh) * ((u0) + t[3])}
+#define DZ1(f) d1(qz[SM4][f], qz[SM3][f], qz[SM1][f], qz[S0][f])
+#define DZ2(f) d2(qz[SM4][f], qz[SM3][f], qz[SM2][f], qz[SM1][f], qz[S0][f])
+#define PHASES                                                                  \
+    constexpr int PH = decltype(phc)::value;                                    \
+    constexpr int S0 = PH, SM1 = (PH + 4) % 5, SM2 = (PH + 3) % 5;              \
+    constexpr int SM3 = (PH + 2) % 5, SM4 = (PH + 1) % 5;                       \
+    (void)S0, (void)SM1, (void)SM2, (void)SM3, (void)SM4
+// the five phases of the ring, left at the last plane of the march
+#define MARCH(step)                                       \
+    for (int zp = z0 - 2;;) {                             \
+        step(TIC<0>{}, zp);                               \
+        if (++zp > zlast) break;                          \
+        step(TIC<1>{}, zp);                               \
+        if (++zp > zlast) break;                          \
+        step(TIC<2>{}, zp);                               \
+        if (++zp > zlast) break;                          \
+        step(TIC<3>{}, zp);                               \
+        if (++zp > zlast) break;                          \
+        step(TIC<4>{}, zp);                               \
+        if (++zp > zlast) break;                          \
+    }
+
+    auto acc_point = [&](int zf) {   // accumulator point of plane zf (a valid one outside the chunk)
+        return (int64_t)((zf >= z0 && zf < z1) ? zf : z0) * c.nxy + col;
+    };
+
+    if (grp == 0) {
+        // ------------------------------------------------------------ group A
+        // Group A alone loads: pairs of points with one 16-byte load each
+        // (even nx).  Sharing the loads between A and B, one point per
+        // thread, balances the arithmetic better but was 10% slower.
+        enum { Z_R, Z_E, Z_W, Z_Q, NZ };
+        enum { R_MASS, R_EN, NR };
+        double qz[5][NZ];      // rho', E', w, p' w of planes zp .. zp - 2 (zp - 3 with diagnostics)
+        double ra[5][NR];      // pending mass and energy residuals
+        double acc[2] = {0.0, 0.0}, accn[2] = {0.0, 0.0};   // of this and the next step's point
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+#pragma unroll
+            for (int f = 0; f < NZ; ++f) qz[q][f] = 0.0;
+#pragma unroll
+            for (int f = 0; f < NR; ++f) ra[q][f] = 0.0;
+        }
+
+        // Plane offsets and LDS cells of the points this thread loads;
+        // lcell < 0 marks an unused slot.
+        int loff[NLOAD], lcell[NLOAD];
+#pragma unroll
+        for (int r = 0; r < NLOAD; ++r) {
+            const int idx = PW * (pt + r * NT);
+            lcell[r] = idx < HP ? idx : -1;
+            loff[r] = 0;
+            if (idx < HP) {
+                int xx = (x0 + idx % HX - 2) % c.nx;
+                if (xx < 0) xx += c.nx;
+                int yy = (y0 + idx / HX - 2) % c.ny;
+                if (yy < 0) yy += c.ny;
+                loff[r] = yy * c.nx + xx;
+            }
+        }
+        double pf[NLOAD][5][PW];   // plane zp + 1, staged in step zp
+        double pg[NLOAD][5][PW];   // plane zp + 2, loaded in step zp
+        auto load_plane = [&](int zp, double (&dst)[NLOAD][5][PW]) {
+            int zw = zp % c.nz;
+            if (zw < 0) zw += c.nz;
+            const int64_t base = (int64_t)zw * c.nxy;
+#pragma unroll
+            for (int r = 0; r < NLOAD; ++r)
+#pragma unroll
+                for (int f = 0; f < 5; ++f) {
+                    if constexpr (PAIR) {
+                        const d2_t v = *(const d2_t *)(qin + base + loff[r] + f * N);
+                        dst[r][f][0] = v.x;
+                        dst[r][f][1] = v.y;
+                    } else {
+                        dst[r][f][0] = qin[base + loff[r] + f * N];
+                    }
+                }
+        };
+        auto stage_plane = [&](int b) {
+#pragma unroll
+            for (int r = 0; r < NLOAD; ++r) {
+                if (lcell[r] < 0) continue;
+                double val[NF][PW];
+#pragma unroll
+                for (int j = 0; j < PW; ++j) {
+                    const double rho = pf[r][0][j], m0 = pf[r][1][j], m1 = pf[r][2][j], m2 = pf[r][3][j];
+                    const double E = pf[r][4][j] - c.rhoE_ref;
+                    const double inv = tr_recip(rho);
+                    const double u = m0 * inv, v = m1 * inv, w = m2 * inv;
+                    const double p = c.gm1 * (E - 0.5 * (m0 * u + m1 * v + m2 * w));
+                    const double rd = rho - 1.0;
+                    val[L_R][j] = rd;
+                    val[L_M0][j] = m0;
+                    val[L_M1][j] = m1;
+                    val[L_M2][j] = m2;
+                    val[L_E][j] = E;
+                    val[L_U][j] = u;
+                    val[L_V][j] = v;
+                    val[L_W][j] = w;
+                    val[L_P][j] = p;
+                    val[L_T][j] = (c.gM2 * p - rd) * inv;
+                }
+                const int i = lcell[r];
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    if constexpr (PAIR) {
+                        d2_t v2;
+                        v2.x = val[f][0];
+                        v2.y = val[f][1];
+                        ((d2_t *)&lds[b][f][0])[i >> 1] = v2;
+                    } else {
+                        lds[b][f][i] = val[f][0];
+                    }
+                }
+            }
+        };
+        auto next_plane = [&]() {
+#pragma unroll
+            for (int r = 0; r < NLOAD; ++r)
+#pragma unroll
+                for (int f = 0; f < 5; ++f)
+#pragma unroll
+                    for (int j = 0; j < PW; ++j) pf[r][f][j] = pg[r][f][j];
+        };
+
+        auto step = [&](auto phc, int zp) {
+            PHASES;
+            const int b = (zp - z0) & 1;
+            const int zf = zp - 3;
+            const bool do_fin = (zf >= z0 && zf < z1);
+            const bool do_plane = (zp >= z0 && zp < z1);
+            // Plane zp + 2 and the accumulator of the next step's point are
+            // loaded now, before this step's stores: vector memory counters
+            // retire loads and stores in issue order, so a load issued after
+            // a store could only be waited for together with that store.
+            // Idle lanes read a valid address they ignore.
+            load_plane(zp + 2, pg);
+            if constexpr (MODE >= 1) {
+                const int64_t pn = acc_point(zf + 1);
+                acc[0] = accn[0];
+                acc[1] = accn[1];
+                accn[0] = __builtin_nontemporal_load(accsrc + pn);
+                accn[1] = __builtin_nontemporal_load(accsrc + 4 * N + pn);
+            }
+            const double r = LV(L_R, 0, 0), E = LV(L_E, 0, 0), w = LV(L_W, 0, 0);
+            const double p = LV(L_P, 0, 0);
+            double rm = 0.0, re = 0.0;
+            if (do_plane) {
+                const double u = LV(L_U, 0, 0), v = LV(L_V, 0, 0);
+                {
+                    TAPS_X(ut, L_U);
+                    TAPS_X(rt, L_R);
+                    TAPS_X(et, L_E);
+                    TAPS_X(pt4, L_P);
+                    HALF_SUMS(su, u, ut, k.x4, k.xh);
+                    rm = conv(rm, r, rt, su);
+                    re = conv(re, E, et, su);
+                    re = __builtin_fma(-c1x, d1_prod(pt4, ut), re);
+                    vbuf[b][H_PX][pt] = c1x * D1T(pt4);
+                }
+                {
+                    TAPS_Y(vt, L_V);
+                    TAPS_Y(rt, L_R);
+                    TAPS_Y(et, L_E);
+                    TAPS_Y(pt4, L_P);
+                    HALF_SUMS(sv, v, vt, k.y4, k.yh);
+                    rm = conv(rm, r, rt, sv);
+                    re = conv(re, E, et, sv);
+                    re = __builtin_fma(-c1y, d1_prod(pt4, vt), re);
+                    vbuf[b][H_PY][pt] = c1y * D1T(pt4);
+                }
+            }
+            // fluxes between plane zp and planes zp - 1, zp - 2
+            {
+                const double q = p * w;
+                const double s1 = k.z4 * (w + qz[SM1][Z_W]), s2 = k.zh * (w + qz[SM2][Z_W]);
+                const double m1 = (r + qz[SM1][Z_R]) * s1, m2 = (r + qz[SM2][Z_R]) * s2;
+                const double e1 = (E + qz[SM1][Z_E]) * s1 + k.z8 * (q + qz[SM1][Z_Q]);
+                const double e2 = (E + qz[SM2][Z_E]) * s2 + c1z * (q + qz[SM2][Z_Q]);
+                ra[S0][R_MASS] = rm + (m1 - m2);
+                ra[SM1][R_MASS] -= m1;
+                ra[SM2][R_MASS] += m2;
+                ra[S0][R_EN] = re + (e1 - e2);
+                ra[SM1][R_EN] -= e1;
+                ra[SM2][R_EN] += e2;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    KEEP(ra[S0][q]);
+                    KEEP(ra[SM1][q]);
+                    KEEP(ra[SM2][q]);
+                }
+                qz[S0][Z_R] = r;
+                qz[S0][Z_E] = E;
+                qz[S0][Z_W] = w;
+                qz[S0][Z_Q] = q;
+            }
+
+            // stage plane zp + 1 into the other buffer (last read in the
+            // previous step, before its barrier)
+            stage_plane(b ^ 1);
+
+            // finish plane zp - 3: group C's part, RK update, output
+            if (do_fin) {
+                const int64_t pidx = (int64_t)zf * c.nxy + col;
+                const double R0 = ra[SM3][R_MASS] - vbuf[b ^ 1][H_DIV][pt];
+                const double R4 = ra[SM3][R_EN] + (vbuf[b ^ 1][H_EN][pt] + vbuf[b ^ 1][H_HEAT][pt]);
+                if (active) {
+                    if constexpr (MODE == 0) {
+                        s.rout[pidx] = R0;
+                        s.rout[4 * N + pidx] = R4;
+                    } else {
+                        if constexpr (DIAG) {
+                            dr[0] += acc[0];
+                            dr[1] += acc[1];
+                            const double ox = vbuf[b ^ 1][H_OX][pt], oy = vbuf[b ^ 1][H_OY][pt];
+                            dr[2] += (0.5 * (1.0 + qz[SM3][Z_R])) * (ox * ox + oy * oy);
+                        }
+                        double *qo = (double *)s.qout;
+                        __builtin_nontemporal_store(acc[0] + s.a_dt * R0, qo + pidx);
+                        __builtin_nontemporal_store(acc[1] + s.a_dt * R4, qo + 4 * N + pidx);
+                        if constexpr (MODE < 3) {
+                            __builtin_nontemporal_store(acc[0] + s.b_dt * R0, s.acc_out + pidx);
+                            __builtin_nontemporal_store(acc[1] + s.b_dt * R4, s.acc_out + 4 * N + pidx);
+                        }
+                    }
+                }
+            }
+            if constexpr (DIAG) {
+                // omega_z is complete in its plane
+                if (active && zp - 1 >= z0 && zp - 1 < z1) {
+                    const double oz = vbuf[b ^ 1][H_OZ][pt];
+                    dr[2] += (0.5 * (1.0 + qz[SM1][Z_R])) * (oz * oz);
+                }
+            }
+            next_plane();
+            lds_barrier();
+        };
+
+        load_plane(z0 - 2, pf);
+        stage_plane(0);
+        load_plane(z0 - 1, pf);
+        lds_barrier();
+        MARCH(step)
+    } else if (grp == 1) {
+        // ------------------------------------------------------------ group B
+        enum { Z_M0, Z_M1, Z_M2, Z_W, Z_P, Z_T, NZ };
+        double qz[5][NZ];      // rho u, rho v, rho w, w, p' and T' of planes zp .. zp - 2
+        double ra[5][3];       // pending momentum residuals
+        double rh[5] = {0.0, 0.0, 0.0, 0.0, 0.0};   // pending heat conduction
+        double acc[3] = {0.0, 0.0, 0.0}, accn[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+#pragma unroll
+            for (int f = 0; f < NZ; ++f) qz[q][f] = 0.0;
+#pragma unroll
+            for (int f = 0; f < 3; ++f) ra[q][f] = 0.0;
+        }
+
+        auto step = [&](auto phc, int zp) {
+            PHASES;
+            const int b = (zp - z0) & 1;
+            const int zf = zp - 3;
+            const bool do_fin = (zf >= z0 && zf < z1);
+            const bool do_plane = (zp >= z0 && zp < z1);
+            if constexpr (MODE >= 1) {
+                const int64_t pn = acc_point(zf + 1);
+#pragma unroll
+                for (int f = 0; f < 3; ++f) {
+                    acc[f] = accn[f];
+                    accn[f] = __builtin_nontemporal_load(accsrc + (1 + f) * N + pn);
+                }
+            }
+            const double m[3] = {LV(L_M0, 0, 0), LV(L_M1, 0, 0), LV(L_M2, 0, 0)};
+            const double w = LV(L_W, 0, 0), p = LV(L_P, 0, 0), T = LV(L_T, 0, 0);
+            double he = 0.0;
+            double rr[3] = {0.0, 0.0, 0.0};
+            if (do_plane) {
+                const double u = LV(L_U, 0, 0), v = LV(L_V, 0, 0);
+                {
+                    TAPS_X(ut, L_U);
+                    TAPS_X(m0t, L_M0);
+                    TAPS_X(m1t, L_M1);
+                    TAPS_X(m2t, L_M2);
+                    TAPS_X(tt, L_T);
+                    HALF_SUMS(su, u, ut, k.x4, k.xh);
+                    he = k.kx * D2T(tt, T);
+                    rr[0] = conv(0.0, m[0], m0t, su);
+                    rr[1] = conv(0.0, m[1], m1t, su);
+                    rr[2] = conv(0.0, m[2], m2t, su);
+                }
+                {
+                    TAPS_Y(vt, L_V);
+                    TAPS_Y(m0t, L_M0);
+                    TAPS_Y(m1t, L_M1);
+                    TAPS_Y(m2t, L_M2);
+                    TAPS_Y(tt, L_T);
+                    HALF_SUMS(sv, v, vt, k.y4, k.yh);
+                    he += k.ky * D2T(tt, T);
+                    rr[0] = conv(rr[0], m[0], m0t, sv);
+                    rr[1] = conv(rr[1], m[1], m1t, sv);
+                    rr[2] = conv(rr[2], m[2], m2t, sv);
+                }
+                if constexpr (DIAG) {
+                    if (active) dr[3] += 0.5 * (m[0] * u + m[1] * v + m[2] * w);
+                }
+            }
+            // the in-plane pressure gradient of plane zp - 1, from A's last
+            // step (outside the chunk an undefined value, in a residual that
+            // is never output)
+            ra[SM1][0] -= vbuf[b ^ 1][H_PX][pt];
+            ra[SM1][1] -= vbuf[b ^ 1][H_PY][pt];
+            // fluxes between plane zp and planes zp - 1, zp - 2
+            {
+                const double s1 = k.z4 * (w + qz[SM1][Z_W]), s2 = k.zh * (w + qz[SM2][Z_W]);
+#pragma unroll
+                for (int f = 0; f < 3; ++f) {
+                    double f1 = (m[f] + qz[SM1][Z_M0 + f]) * s1, f2 = (m[f] + qz[SM2][Z_M0 + f]) * s2;
+                    if (f == 2) {
+                        f1 = __builtin_fma(k.z8, p + qz[SM1][Z_P], f1);
+                        f2 = __builtin_fma(c1z, p + qz[SM2][Z_P], f2);
+                    }
+                    ra[S0][f] = rr[f] + (f1 - f2);
+                    ra[SM1][f] -= f1;
+                    ra[SM2][f] += f2;
+                    KEEP(ra[S0][f]);
+                    KEEP(ra[SM1][f]);
+                    KEEP(ra[SM2][f]);
+                    qz[S0][Z_M0 + f] = m[f];
+                }
+                const double h1 = k.kz16 * (T - qz[SM1][Z_T]), h2 = k.kz * (T - qz[SM2][Z_T]);
+                rh[S0] = he - (h1 - h2);
+                rh[SM1] += h1;
+                rh[SM2] -= h2;
+                KEEP(rh[S0]);
+                KEEP(rh[SM1]);
+                vbuf[b][H_HEAT][pt] = rh[SM2];
+                qz[S0][Z_W] = w;
+                qz[S0][Z_P] = p;
+                qz[S0][Z_T] = T;
+            }
+
+            // finish plane zp - 3: viscous vector from C, RK update, output
+            if (do_fin) {
+                const int64_t pidx = (int64_t)zf * c.nxy + col;
+                double R[3];
+#pragma unroll
+                for (int f = 0; f < 3; ++f) R[f] = ra[SM3][f] + inv_re * vbuf[b ^ 1][H_VX + f][pt];
+                if (active) {
+                    if constexpr (MODE == 0) {
+#pragma unroll
+                        for (int f = 0; f < 3; ++f) s.rout[(1 + f) * N + pidx] = R[f];
+                    } else {
+                        if constexpr (DIAG) {
+#pragma unroll
+                            for (int f = 0; f < 3; ++f) dr[f] += acc[f];
+                        }
+                        double *qo = (double *)s.qout;
+#pragma unroll
+                        for (int f = 0; f < 3; ++f) {
+                            __builtin_nontemporal_store(acc[f] + s.a_dt * R[f], qo + (1 + f) * N + pidx);
+                            if constexpr (MODE < 3)
+                                __builtin_nontemporal_store(acc[f] + s.b_dt * R[f], s.acc_out + (1 + f) * N + pidx);
+                        }
+                    }
+                }
+            }
+            lds_barrier();
+        };
+
+        lds_barrier();   // group A's prologue
+        MARCH(step)
+    } else {
+        // ------------------------------------------------------------ group C
+        enum { Z_U, Z_V, Z_W, NZ };
+        double qz[5][NZ];               // ring: u, v, w of the own column
+        double qa[5], qb[5], qc[5];     // ring: D_x u + D_y v, D_x w, D_y w
+        double rv[5][3];                // in-plane viscous vector of planes zp .. zp - 2
+        double rp[5];                   // in-plane part of the dissipation, same planes
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            qa[q] = qb[q] = qc[q] = rp[q] = 0.0;
+#pragma unroll
+            for (int f = 0; f < NZ; ++f) qz[q][f] = rv[q][f] = 0.0;
+        }
+
+        auto step = [&](auto phc, int zp) {
+            PHASES;
+            const int b = (zp - z0) & 1;
+            const int zf = zp - 2;
+            const bool do_fin = (zf >= z0 && zf < z1);
+            // The reads of a field are kept ahead of the arithmetic of the
+            // field before it, and its arithmetic behind them: a few waits
+            // for LDS, and no more taps in registers than two fields need.
+            const int hx = (tx < 2) ? -2 : (tx >= BX - 2 ? 2 : 0);
+#define LVH(f, dy) lds[b][f][own + (dy) * HX + hx]
+            double phi, r0, r1, r2;
+            {
+                const double u = LV(L_U, 0, 0);
+                TAPS_Y(uy, L_U);
+                TAPS_X(ux, L_U);
+                const double hu4[4] = {LVH(L_U, -2), LVH(L_U, -1), LVH(L_U, 1), LVH(L_U, 2)};
+                SB();
+                const double v = LV(L_V, 0, 0);
+                TAPS_Y(vy, L_V);
+                TAPS_X(vx, L_V);
+                const double hv4[4] = {LVH(L_V, -2), LVH(L_V, -1), LVH(L_V, 1), LVH(L_V, 2)};
+                SB();
+                // mixed derivatives d_x d_y u and d_x d_y v: the x-stencil
+                // applied across the row's lanes to the y-derivatives they
+                // already hold; a row's two end lanes on each side take the
+                // y-derivative at their halo column (x - 2 at the start of
+                // the row, x + 2 at its end).  The other lanes read their own
+                // column, which keeps the wave's addresses on distinct banks.
+                const double dyu = D1T(uy);
+                const double Gxx = c1x * D1T(ux), Gxy = c1y * dyu;
+                r0 = k.vx * D2T(ux, u) + c2y * D2T(uy, u);
+                r1 = k.mxy * d1u_x_lanes<BX>(dyu, D1T(hu4), tx);
+                qz[S0][Z_U] = u;
+                SB();
+                const double w = LV(L_W, 0, 0);
+                TAPS_Y(wy, L_W);
+                TAPS_X(wx, L_W);
+                SB();
+                const double dyv = D1T(vy);
+                const double Gyx = c1x * D1T(vx), Gyy = c1y * dyv;
+                r1 += c2x * D2T(vx, v) + k.vy * D2T(vy, v);
+                r0 += k.mxy * d1u_x_lanes<BX>(dyv, D1T(hv4), tx);
+                qz[S0][Z_V] = v;
+                qa[S0] = Gxx + Gyy;
+                // tau_ij du_i/dx_j restricted to terms without a z derivative
+                phi = 2.0 * (Gxx * Gxx + Gyy * Gyy) + Gxy * Gxy + Gyx * Gyx + 2.0 * Gxy * Gyx;
+                if constexpr (DIAG) vbuf[b][H_OZ][pt] = Gyx - Gxy;
+                SB();
+                const double Gzx = c1x * D1T(wx), Gzy = c1y * D1T(wy);
+                r2 = c2x * D2T(wx, w) + c2y * D2T(wy, w);
+                phi += Gzx * Gzx + Gzy * Gzy;
+                qz[S0][Z_W] = w;
+                qb[S0] = Gzx;
+                qc[S0] = Gzy;
+            }
+#undef LVH
+            KEEP(r0);
+            KEEP(r1);
+            KEEP(r2);
+            KEEP(phi);
+            KEEP(qa[S0]);
+            KEEP(qb[S0]);
+            KEEP(qc[S0]);
+            rv[S0][0] = r0;
+            rv[S0][1] = r1;
+            rv[S0][2] = r2;
+            rp[S0] = phi;
+            // plane zf = zp - 2: gathered z terms, hand-over to A and B
+            if (do_fin) {
+                const double u = qz[SM2][Z_U], v = qz[SM2][Z_V], w = qz[SM2][Z_W];
+                const double a = qa[SM2], bb = qb[SM2], cc = qc[SM2];
+                const double Gxz = c1z * DZ1(Z_U), Gyz = c1z * DZ1(Z_V), Gzz = c1z * DZ1(Z_W);
+                const double Vx = rv[SM2][0] + (c2z * DZ2(Z_U) + k.mz * d1(qb[SM4], qb[SM3], qb[SM1], qb[S0]));
+                const double Vy = rv[SM2][1] + (c2z * DZ2(Z_V) + k.mz * d1(qc[SM4], qc[SM3], qc[SM1], qc[S0]));
+                const double Vz = rv[SM2][2] + (k.vz * DZ2(Z_W) + k.mz * d1(qa[SM4], qa[SM3], qa[SM1], qa[S0]));
+                const double div = a + Gzz;
+                const double phi = Gxz * Gxz + Gyz * Gyz + 2.0 * Gzz * Gzz
+                                   + 2.0 * (Gxz * bb + Gyz * cc) - (2.0 / 3.0) * div * div;
+                vbuf[b][H_VX][pt] = Vx;
+                vbuf[b][H_VY][pt] = Vy;
+                vbuf[b][H_VZ][pt] = Vz;
+                vbuf[b][H_EN][pt] = inv_re * (u * Vx + v * Vy + w * Vz + (rp[SM2] + phi)) - c.H_ref * div;
+                vbuf[b][H_DIV][pt] = div;
+                if constexpr (DIAG) {
+                    vbuf[b][H_OX][pt] = cc - Gyz;
+                    vbuf[b][H_OY][pt] = Gxz - bb;
+                }
+            }
+            lds_barrier();
+        };
+
+        lds_barrier();   // group A's prologue
+        MARCH(step)
+    }
+#undef MARCH
+#undef PHASES
+#undef DZ1
+#undef DZ2
+#undef HALF_SUMS
+#undef SB
+#undef KEEP
+#undef D1T
+#undef D2T
+#undef TAPS_X
+#undef TAPS_Y
+#undef LV
+
+    if constexpr (DIAG) {
+        // block reduction of the diagnostic partial sums, fixed order: each
+        // thread takes the column sums of its own group's slots (the other
+        // groups' slots count zero for it), then waves, then the block
+        const int tid = threadIdx.x;
+        __syncthreads();
+        double dsum[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        if (grp == 0) {
+            dsum[0] = dr[0];
+            dsum[4] = dr[1];
+            dsum[6] = dr[2];
+        } else if (grp == 1) {
+            dsum[1] = dr[0];
+            dsum[2] = dr[1];
+            dsum[3] = dr[2];
+            dsum[5] = dr[3];
+        }
+#pragma unroll
+        for (int k = 0; k < 7; ++k) {
+            double vsum = dsum[k];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) vsum += __shfl_xor(vsum, off, 64);
+            dsum[k] = vsum;
+        }
+        if ((tid & 63) == 0) {
+#pragma unroll
+            for (int k = 0; k < 7; ++k) red[tid >> 6][k] = dsum[k];
+        }
+        __syncthreads();
+        if (tid == 0) {
+            const int64_t blin = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+            for (int k = 0; k < 7; ++k) {
+                double t = 0.0;
+                for (int wv = 0; wv < NW; ++wv) t += red[wv][k];
+                s.diag_partial[blin * kDiag + k] = t;
+            }
+            s.diag_partial[blin * kDiag + 7] = 0.0;
+        }
+    }
+}
+
+namespace {
+
+template <int BX, int BY, bool PAIR>
+hipError_t launch_trio_p(const Consts &c, const StageArgs &s, hipStream_t st)
+{
+    const dim3 block(3 * BX * BY, 1, 1);
+    const dim3 grid((c.nx + BX - 1) / BX, (c.ny + BY - 1) / BY, (c.nz + s.zchunk - 1) / s.zchunk);
+    const TrioK k = make_k(c);
+    switch (s.mode) {
+    case 0: hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 0, false, PAIR>), grid, block, 0, st, c, k, s); break;
+    case 1:
+        if (s.diag_partial != nullptr)
+            hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 1, true, PAIR>), grid, block, 0, st, c, k, s);
+        else
+            hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 1, false, PAIR>), grid, block, 0, st, c, k, s);
+        break;
+    case 2: hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 2, false, PAIR>), grid, block, 0, st, c, k, s); break;
+    case 3: hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 3, false, PAIR>), grid, block, 0, st, c, k, s); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// The halo plane is loaded in x-neighbour pairs when nx is even: pairs start
+// at even x, so they never straddle the periodic wrap.
+template <int BX, int BY>
+hipError_t launch_trio(const Consts &c, const StageArgs &s, hipStream_t st)
+{
+    return c.nx % 2 == 0 ? launch_trio_p<BX, BY, true>(c, s, st) : launch_trio_p<BX, BY, false>(c, s, st);
+}
+
+template <int BX, int BY>
+int resident_trio()
+{
+    int dev = 0, cus = 0, per = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per, reinterpret_cast<const void *>(&trio_stage_kernel<BX, BY, 2, false, true>), 3 * BX * BY, 0) != hipSuccess)
+        return 0;
+    return cus * (per > 0 ? per : 1);
+}
+
+}  // namespace
+
+int trio_resident_blocks(int tile)
+{
+    switch (tile) {
+    case TILE_16x8_2G: return resident_trio<16, 8>();
+    case TILE_32x8_2G: return resident_trio<32, 8>();
+    case TILE_16x4_2G: return resident_trio<16, 4>();
+    default: return 0;
+    }
+}
+
+hipError_t launch_trio_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st)
+{
+    switch (tile) {
+    case TILE_16x8_2G: return launch_trio<16, 8>(c, s, st);
+    case TILE_32x8_2G: return launch_trio<32, 8>(c, s, st);
+    case TILE_16x4_2G: return launch_trio<16, 4>(c, s, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace ns
