@@ -49,56 +49,67 @@ hipError_t launch_tgv_init(const Consts &c, const ns_params *p, double *state, h
 }
 
 // ---------------------------------------------------------------------------
-// Diagnostics partials: one block of 256 threads per (x-row strip of 256
-// points); each thread handles one point, vorticity from fd stencils of
-// u = m / rho evaluated at the taps.
-constexpr int kDiagThreads = 256;
+// Diagnostics partials: a block owns a 32 x 8 column tile and marches along z
+// through a chunk of planes.  Each plane's velocities go through LDS for the
+// x and y stencils (fd); u and v also keep a ring of five planes of the own
+// column for the z stencils.  w has no z derivative in the vorticity, u no x
+// and v no y derivative, so the halo is two rows (u, w) and two columns (v, w)
+// on each side and no corners.
+//
+// Bound by memory: 40 B per point must be read; the halo rows and columns add
+// about 30% of L2 reads and the planes above and below a chunk 4 / chunk.
+// Whole diagnostics() calls: 256^3 561 -> 199 us, 512^3 5.03 -> 1.21 ms (4.4
+// TB/s) against one thread per point gathering its neighbours through the
+// caches with a division per velocity.
+constexpr int kDiagBX = 32, kDiagBY = 8, kDiagThreads = kDiagBX * kDiagBY;
 
-int64_t diag_num_blocks(const Consts &c) { return (c.N + kDiagThreads - 1) / kDiagThreads; }
-
-__device__ __forceinline__ double vel(const double *Q, int64_t N, int64_t i, int comp)
+// Planes per block: the shortest chunk that still leaves about 2048 blocks (a
+// compute unit holds up to eight), so that large grids read few planes twice
+// and small ones fill the device (16^3: one plane per block).
+static int diag_zchunk(const Consts &c)
 {
-    return Q[(1 + comp) * N + i] / Q[i];
+    const int64_t tiles = (int64_t)((c.nx + kDiagBX - 1) / kDiagBX) * ((c.ny + kDiagBY - 1) / kDiagBY);
+    const int64_t chunks = (2048 + tiles - 1) / tiles;
+    return (int)((c.nz + chunks - 1) / chunks);
 }
 
-__global__ void __launch_bounds__(kDiagThreads)
-diag_partial_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ partial)
+// Grids of fewer points than this take one thread per point instead
+// (diag_point_kernel): a march is at least five dependent plane loads, which
+// a small grid cannot hide.  diagnostics() calls, point kernel | march: 16^3
+// 29.8 | 32.1, 64^3 35.5 | 40.0, 101x77x53 43.5 | 43.6, 128^3 (as it was) 86 | 61 us.
+constexpr int64_t kDiagMarchPoints = (int64_t)1 << 19;
+
+static bool diag_march(const Consts &c) { return c.N >= kDiagMarchPoints; }
+
+static dim3 diag_grid(const Consts &c)
+{
+    if (!diag_march(c)) return dim3((unsigned)((c.N + kDiagThreads - 1) / kDiagThreads));
+    const int zc = diag_zchunk(c);
+    return dim3((c.nx + kDiagBX - 1) / kDiagBX, (c.ny + kDiagBY - 1) / kDiagBY, (c.nz + zc - 1) / zc);
+}
+
+int64_t diag_num_blocks(const Consts &c)
+{
+    const dim3 g = diag_grid(c);
+    return (int64_t)g.x * g.y * g.z;
+}
+
+// 1/x by the hardware estimate and two Newton steps (x a density: positive
+// and normal), to double rounding error.
+__device__ __forceinline__ double diag_recip(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    double e = __builtin_fma(-x, r, 1.0);
+    r = __builtin_fma(r, e, r);
+    e = __builtin_fma(-x, r, 1.0);
+    return __builtin_fma(r, e, r);
+}
+
+// Block sum of the seven per-thread sums in a fixed order, into the block's
+// partial record.
+__device__ __forceinline__ void diag_block_sum(double (&s)[7], double *__restrict__ partial, int64_t blin)
 {
     __shared__ double red[kDiagThreads / 64][kDiag];
-    const int64_t idx = (int64_t)blockIdx.x * kDiagThreads + threadIdx.x;
-    double s[7] = {0, 0, 0, 0, 0, 0, 0};
-    if (idx < c.N) {
-        const int64_t N = c.N;
-        const int i = (int)(idx % c.nx);
-        const int j = (int)((idx / c.nx) % c.ny);
-        const int k = (int)(idx / c.nxy);
-        const int co[3] = {i, j, k};
-        const int nn[3] = {c.nx, c.ny, c.nz};
-        const int64_t st[3] = {1, c.nx, c.nxy};
-        // G[a][d] = d u_a / d x_d
-        double G[3][3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const int64_t im2 = idx + (int64_t)(wrap1(co[d] - 2, nn[d]) - co[d]) * st[d];
-            const int64_t im1 = idx + (int64_t)(wrap1(co[d] - 1, nn[d]) - co[d]) * st[d];
-            const int64_t ip1 = idx + (int64_t)(wrap1(co[d] + 1, nn[d]) - co[d]) * st[d];
-            const int64_t ip2 = idx + (int64_t)(wrap1(co[d] + 2, nn[d]) - co[d]) * st[d];
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                G[a][d] = c.c1[d] * d1u(vel(Q, N, im2, a), vel(Q, N, im1, a), vel(Q, N, ip1, a),
-                                        vel(Q, N, ip2, a));
-        }
-        const double rho = Q[idx];
-        const double m0 = Q[N + idx], m1 = Q[2 * N + idx], m2 = Q[3 * N + idx];
-        const double ox = G[2][1] - G[1][2], oy = G[0][2] - G[2][0], oz = G[1][0] - G[0][1];
-        s[0] = rho;
-        s[1] = m0;
-        s[2] = m1;
-        s[3] = m2;
-        s[4] = Q[4 * N + idx];
-        s[5] = 0.5 * (m0 * m0 + m1 * m1 + m2 * m2) / rho;
-        s[6] = 0.5 * rho * (ox * ox + oy * oy + oz * oz);
-    }
 #pragma unroll
     for (int q = 0; q < 7; ++q) {
         double v = s[q];
@@ -114,16 +125,179 @@ diag_partial_kernel(Consts c, const double *__restrict__ Q, double *__restrict__
         for (int q = 0; q < 7; ++q) {
             double t = 0.0;
             for (int wv = 0; wv < kDiagThreads / 64; ++wv) t += red[wv][q];
-            partial[(int64_t)blockIdx.x * kDiag + q] = t;
+            partial[blin * kDiag + q] = t;
         }
-        partial[(int64_t)blockIdx.x * kDiag + 7] = 0.0;
+        partial[blin * kDiag + 7] = 0.0;
     }
+}
+
+// One thread per point, neighbours through the caches.
+__global__ void __launch_bounds__(kDiagThreads)
+diag_point_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ partial)
+{
+    const int64_t idx = (int64_t)blockIdx.x * kDiagThreads + threadIdx.x;
+    double s[7] = {0, 0, 0, 0, 0, 0, 0};
+    if (idx < c.N) {
+        const int64_t N = c.N;
+        const int i = (int)(idx % c.nx);
+        const int j = (int)((idx / c.nx) % c.ny);
+        const int k = (int)(idx / c.nxy);
+        const int co[3] = {i, j, k};
+        const int nn[3] = {c.nx, c.ny, c.nz};
+        const int64_t st[3] = {1, c.nx, c.nxy};
+        // G[d][e] = D_d of the two velocities other than u_d: (d + 1) % 3 and (d + 2) % 3
+        double G[3][2];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const int off[4] = {-2, -1, 1, 2};
+            double t[2][4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t at = idx + (int64_t)(wrap1(co[d] + off[q], nn[d]) - co[d]) * st[d];
+                const double inv = diag_recip(Q[at]);
+#pragma unroll
+                for (int e = 0; e < 2; ++e) t[e][q] = Q[(1 + (d + 1 + e) % 3) * N + at] * inv;
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) G[d][e] = c.c1[d] * d1u(t[e][0], t[e][1], t[e][2], t[e][3]);
+        }
+        const double rho = Q[idx];
+        const double m0 = Q[N + idx], m1 = Q[2 * N + idx], m2 = Q[3 * N + idx];
+        const double ox = G[1][0] - G[2][1], oy = G[2][0] - G[0][1], oz = G[0][0] - G[1][1];
+        s[0] = rho;
+        s[1] = m0;
+        s[2] = m1;
+        s[3] = m2;
+        s[4] = Q[4 * N + idx];
+        s[5] = 0.5 * (m0 * m0 + m1 * m1 + m2 * m2) / rho;
+        s[6] = 0.5 * rho * (ox * ox + oy * oy + oz * oz);
+    }
+    diag_block_sum(s, partial, blockIdx.x);
+}
+
+__global__ void __launch_bounds__(kDiagThreads)
+diag_march_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ partial, int zchunk)
+{
+    constexpr int BX = kDiagBX, BY = kDiagBY, HX = BX + 4, HY = BY + 4;
+    constexpr int YH = 4 * BX, XH = 4 * BY;      // halo points above and below, left and right
+    static_assert(YH + XH <= kDiagThreads, "one halo point per thread");
+    __shared__ double lu[2][HY][BX];             // u: own columns, two halo rows each side
+    __shared__ double lv[2][BY][HX];             // v: own rows, two halo columns each side
+    __shared__ double lw[2][HY][HX];             // w: both
+    const int tid = threadIdx.x, tx = tid % BX, ty = tid / BX;
+    int tbx, tby, tbz;
+    xcd_tile(&tbx, &tby, &tbz);
+    const int x0 = tbx * BX, y0 = tby * BY;
+    const int z0 = tbz * zchunk, z1 = min(z0 + zchunk, c.nz);
+    const bool active = x0 + tx < c.nx && y0 + ty < c.ny;
+    const int64_t N = c.N;
+    // Own column (wrapped, valid memory beyond the grid: a partial tile's
+    // last columns read their halo there) and this thread's halo point.
+    const int ox = (x0 + tx) % c.nx, oy = (y0 + ty) % c.ny;
+    const int ocol = oy * c.nx + ox;
+    const bool yhalo = tid < YH, xhalo = tid >= YH && tid < YH + XH;
+    int hx = 0, hy = 0;                          // cell in the tile with its halo
+    if (yhalo) {
+        const int row = tid / BX;
+        hx = tid % BX + 2;
+        hy = row < 2 ? row : BY + row;
+    } else if (xhalo) {
+        const int q = tid - YH, cc = q % 4;
+        hx = cc < 2 ? cc : BX + cc;
+        hy = q / 4 + 2;
+    }
+    int hxx = (x0 + hx - 2) % c.nx, hyy = (y0 + hy - 2) % c.ny;
+    if (hxx < 0) hxx += c.nx;
+    if (hyy < 0) hyy += c.ny;
+    const int hcol = hyy * c.nx + hxx;
+    const int64_t hf = yhalo ? N : 2 * N;        // the halo point's second velocity: u or v
+
+    double s[7] = {0, 0, 0, 0, 0, 0, 0};
+    double qu[5], qv[5];                         // u, v of the own column, planes zp-4 .. zp
+    double qx[3], qy[3], qr[3];                  // D_x w, D_y w, rho of planes zp-2 .. zp
+#pragma unroll
+    for (int k = 0; k < 5; ++k) qu[k] = qv[k] = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) qx[k] = qy[k] = qr[k] = 0.0;
+
+    double p0[5], ph[3];                         // next plane: own point, halo point
+    auto load = [&](int zp) {
+        int zw = zp % c.nz;
+        if (zw < 0) zw += c.nz;
+        const double *q = Q + (int64_t)zw * c.nxy;
+#pragma unroll
+        for (int f = 0; f < 5; ++f) p0[f] = q[f * N + ocol];
+        // threads without a halo point read the tile's first one
+        ph[0] = q[hcol];
+        ph[1] = q[hf + hcol];
+        ph[2] = q[3 * N + hcol];
+    };
+
+    load(z0 - 2);
+    for (int zp = z0 - 2; zp < z1 + 2; ++zp) {
+        const int b = (zp - z0) & 1;
+        const double rho = p0[0], m0 = p0[1], m1 = p0[2], m2 = p0[3], E = p0[4];
+        const double inv = diag_recip(rho);
+        const double u = m0 * inv, v = m1 * inv, w = m2 * inv;
+        lu[b][ty + 2][tx] = u;
+        lv[b][ty][tx + 2] = v;
+        lw[b][ty + 2][tx + 2] = w;
+        if (yhalo || xhalo) {
+            const double hinv = diag_recip(ph[0]);
+            if (yhalo)
+                lu[b][hy][hx - 2] = ph[1] * hinv;
+            else
+                lv[b][hy - 2][hx] = ph[1] * hinv;
+            lw[b][hy][hx] = ph[2] * hinv;
+        }
+        lds_barrier();
+        if (zp + 1 < z1 + 2) load(zp + 1);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            qu[k] = qu[k + 1];
+            qv[k] = qv[k + 1];
+        }
+        qu[4] = u;
+        qv[4] = v;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            qx[k] = qx[k + 1];
+            qy[k] = qy[k + 1];
+            qr[k] = qr[k + 1];
+        }
+        qr[2] = rho;
+        if (zp >= z0 && zp < z1) {
+            qx[2] = c.c1[0] * d1u(lw[b][ty + 2][tx], lw[b][ty + 2][tx + 1], lw[b][ty + 2][tx + 3], lw[b][ty + 2][tx + 4]);
+            qy[2] = c.c1[1] * d1u(lw[b][ty][tx + 2], lw[b][ty + 1][tx + 2], lw[b][ty + 3][tx + 2], lw[b][ty + 4][tx + 2]);
+            const double oz = c.c1[0] * d1u(lv[b][ty][tx], lv[b][ty][tx + 1], lv[b][ty][tx + 3], lv[b][ty][tx + 4])
+                              - c.c1[1] * d1u(lu[b][ty][tx], lu[b][ty + 1][tx], lu[b][ty + 3][tx], lu[b][ty + 4][tx]);
+            if (active) {
+                s[0] += rho;
+                s[1] += m0;
+                s[2] += m1;
+                s[3] += m2;
+                s[4] += E;
+                s[5] += 0.5 * (m0 * u + m1 * v + m2 * w);
+                s[6] += 0.5 * rho * (oz * oz);
+            }
+        }
+        // the vorticity components with z derivatives of plane zp - 2
+        if (active && zp - 2 >= z0) {
+            const double wx = qy[0] - c.c1[2] * d1u(qv[0], qv[1], qv[3], qv[4]);
+            const double wy = c.c1[2] * d1u(qu[0], qu[1], qu[3], qu[4]) - qx[0];
+            s[6] += 0.5 * qr[0] * (wx * wx + wy * wy);
+        }
+    }
+    diag_block_sum(s, partial, ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
 }
 
 hipError_t launch_diag_partials(const Consts &c, const double *state, double *partial, hipStream_t st)
 {
-    hipLaunchKernelGGL(diag_partial_kernel, dim3((unsigned)diag_num_blocks(c)), dim3(kDiagThreads), 0, st,
-                       c, state, partial);
+    if (diag_march(c))
+        hipLaunchKernelGGL(diag_march_kernel, diag_grid(c), dim3(kDiagThreads), 0, st, c, state, partial,
+                           diag_zchunk(c));
+    else
+        hipLaunchKernelGGL(diag_point_kernel, diag_grid(c), dim3(kDiagThreads), 0, st, c, state, partial);
     return hipGetLastError();
 }
 
