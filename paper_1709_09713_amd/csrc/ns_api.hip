@@ -370,7 +370,8 @@ ns_status ns_residual(const ns_params *p, ns_algo algo, const double *Q, double 
     st = check_work(work, work_bytes, L.total);
     if (st != NS_OK) return st;
     if (algo == NS_ALGO_SOME) {
-        NS_HIP_OK(rs_stage(c, Q, at<double>(work, L.G), nullptr, nullptr, nullptr, R, 0.0, 0.0, 0, s));
+        NS_HIP_OK(rs_stage(c, Q, at<double>(work, L.G), nullptr, nullptr, nullptr, R, 0.0, 0.0, 0,
+                           default_zchunk(c, NS_FP64, TILE_32x8_2G), s));
         return NS_OK;
     }
     NS_HIP_OK(stored_residual(c, Q, R, at<double>(work, L.stored), s));
@@ -409,14 +410,15 @@ ns_status rk3_step(const ns_params *p, ns_algo algo, ns_precision prec, double d
     if (algo == NS_ALGO_SOME) {
         double *G = at<double>(work, L.G);
         double *q1 = (double *)b1, *q2 = (double *)b2;
+        const int zc = default_zchunk(c, NS_FP64, TILE_32x8_2G);
         for (int32_t step = 0; step < nsteps; ++step) {
             if (diag_dev) {
                 NS_HIP_OK(launch_diag_partials(c, state, partial, s));
                 NS_HIP_OK(launch_diag_finalize(c, partial, diag_num_blocks(c), diag_dev + step, s));
             }
-            NS_HIP_OK(rs_stage(c, state, G, nullptr, acc, q1, nullptr, rk_a(0) * dt, rk_b(0) * dt, 1, s));
-            NS_HIP_OK(rs_stage(c, q1, G, acc, acc, q2, nullptr, rk_a(1) * dt, rk_b(1) * dt, 2, s));
-            NS_HIP_OK(rs_stage(c, q2, G, acc, nullptr, state, nullptr, rk_a(2) * dt, 0.0, 3, s));
+            NS_HIP_OK(rs_stage(c, state, G, nullptr, acc, q1, nullptr, rk_a(0) * dt, rk_b(0) * dt, 1, zc, s));
+            NS_HIP_OK(rs_stage(c, q1, G, acc, acc, q2, nullptr, rk_a(1) * dt, rk_b(1) * dt, 2, zc, s));
+            NS_HIP_OK(rs_stage(c, q2, G, acc, nullptr, state, nullptr, rk_a(2) * dt, 0.0, 3, zc, s));
         }
         return NS_OK;
     }

@@ -27,6 +27,7 @@ struct StageArgs {
     int mode;               // 0 = residual, 1..3 = RK stage
     int zchunk;             // planes per block along z
     double *diag_partial;   // per-block diagnostic partial sums, or nullptr
+    const double *grad;     // stored velocity gradients (intermediate-storage class)
     int order;              // in-plane evaluation order: 0 by equation, 1 by direction
 };
 
@@ -45,6 +46,8 @@ int split_resident_blocks(int tile);
 hipError_t launch_split_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st);
 int trio_resident_blocks(int tile);
 hipError_t launch_trio_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st);
+// The 32x8 three-group kernel with the velocity gradients taken from s.grad.
+hipError_t launch_trio_grad(const Consts &c, const StageArgs &s, hipStream_t st);
 // Planes a block marches beyond its chunk (halo and pipeline depth).
 int fused_extra_planes(int tile);
 
@@ -91,9 +94,10 @@ size_t stored_workspace_doubles(const Consts &c);
 // Intermediate-storage class: nine gradient arrays; one stage = gradient
 // sweep + residual/RK sweep (mode 0 writes R to rout).
 size_t rs_workspace_doubles(const Consts &c);
+// zchunk: planes per block of the second sweep.
 hipError_t rs_stage(const Consts &c, const double *qin, double *G, const double *acc_in,
                     double *acc_out, double *qout, double *rout, double a_dt, double b_dt,
-                    int mode, hipStream_t st);
+                    int mode, int zchunk, hipStream_t st);
 hipError_t stored_residual(const Consts &c, const double *Q, double *R, double *work,
                            hipStream_t st);
 hipError_t launch_rk_update(const Consts &c, const double *R, const double *acc_in,

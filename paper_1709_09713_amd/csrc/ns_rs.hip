@@ -3,15 +3,14 @@
 // du_i/dx_j are kept in global arrays, every other derivative is evaluated
 // inline at the point that needs it.
 //
-// Per RK stage: rs_gradient_kernel evaluates the nine gradients from the
-// conserved variables at the first-derivative taps (u_i = m_i / rho formed
-// per tap) and stores them; rs_stage_kernel then evaluates the residual of
-// the governing-equations section at each point -- convective, pressure and
-// heat-conduction derivatives from the conserved variables at their taps,
-// the velocity gradient, divergence and dissipation from the stored arrays,
-// the mixed viscous derivatives d/dx_i (du_k/dx_k) as first derivatives of
-// the stored diagonal gradients along x_i -- and applies the low-storage RK
-// update of the generic-algorithm figure in the same pass.  FP64 only.
+// Per RK stage: rs_gradient_kernel evaluates the nine gradients and stores
+// them; the three-group stage kernel (ns_trio.hip, GRAD) then evaluates the
+// residual of the governing-equations section -- convective, pressure, heat
+// conduction and second derivatives inline from LDS-staged planes; div u, the
+// dissipation and the mixed viscous derivatives d/dx_i (du_k/dx_k) from the
+// stored arrays -- and applies the low-storage RK update of the
+// generic-algorithm figure in the same pass.  Small grids take one thread per
+// point with every tap through the caches instead.  FP64 only.
 #include "ns_common.hpp"
 #include "ns_kernels.hpp"
 
@@ -19,7 +18,128 @@ namespace ns {
 
 namespace {
 
-constexpr int RS_BX = 64, RS_BY = 4;
+constexpr int RS_BX = 32, RS_BY = 8, RS_NT = RS_BX * RS_BY;
+
+// 1/x: hardware estimate and two Newton steps, to double rounding error (x a
+// density: positive and normal).
+__device__ __forceinline__ double rs_recip(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    double e = __builtin_fma(-x, r, 1.0);
+    r = __builtin_fma(r, e, r);
+    e = __builtin_fma(-x, r, 1.0);
+    return __builtin_fma(r, e, r);
+}
+
+// A block owns a 32 x 8 column tile and marches along z: each plane's
+// velocities go through LDS for the x and y gradients, which are stored in
+// the plane's step; the z gradients of plane zp - 2 come from a ring of five
+// planes of the own column.  No corners: a gradient has taps in one direction
+// only.
+//
+// Bound by memory: 32 B read and 72 B written per point (0.45 ms at 256^3,
+// 3.9 TB/s; one thread per point, three divisions per tap: 0.75 ms).
+__global__ void __launch_bounds__(RS_NT)
+rs_gradient_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ G, int zchunk)
+{
+    constexpr int HX = RS_BX + 4, HY = RS_BY + 4;
+    constexpr int YH = 4 * RS_BX, XH = 4 * RS_BY;   // halo points above and below, left and right
+    static_assert(YH + XH <= RS_NT, "one halo point per thread");
+    __shared__ double lu[2][3][HY][HX];
+    const int tid = threadIdx.x, tx = tid % RS_BX, ty = tid / RS_BX;
+    int tbx, tby, tbz;
+    xcd_tile(&tbx, &tby, &tbz);
+    const int x0 = tbx * RS_BX, y0 = tby * RS_BY;
+    const int z0 = tbz * zchunk, z1 = min(z0 + zchunk, c.nz);
+    const bool active = x0 + tx < c.nx && y0 + ty < c.ny;
+    const int64_t N = c.N;
+    // Own column, wrapped beyond the grid: a partial tile's last columns read
+    // their halo there.
+    const int ocol = ((y0 + ty) % c.ny) * c.nx + (x0 + tx) % c.nx;
+    const bool halo = tid < YH + XH;
+    int hx = 2, hy = 2;   // threads without a halo point read the tile's first point
+    if (tid < YH) {
+        const int row = tid / RS_BX;
+        hx = tid % RS_BX + 2;
+        hy = row < 2 ? row : RS_BY + row;
+    } else if (halo) {
+        const int q = tid - YH, cc = q % 4;
+        hx = cc < 2 ? cc : RS_BX + cc;
+        hy = q / 4 + 2;
+    }
+    int hxx = (x0 + hx - 2) % c.nx, hyy = (y0 + hy - 2) % c.ny;
+    if (hxx < 0) hxx += c.nx;
+    if (hyy < 0) hyy += c.ny;
+    const int hcol = hyy * c.nx + hxx;
+
+    double po[4], ph[4];   // rho and momenta of the next plane: own and halo point
+    auto load = [&](int zp) {
+        int zw = zp % c.nz;
+        if (zw < 0) zw += c.nz;
+        const double *q = Q + (int64_t)zw * c.nxy;
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            po[f] = q[f * N + ocol];
+            ph[f] = q[f * N + hcol];
+        }
+    };
+    double qz[5][3];       // u, v, w of planes zp - 4 .. zp
+#pragma unroll
+    for (int k = 0; k < 5; ++k) qz[k][0] = qz[k][1] = qz[k][2] = 0.0;
+
+    load(z0 - 2);
+    for (int zp = z0 - 2; zp < z1 + 2; ++zp) {
+        const int b = (zp - z0) & 1;
+        const double inv = rs_recip(po[0]);
+        double u[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            u[a] = po[1 + a] * inv;
+            lu[b][a][ty + 2][tx + 2] = u[a];
+        }
+        if (halo) {
+            const double hinv = rs_recip(ph[0]);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) lu[b][a][hy][hx] = ph[1 + a] * hinv;
+        }
+        lds_barrier();
+        if (zp + 1 < z1 + 2) load(zp + 1);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) qz[k][a] = qz[k + 1][a];
+            qz[4][a] = u[a];
+        }
+        if (active && zp >= z0 && zp < z1) {
+            double *g = G + (int64_t)zp * c.nxy + ocol;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const double(&l)[HY][HX] = lu[b][a];
+                g[(3 * a) * N] = c.c1[0] * d1u(l[ty + 2][tx], l[ty + 2][tx + 1], l[ty + 2][tx + 3], l[ty + 2][tx + 4]);
+                g[(3 * a + 1) * N] = c.c1[1] * d1u(l[ty][tx + 2], l[ty + 1][tx + 2], l[ty + 3][tx + 2], l[ty + 4][tx + 2]);
+            }
+        }
+        if (active && zp - 2 >= z0) {
+            double *g = G + (int64_t)(zp - 2) * c.nxy + ocol;
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+                g[(3 * a + 2) * N] = c.c1[2] * d1u(qz[0][a], qz[1][a], qz[3][a], qz[4][a]);
+        }
+    }
+}
+
+// Planes per block of the gradient sweep: about 2048 blocks (up to eight fit
+// on a compute unit), so that few planes are read twice.
+int gradient_zchunk(const Consts &c)
+{
+    const int64_t tiles = (int64_t)((c.nx + RS_BX - 1) / RS_BX) * ((c.ny + RS_BY - 1) / RS_BY);
+    const int64_t chunks = (2048 + tiles - 1) / tiles;
+    return (int)((c.nz + chunks - 1) / chunks);
+}
+
+// ---------------------------------------------------------------- small grids
+// One thread per point, taps through the caches.
+constexpr int PT_BX = 64, PT_BY = 4;
 
 // Offsets of the four taps of direction d around (i, j, k), periodic.
 struct Taps {
@@ -81,10 +201,10 @@ __device__ __forceinline__ double tap_velocity(double m, double inv)
     return m * inv;
 }
 
-__global__ void __launch_bounds__(RS_BX * RS_BY)
-rs_gradient_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ G)
+__global__ void __launch_bounds__(PT_BX * PT_BY)
+rs_point_gradient_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ G)
 {
-    const int i = blockIdx.x * RS_BX + threadIdx.x, j = blockIdx.y * RS_BY + threadIdx.y;
+    const int i = blockIdx.x * PT_BX + threadIdx.x, j = blockIdx.y * PT_BY + threadIdx.y;
     const int k = blockIdx.z;
     if (i >= c.nx || j >= c.ny) return;
     const int64_t idx = (int64_t)k * c.nxy + (int64_t)j * c.nx + i;
@@ -106,26 +226,15 @@ rs_gradient_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ 
     }
 }
 
-struct RsArgs {
-    const double *qin;
-    const double *G;
-    const double *acc_in;
-    double *acc_out;
-    double *qout;
-    double *rout;
-    double a_dt, b_dt;
-    int mode;   // 0 = residual only, 1..3 = RK stage
-};
-
-__global__ void __launch_bounds__(RS_BX * RS_BY) rs_stage_kernel(Consts c, RsArgs s)
+__global__ void __launch_bounds__(PT_BX * PT_BY) rs_point_stage_kernel(Consts c, StageArgs s)
 {
-    const int i = blockIdx.x * RS_BX + threadIdx.x, j = blockIdx.y * RS_BY + threadIdx.y;
+    const int i = blockIdx.x * PT_BX + threadIdx.x, j = blockIdx.y * PT_BY + threadIdx.y;
     const int k = blockIdx.z;
     if (i >= c.nx || j >= c.ny) return;
     const int64_t idx = (int64_t)k * c.nxy + (int64_t)j * c.nx + i;
     const int64_t N = c.N;
-    const double *__restrict__ Q = s.qin;
-    const double *__restrict__ G = s.G;
+    const double *__restrict__ Q = (const double *)s.qin;
+    const double *__restrict__ G = s.grad;
 
     const TapVals o = tap_vals(c, Q, idx);
     double g[3][3];   // g[a][d] = du_a / dx_d (stored)
@@ -210,26 +319,29 @@ __global__ void __launch_bounds__(RS_BX * RS_BY) rs_stage_kernel(Consts c, RsArg
 #pragma unroll
     for (int f = 0; f < 5; ++f) {
         const double acc = (s.mode == 1) ? Q[f * N + idx] : s.acc_in[f * N + idx];
-        s.qout[f * N + idx] = acc + s.a_dt * R[f];
+        ((double *)s.qout)[f * N + idx] = acc + s.a_dt * R[f];
         if (s.mode < 3) s.acc_out[f * N + idx] = acc + s.b_dt * R[f];
     }
 }
 
-dim3 rs_grid(const Consts &c) { return dim3((c.nx + RS_BX - 1) / RS_BX, (c.ny + RS_BY - 1) / RS_BY, c.nz); }
+dim3 point_grid(const Consts &c) { return dim3((c.nx + PT_BX - 1) / PT_BX, (c.ny + PT_BY - 1) / PT_BY, c.nz); }
+
+// The marching kernels' blocks step through at least five planes one after
+// another, which small grids cannot hide.  ms per RK3 step, one thread per
+// point | marching: 16^3 0.033 | 0.052, 64^3 0.092 | 0.110, 101x77x53 (412,000
+// points) 0.170 | 0.159, 128^3 0.786 | 0.476, 256^3 6.14 | 3.46.
+constexpr int64_t kMarchPoints = 400000;
 
 }  // namespace
 
 size_t rs_workspace_doubles(const Consts &c) { return 9 * (size_t)c.N; }
 
 hipError_t rs_stage(const Consts &c, const double *qin, double *G, const double *acc_in, double *acc_out,
-                    double *qout, double *rout, double a_dt, double b_dt, int mode, hipStream_t st)
+                    double *qout, double *rout, double a_dt, double b_dt, int mode, int zchunk, hipStream_t st)
 {
-    hipLaunchKernelGGL(rs_gradient_kernel, rs_grid(c), dim3(RS_BX, RS_BY, 1), 0, st, c, qin, G);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    RsArgs a;
+    StageArgs a = {};
     a.qin = qin;
-    a.G = G;
+    a.grad = G;
     a.acc_in = acc_in;
     a.acc_out = acc_out;
     a.qout = qout;
@@ -237,8 +349,20 @@ hipError_t rs_stage(const Consts &c, const double *qin, double *G, const double 
     a.a_dt = a_dt;
     a.b_dt = b_dt;
     a.mode = mode;
-    hipLaunchKernelGGL(rs_stage_kernel, rs_grid(c), dim3(RS_BX, RS_BY, 1), 0, st, c, a);
-    return hipGetLastError();
+    a.zchunk = zchunk;
+    if (c.N < kMarchPoints) {
+        hipLaunchKernelGGL(rs_point_gradient_kernel, point_grid(c), dim3(PT_BX, PT_BY, 1), 0, st, c, qin, G);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(rs_point_stage_kernel, point_grid(c), dim3(PT_BX, PT_BY, 1), 0, st, c, a);
+        return hipGetLastError();
+    }
+    const int gz = gradient_zchunk(c);
+    const dim3 grid((c.nx + RS_BX - 1) / RS_BX, (c.ny + RS_BY - 1) / RS_BY, (c.nz + gz - 1) / gz);
+    hipLaunchKernelGGL(rs_gradient_kernel, grid, dim3(RS_NT), 0, st, c, qin, G, gz);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_trio_grad(c, a, st);
 }
 
 }  // namespace ns

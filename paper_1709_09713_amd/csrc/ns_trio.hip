@@ -63,7 +63,7 @@ struct TrioK {
     double z8;                       // 8 c1_z
     double kx, ky, kz, kz16;         // kappa c2 of each direction, 16 kappa c2_z
     double vx, vy, vz;               // 4/3 c2 of each direction
-    double mxy, mz;                  // c1_x c1_y / 3, c1_z / 3
+    double mx, my, mz, mxy;          // c1 / 3 of each direction, c1_x c1_y / 3
 };
 
 TrioK make_k(const Consts &c)
@@ -83,6 +83,8 @@ TrioK make_k(const Consts &c)
     k.vx = 4.0 * c.c2[0] / 3.0;
     k.vy = 4.0 * c.c2[1] / 3.0;
     k.vz = 4.0 * c.c2[2] / 3.0;
+    k.mx = c.c1[0] / 3.0;
+    k.my = c.c1[1] / 3.0;
     k.mxy = c.c1[0] * c.c1[1] / 3.0;
     k.mz = c.c1[2] / 3.0;
     return k;
@@ -138,7 +140,11 @@ __device__ __forceinline__ double d1_prod(const double (&f)[4], const double (&g
 }  // namespace
 
 // MODE: 0 = residual only (R to s.rout), 1..3 = RK stage.
-template <int BX, int BY, int MODE, bool DIAG, bool PAIR>
+// GRAD: the intermediate-storage class: group C takes the nine velocity
+// gradients from the arrays that rs_gradient_kernel wrote (s.grad) instead of
+// evaluating them, and the mixed viscous derivatives are first derivatives of
+// the stored diagonal ones.
+template <int BX, int BY, int MODE, bool DIAG, bool PAIR, bool GRAD>
 __global__ void __launch_bounds__(3 * BX * BY) __attribute__((amdgpu_waves_per_eu(BX * BY >= 128 ? 3 : 2)))
 trio_stage_kernel(Consts c, TrioK k, StageArgs s)
 {
@@ -147,7 +153,7 @@ trio_stage_kernel(Consts c, TrioK k, StageArgs s)
     // fusion across statements can differ between them, which would make a
     // point's rounding depend on where its plane falls in a z-chunk.
 #pragma clang fp contract(on)
-    static_assert(!DIAG || MODE == 1, "diagnostics of the step's input state are taken in stage 1");
+    static_assert(!DIAG || (MODE == 1 && !GRAD), "diagnostics of the step's input state are taken in stage 1");
     constexpr int HX = BX + 4, HY = BY + 4, HP = HX * HY, NT = BX * BY;
     static_assert(BX % 2 == 0 && HP % 2 == 0, "pairs need an even tile width and even LDS offsets");
     constexpr int PW = PAIR ? 2 : 1;                      // points per load slot
@@ -164,6 +170,7 @@ trio_stage_kernel(Consts c, TrioK k, StageArgs s)
     __shared__ __attribute__((aligned(16))) double lds[2][NF][HP];
     __shared__ double vbuf[2][DIAG ? 11 : 8][NT];
     __shared__ double red[NW][kDiag];
+    __shared__ double sbuf[GRAD ? 2 : 1][GRAD ? HY : 1][BX];   // GRAD: D_x u + D_z w with two halo rows each side
 
     // The group is a property of the wave; reading it through a scalar
     // register makes the branches below scalar branches, so each wave runs
@@ -589,6 +596,132 @@ trio_stage_kernel(Consts c, TrioK k, StageArgs s)
 
         lds_barrier();   // group A's prologue
         MARCH(step)
+    } else if constexpr (GRAD) {
+        // ---------------------------------------- group C, stored gradients
+        // Reads 72 B per point more than the fused form (232 B in all in
+        // stage 2), which then bounds the stage: 0.83 ms at 256^3 in stage 2,
+        // 4.7 TB/s.  A step with the gradient sweep: 6.14 -> 3.46 ms against
+        // one thread per point with thirteen divisions and every tap through
+        // the caches.
+        enum { Z_U, Z_V, Z_W, NZ };
+        enum { XX, XY, XZ, YX, YY, YZ, ZX, ZY, ZZ, NG };   // du_i / dx_j
+        double qz[5][NZ];      // ring: u, v, w of the own column
+        double qs[5];          // ring: D_x u + D_y v
+        double rv[5][3];       // in-plane viscous vector of planes zp .. zp - 2
+        double rp[5], rd[5];   // dissipation and div u, same planes and zp + 1
+        double rx[5];          // mixed x-derivative of plane zp + 1
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            qs[q] = rp[q] = rd[q] = rx[q] = 0.0;
+#pragma unroll
+            for (int f = 0; f < NZ; ++f) qz[q][f] = rv[q][f] = 0.0;
+        }
+        // Every lane reads gradients, at its column wrapped into the grid:
+        // a lane beyond the grid's edge holds its neighbours' x-taps.
+        // Column of the row's end lanes' halo (others: their own), and the
+        // halo-row point that threads below 4 BX put into sbuf.
+        const int wx = gx % c.nx, wy = gy % c.ny;
+        const int hx = (tx < 2) ? -2 : (tx >= BX - 2 ? 2 : 0);
+        int hxx = (gx + hx) % c.nx;
+        if (hxx < 0) hxx += c.nx;
+        const int row = pt / BX, hy = row < 2 ? row : BY + row;
+        int hyy = (y0 + hy - 2) % c.ny;
+        if (hyy < 0) hyy += c.ny;
+        const bool halo_row = pt < 4 * BX;
+        const int gown = wy * c.nx + wx, ghx = wy * c.nx + hxx, ghy = halo_row ? hyy * c.nx + wx : gown;
+        double gn[NG], hn[2], yn[2];   // plane zp + 1: own column; D_y v, D_z w of the x-halo
+                                       // column; D_x u, D_z w of the halo-row point
+        auto load_grad = [&](int zp) {
+            int zw = zp % c.nz;
+            if (zw < 0) zw += c.nz;
+            const double *G = s.grad + (int64_t)zw * c.nxy;
+#pragma unroll
+            for (int q = 0; q < NG; ++q) gn[q] = G[q * N + gown];
+            hn[0] = G[YY * N + ghx];
+            hn[1] = G[ZZ * N + ghx];
+            yn[0] = G[XX * N + ghy];
+            yn[1] = G[ZZ * N + ghy];
+        };
+        // Everything the gradients of one plane give at their own point, into
+        // ring slot S, and the field of the y-stencil into sbuf: four values
+        // wait for the plane's step instead of eleven.
+        auto take_grad = [&](auto sc, int b) {
+            constexpr int S = decltype(sc)::value;
+            const double g_xx = gn[XX], g_yy = gn[YY], g_zz = gn[ZZ];
+            sbuf[b][ty + 2][tx] = g_xx + g_zz;
+            if (halo_row) sbuf[b][hy][tx] = yn[0] + yn[1];
+            double div = g_xx + g_yy + g_zz, sxy = g_xx + g_yy;
+            double phi = 2.0 * (g_xx * g_xx + g_yy * g_yy + g_zz * g_zz) + gn[XY] * gn[XY] + gn[YX] * gn[YX]
+                         + gn[XZ] * gn[XZ] + gn[ZX] * gn[ZX] + gn[YZ] * gn[YZ] + gn[ZY] * gn[ZY]
+                         + 2.0 * (gn[XY] * gn[YX] + gn[XZ] * gn[ZX] + gn[YZ] * gn[ZY]) - (2.0 / 3.0) * div * div;
+            // the x-stencil of D_y v + D_z w across the row's lanes
+            double mix = k.mx * d1u_x_lanes<BX>(g_yy + g_zz, hn[0] + hn[1], tx);
+            KEEP(div);
+            KEEP(sxy);
+            KEEP(phi);
+            KEEP(mix);
+            rd[S] = div;
+            qs[S] = sxy;
+            rp[S] = phi;
+            rx[S] = mix;
+        };
+
+        auto step = [&](auto phc, int zp) {
+            PHASES;
+            const int b = (zp - z0) & 1;
+            const int zf = zp - 2;
+            const bool do_fin = (zf >= z0 && zf < z1);
+            load_grad(zp + 1);
+            double r0, r1, r2;
+            {
+                const double u = LV(L_U, 0, 0);
+                TAPS_X(ux, L_U);
+                TAPS_Y(uy, L_U);
+                const double sy[4] = {sbuf[b][ty][tx], sbuf[b][ty + 1][tx], sbuf[b][ty + 3][tx], sbuf[b][ty + 4][tx]};
+                r0 = k.vx * D2T(ux, u) + c2y * D2T(uy, u) + rx[S0];
+                r1 = k.my * D1T(sy);
+                qz[S0][Z_U] = u;
+            }
+            {
+                const double v = LV(L_V, 0, 0);
+                TAPS_X(vx, L_V);
+                TAPS_Y(vy, L_V);
+                r1 += c2x * D2T(vx, v) + k.vy * D2T(vy, v);
+                qz[S0][Z_V] = v;
+            }
+            {
+                const double w = LV(L_W, 0, 0);
+                TAPS_X(wx4, L_W);
+                TAPS_Y(wy4, L_W);
+                r2 = c2x * D2T(wx4, w) + c2y * D2T(wy4, w);
+                qz[S0][Z_W] = w;
+            }
+            KEEP(r0);
+            KEEP(r1);
+            KEEP(r2);
+            rv[S0][0] = r0;
+            rv[S0][1] = r1;
+            rv[S0][2] = r2;
+            // plane zf = zp - 2: gathered z terms, hand-over to A and B
+            if (do_fin) {
+                const double u = qz[SM2][Z_U], v = qz[SM2][Z_V], w = qz[SM2][Z_W];
+                const double Vx = rv[SM2][0] + c2z * DZ2(Z_U);
+                const double Vy = rv[SM2][1] + c2z * DZ2(Z_V);
+                const double Vz = rv[SM2][2] + (k.vz * DZ2(Z_W) + k.mz * d1(qs[SM4], qs[SM3], qs[SM1], qs[S0]));
+                vbuf[b][H_VX][pt] = Vx;
+                vbuf[b][H_VY][pt] = Vy;
+                vbuf[b][H_VZ][pt] = Vz;
+                vbuf[b][H_EN][pt] = inv_re * (u * Vx + v * Vy + w * Vz + rp[SM2]) - c.H_ref * rd[SM2];
+                vbuf[b][H_DIV][pt] = rd[SM2];
+            }
+            take_grad(TIC<SM4>{}, b ^ 1);   // plane zp + 1's slot
+            lds_barrier();
+        };
+
+        load_grad(z0 - 2);
+        take_grad(TIC<0>{}, 0);
+        lds_barrier();   // group A's prologue
+        MARCH(step)
     } else {
         // ------------------------------------------------------------ group C
         enum { Z_U, Z_V, Z_W, NZ };
@@ -753,22 +886,25 @@ trio_stage_kernel(Consts c, TrioK k, StageArgs s)
 
 namespace {
 
-template <int BX, int BY, bool PAIR>
+template <int BX, int BY, bool PAIR, bool GRAD>
 hipError_t launch_trio_p(const Consts &c, const StageArgs &s, hipStream_t st)
 {
     const dim3 block(3 * BX * BY, 1, 1);
     const dim3 grid((c.nx + BX - 1) / BX, (c.ny + BY - 1) / BY, (c.nz + s.zchunk - 1) / s.zchunk);
     const TrioK k = make_k(c);
     switch (s.mode) {
-    case 0: hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 0, false, PAIR>), grid, block, 0, st, c, k, s); break;
+    case 0: hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 0, false, PAIR, GRAD>), grid, block, 0, st, c, k, s); break;
     case 1:
-        if (s.diag_partial != nullptr)
-            hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 1, true, PAIR>), grid, block, 0, st, c, k, s);
-        else
-            hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 1, false, PAIR>), grid, block, 0, st, c, k, s);
+        if constexpr (!GRAD) {
+            if (s.diag_partial != nullptr) {
+                hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 1, true, PAIR, GRAD>), grid, block, 0, st, c, k, s);
+                break;
+            }
+        }
+        hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 1, false, PAIR, GRAD>), grid, block, 0, st, c, k, s);
         break;
-    case 2: hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 2, false, PAIR>), grid, block, 0, st, c, k, s); break;
-    case 3: hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 3, false, PAIR>), grid, block, 0, st, c, k, s); break;
+    case 2: hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 2, false, PAIR, GRAD>), grid, block, 0, st, c, k, s); break;
+    case 3: hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 3, false, PAIR, GRAD>), grid, block, 0, st, c, k, s); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -776,10 +912,10 @@ hipError_t launch_trio_p(const Consts &c, const StageArgs &s, hipStream_t st)
 
 // The halo plane is loaded in x-neighbour pairs when nx is even: pairs start
 // at even x, so they never straddle the periodic wrap.
-template <int BX, int BY>
+template <int BX, int BY, bool GRAD = false>
 hipError_t launch_trio(const Consts &c, const StageArgs &s, hipStream_t st)
 {
-    return c.nx % 2 == 0 ? launch_trio_p<BX, BY, true>(c, s, st) : launch_trio_p<BX, BY, false>(c, s, st);
+    return c.nx % 2 == 0 ? launch_trio_p<BX, BY, true, GRAD>(c, s, st) : launch_trio_p<BX, BY, false, GRAD>(c, s, st);
 }
 
 template <int BX, int BY>
@@ -789,7 +925,7 @@ int resident_trio()
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per, reinterpret_cast<const void *>(&trio_stage_kernel<BX, BY, 2, false, true>), 3 * BX * BY, 0) != hipSuccess)
+            &per, reinterpret_cast<const void *>(&trio_stage_kernel<BX, BY, 2, false, true, false>), 3 * BX * BY, 0) != hipSuccess)
         return 0;
     return cus * (per > 0 ? per : 1);
 }
@@ -804,6 +940,11 @@ int trio_resident_blocks(int tile)
     case TILE_16x4_2G: return resident_trio<16, 4>();
     default: return 0;
     }
+}
+
+hipError_t launch_trio_grad(const Consts &c, const StageArgs &s, hipStream_t st)
+{
+    return launch_trio<32, 8, true>(c, s, st);
 }
 
 hipError_t launch_trio_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st)

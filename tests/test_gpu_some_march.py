@@ -1,0 +1,50 @@
+"""The marching form of the intermediate-storage class (grids from 400,000
+points) against the oracle: extents at, one below and one above a tile, odd
+and even, shorter than a tile's width, and the smallest grid it takes.
+
+Tolerances: the parity tests' bars (states 1e-12 of a field's maximum; the
+residual 1e-12 max(1, N/32), its rounding floor growing like 1/h)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ns():
+    import paper_1709_09713_amd as ns
+    assert torch.cuda.is_available()
+    return ns
+
+
+def rel(a, b):
+    scale = [np.abs(b[v]).max() for v in range(5)]
+    scale[1:4] = [max(scale[1:4])] * 3
+    return max(float(np.abs(a[v] - b[v]).max() / scale[v]) for v in range(5))
+
+
+@pytest.mark.parametrize("n", [(80, 80, 63), (33, 9, 1347), (96, 72, 64), (1367, 7, 43), (5, 2000, 41),
+                               (65, 1231, 5)])
+def test_residual_and_steps(ns, n):
+    assert n[0] * n[1] * n[2] >= 400000
+    Q = synth.random_state(n[::-1], seed=n[0] + n[1])
+    ph = oracle.Physics(n=n, reynolds=500.0, mach=0.2)
+    p = ns.make_params(n, reynolds=500.0, mach=0.2)
+    work = torch.empty(ns.ns_workspace_bytes(p, ns.NS_ALGO_SOME, ns.NS_FP64), dtype=torch.uint8, device="cuda")
+    Qd = torch.as_tensor(Q, device="cuda")
+    R = torch.empty_like(Qd)
+    ns.ns_residual(p, ns.NS_ALGO_SOME, Qd, R, work)
+    torch.cuda.synchronize()
+    e = rel(R.cpu().numpy(), oracle.residual(ph, Q))
+    print(f"some march n={n}: residual {e:.2e}", flush=True)
+    assert e < 1e-12 * max(1.0, max(n) / 32.0)
+    dt = 2e-3 * 64.0 / max(n)
+    ns.rk3_step(p, ns.NS_ALGO_SOME, ns.NS_FP64, dt, 2, Qd, work)
+    torch.cuda.synchronize()
+    e = rel(Qd.cpu().numpy(), oracle.rk3(ph, Q, dt, 2))
+    print(f"some march n={n}: state {e:.2e}", flush=True)
+    assert e < 1e-12
