@@ -374,7 +374,10 @@ ns_status ns_residual(const ns_params *p, ns_algo algo, const double *Q, double 
                            default_zchunk(c, NS_FP64, TILE_32x8_2G), s));
         return NS_OK;
     }
-    NS_HIP_OK(stored_residual(c, Q, R, at<double>(work, L.stored), s));
+    StageArgs a = {};
+    a.qin = Q;
+    a.rout = R;
+    NS_HIP_OK(stored_stage(c, a, at<double>(work, L.stored), s));
     return NS_OK;
 }
 
@@ -424,20 +427,24 @@ ns_status rk3_step(const ns_params *p, ns_algo algo, ns_precision prec, double d
     }
 
     // stored-derivative class
-    double *R = at<double>(work, L.R);
-    double *wk = at<double>(work, L.stored);
+    double *D = at<double>(work, L.stored);
     double *q1 = (double *)b1, *q2 = (double *)b2;
     for (int32_t step = 0; step < nsteps; ++step) {
         if (diag_dev) {
             NS_HIP_OK(launch_diag_partials(c, state, partial, s));
             NS_HIP_OK(launch_diag_finalize(c, partial, diag_num_blocks(c), diag_dev + step, s));
         }
-        NS_HIP_OK(stored_residual(c, state, R, wk, s));
-        NS_HIP_OK(launch_rk_update(c, R, state, acc, q1, rk_a(0) * dt, rk_b(0) * dt, s));
-        NS_HIP_OK(stored_residual(c, q1, R, wk, s));
-        NS_HIP_OK(launch_rk_update(c, R, acc, acc, q2, rk_a(1) * dt, rk_b(1) * dt, s));
-        NS_HIP_OK(stored_residual(c, q2, R, wk, s));
-        NS_HIP_OK(launch_rk_update(c, R, acc, nullptr, state, rk_a(2) * dt, 0.0, s));
+        for (int k = 0; k < 3; ++k) {
+            StageArgs a = {};
+            a.qin = k == 0 ? state : k == 1 ? q1 : q2;
+            a.acc_in = acc;
+            a.acc_out = acc;
+            a.qout = k == 0 ? q1 : k == 1 ? q2 : state;
+            a.a_dt = rk_a(k) * dt;
+            a.b_dt = rk_b(k) * dt;
+            a.mode = k + 1;
+            NS_HIP_OK(stored_stage(c, a, D, s));
+        }
     }
     return NS_OK;
 }

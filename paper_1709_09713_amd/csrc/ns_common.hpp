@@ -109,6 +109,23 @@ __device__ __forceinline__ T d1u_x_lanes(T y, T h, int tx)
     return d1u(ym2, ym1, yp1, yp2);
 }
 
+// 1/x from the hardware estimate by two Newton steps r <- r + r (1 - x r), to
+// double rounding error, for positive normal x (a density); and m/x from it
+// with one correction, rounded almost always as the division is.
+__device__ __forceinline__ double recip_f64(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    double e = __builtin_fma(-x, r, 1.0);
+    r = __builtin_fma(r, e, r);
+    e = __builtin_fma(-x, r, 1.0);
+    return __builtin_fma(r, e, r);
+}
+__device__ __forceinline__ double quotient_f64(double m, double x, double inv)
+{
+    const double q = m * inv;
+    return __builtin_fma(__builtin_fma(-q, x, m), inv, q);
+}
+
 // XCD-aware tile order.  The dispatcher hands workgroups to the 8 XCDs
 // round-robin by linear workgroup id, and each XCD has its own L2.  Remap so
 // that XCD k processes the k-th contiguous run of tiles (x fastest, then y,

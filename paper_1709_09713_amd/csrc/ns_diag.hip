@@ -94,17 +94,6 @@ int64_t diag_num_blocks(const Consts &c)
     return (int64_t)g.x * g.y * g.z;
 }
 
-// 1/x by the hardware estimate and two Newton steps (x a density: positive
-// and normal), to double rounding error.
-__device__ __forceinline__ double diag_recip(double x)
-{
-    double r = __builtin_amdgcn_rcp(x);
-    double e = __builtin_fma(-x, r, 1.0);
-    r = __builtin_fma(r, e, r);
-    e = __builtin_fma(-x, r, 1.0);
-    return __builtin_fma(r, e, r);
-}
-
 // Block sum of the seven per-thread sums in a fixed order, into the block's
 // partial record.
 __device__ __forceinline__ void diag_block_sum(double (&s)[7], double *__restrict__ partial, int64_t blin)
@@ -154,7 +143,7 @@ diag_point_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ p
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int64_t at = idx + (int64_t)(wrap1(co[d] + off[q], nn[d]) - co[d]) * st[d];
-                const double inv = diag_recip(Q[at]);
+                const double inv = recip_f64(Q[at]);
 #pragma unroll
                 for (int e = 0; e < 2; ++e) t[e][q] = Q[(1 + (d + 1 + e) % 3) * N + at] * inv;
             }
@@ -237,13 +226,13 @@ diag_march_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ p
     for (int zp = z0 - 2; zp < z1 + 2; ++zp) {
         const int b = (zp - z0) & 1;
         const double rho = p0[0], m0 = p0[1], m1 = p0[2], m2 = p0[3], E = p0[4];
-        const double inv = diag_recip(rho);
+        const double inv = recip_f64(rho);
         const double u = m0 * inv, v = m1 * inv, w = m2 * inv;
         lu[b][ty + 2][tx] = u;
         lv[b][ty][tx + 2] = v;
         lw[b][ty + 2][tx + 2] = w;
         if (yhalo || xhalo) {
-            const double hinv = diag_recip(ph[0]);
+            const double hinv = recip_f64(ph[0]);
             if (yhalo)
                 lu[b][hy][hx - 2] = ph[1] * hinv;
             else

@@ -98,10 +98,8 @@ size_t rs_workspace_doubles(const Consts &c);
 hipError_t rs_stage(const Consts &c, const double *qin, double *G, const double *acc_in,
                     double *acc_out, double *qout, double *rout, double a_dt, double b_dt,
                     int mode, int zchunk, hipStream_t st);
-hipError_t stored_residual(const Consts &c, const double *Q, double *R, double *work,
-                           hipStream_t st);
-hipError_t launch_rk_update(const Consts &c, const double *R, const double *acc_in,
-                            double *acc_out, double *qout, double a_dt, double b_dt,
-                            hipStream_t st);
+// One stage: the 60 derivative arrays into D, then residual and RK update
+// (s as for the fused kernel; s.mode 0 writes R to s.rout).
+hipError_t stored_stage(const Consts &c, const StageArgs &s, double *D, hipStream_t st);
 
 }  // namespace ns

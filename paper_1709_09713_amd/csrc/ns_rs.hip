@@ -20,17 +20,6 @@ namespace {
 
 constexpr int RS_BX = 32, RS_BY = 8, RS_NT = RS_BX * RS_BY;
 
-// 1/x: hardware estimate and two Newton steps, to double rounding error (x a
-// density: positive and normal).
-__device__ __forceinline__ double rs_recip(double x)
-{
-    double r = __builtin_amdgcn_rcp(x);
-    double e = __builtin_fma(-x, r, 1.0);
-    r = __builtin_fma(r, e, r);
-    e = __builtin_fma(-x, r, 1.0);
-    return __builtin_fma(r, e, r);
-}
-
 // A block owns a 32 x 8 column tile and marches along z: each plane's
 // velocities go through LDS for the x and y gradients, which are stored in
 // the plane's step; the z gradients of plane zp - 2 come from a ring of five
@@ -90,17 +79,17 @@ rs_gradient_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ 
     load(z0 - 2);
     for (int zp = z0 - 2; zp < z1 + 2; ++zp) {
         const int b = (zp - z0) & 1;
-        const double inv = rs_recip(po[0]);
+        const double inv = recip_f64(po[0]);
         double u[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            u[a] = po[1 + a] * inv;
+            u[a] = quotient_f64(po[1 + a], po[0], inv);
             lu[b][a][ty + 2][tx + 2] = u[a];
         }
         if (halo) {
-            const double hinv = rs_recip(ph[0]);
+            const double hinv = recip_f64(ph[0]);
 #pragma unroll
-            for (int a = 0; a < 3; ++a) lu[b][a][hy][hx] = ph[1 + a] * hinv;
+            for (int a = 0; a < 3; ++a) lu[b][a][hy][hx] = quotient_f64(ph[1 + a], ph[0], hinv);
         }
         lds_barrier();
         if (zp + 1 < z1 + 2) load(zp + 1);
