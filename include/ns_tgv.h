@@ -206,8 +206,11 @@ ns_status ns_stage_stream(const ns_params *p, int32_t stage, double *state, void
  * z planes one block marches through (>= 1; 0 = automatic: the length that
  * minimises (rounds of device-resident blocks) x (planes each block
  * marches, chunk + 4 halo planes; + 5 for tiles 8-10)).  tile = -1
- * restores the automatic choice: tile 9 for NS_FP64, tile 0 for
- * NS_FP32_STORE.  For a given tile, residuals and states are bitwise
+ * restores the automatic choice: for NS_FP64 tile 9, or tile 8 where the grid
+ * leaves compute units idle, or, with zchunk 0 and grids of up to one 8x4x4
+ * brick per compute unit (32^3), a kernel that stages whole bricks instead of
+ * marching (all three give the same bits; per-step diagnostics differ in the
+ * order of their sums); tile 0 for NS_FP32_STORE.  For a given tile, residuals and states are bitwise
  * independent of zchunk (tiles 8-10 also of the tile among them); different tiles are separate compiled
  * instances and may differ at the rounding level (the compiler can contract
  * a multiply-add differently); per-step diagnostics also differ in the
@@ -216,7 +219,8 @@ ns_status ns_stage_stream(const ns_params *p, int32_t stage, double *state, void
 ns_status ns_set_fused_config(int32_t tile, int32_t zchunk);
 
 /* The (tile, zchunk) the fused kernel would use for p and prec in a call
- * made now by the calling thread. */
+ * made now by the calling thread (of a grid that takes the brick kernel, the
+ * marching shape that gives the same residuals and states). */
 ns_status ns_get_fused_config(const ns_params *p, ns_precision prec,
                               int32_t *tile, int32_t *zchunk);
 

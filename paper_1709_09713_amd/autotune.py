@@ -32,7 +32,9 @@ class Autotuner:
     def __init__(self, cache_path: str | None = None, tiles=None, zchunks=DEFAULT_ZCHUNKS,
                  steps: int = 3, reps: int = 3):
         self.cache_path = cache_path
-        self.tiles = tuple(nat.TILES) if tiles is None else tuple(tiles)
+        # -1 with chunk 0: the library's own choice, which on small FP64 grids
+        # is a kernel that no tile names
+        self.tiles = (-1, *nat.TILES) if tiles is None else tuple(tiles)
         self.zchunks = tuple(zchunks)
         self.steps = steps
         self.reps = reps
@@ -69,7 +71,7 @@ class Autotuner:
         t_wall = time.perf_counter()
         for tile in self.tiles:
             for zc in self.zchunks:
-                if zc and zc > n[2]:
+                if zc and (zc > n[2] or tile < 0):
                     continue
                 b = Batch(1, precision, nstreams=1)
                 try:
@@ -94,7 +96,8 @@ class Autotuner:
         timings.sort()
         best, tile, zc = timings[0]
         dtile = nat.ns_get_fused_config(p, nat.PRECS[precision])[0]
-        dflt = [t for t, tl, z in timings if z == 0 and tl == dtile]
+        dflt = ([t for t, tl, z in timings if tl < 0]
+                or [t for t, tl, z in timings if z == 0 and tl == dtile])
         return {"tile": tile, "zchunk": zc, "ms_per_step": best,
                 "default_ms_per_step": dflt[0] if dflt else None,
                 "candidates": len(timings), "tune_seconds": time.perf_counter() - t_wall,

@@ -46,18 +46,15 @@ static thread_local int g_zchunk = 0;
 static thread_local int g_order = 0;
 
 // Default z-chunk: a block marches zchunk + 4 planes (+ 5 for the
-// tiles 8-10), and the grid runs in ceil(blocks / resident) rounds of resident
-// blocks, so the time of a stage goes as rounds x padded planes.  Pick the
-// number of chunks along z that minimises it (fewest blocks on a tie).
-// resident = blocks the device holds at once (512 on MI355X for the default
-// tiles); when it cannot be queried, 512 is assumed.
-static int default_zchunk(const Consts &c, ns_precision prec, int tile)
+// tiles 8-10), and the grid runs in ceil(blocks / resident) rounds of
+// resident blocks, so the time of a stage goes as rounds x planes.  Pick the
+// number of chunks along z that minimises it (fewest blocks on a tie), and
+// return that cost too.
+static int zchunk_for(const Consts &c, int tile, int64_t resident, int64_t *cost_out)
 {
     int bx, by;
     tile_dims(tile, &bx, &by);
     const int64_t nxy = (int64_t)((c.nx + bx - 1) / bx) * ((c.ny + by - 1) / by);
-    int64_t resident = fused_resident_blocks(prec, tile);
-    if (resident <= 0) resident = 512;
     int best_z = c.nz;
     int64_t best_cost = -1;
     for (int k = 1; k <= c.nz / kMinZChunk; ++k) {
@@ -72,7 +69,53 @@ static int default_zchunk(const Consts &c, ns_precision prec, int tile)
             best_z = z;
         }
     }
+    if (cost_out) *cost_out = best_cost;
     return best_z;
+}
+
+// Blocks of a tile that the device holds at once (512 on MI355X for the
+// one-thread tiles of FP32 storage, 256 for 32x8 in three groups); when the
+// device cannot be queried, 512 is assumed.
+static int64_t resident_blocks(ns_precision prec, int tile)
+{
+    const int r = fused_resident_blocks(prec, tile);
+    return r > 0 ? r : 512;
+}
+
+static int default_zchunk(const Consts &c, ns_precision prec, int tile)
+{
+    return zchunk_for(c, tile, resident_blocks(prec, tile), nullptr);
+}
+
+// Compute units of the current device: the blocks it holds of the 32x8
+// three-group kernel, one each.
+static int64_t compute_units()
+{
+    const int r = fused_resident_blocks(NS_FP64, TILE_32x8_2G);
+    return r > 0 ? r : 256;
+}
+
+// FP64 on grids that leave most compute units with one block: a plane of a
+// 16x8 block takes about two thirds of the time of a plane of a 32x8 block,
+// so the narrow tile is faster where one block per compute unit and its longer
+// chunks still come to less.  Measured, 16x8 | 32x8, us per RK3 step: 48^3
+// 33.2 | 38.9, 56^3 43.3 | 46.9, 64^3 49.3 | 50.5, 80^3 77.0 | 81.2, 88^3
+// 116.9 | 98.5, 96^3 129.0 | 106.8, 101x77x53 83.1 | 77.0, 200x20x20 33.6 |
+// 36.0.  Both give the same bits.
+static int default_fp64_tile(const Consts &c, int *zchunk)
+{
+    const int64_t cus = compute_units();
+    int64_t narrow, wide;
+    const int z9 = zchunk_for(c, TILE_32x8_2G, cus, &wide);
+    if (fused_num_blocks(c, TILE_16x8_2G, c.nz) <= cus) {
+        const int z8 = zchunk_for(c, TILE_16x8_2G, cus, &narrow);
+        if (fused_num_blocks(c, TILE_16x8_2G, z8) <= cus && 2 * narrow < 3 * wide) {
+            *zchunk = z8;
+            return TILE_16x8_2G;
+        }
+    }
+    *zchunk = z9;
+    return TILE_32x8_2G;
 }
 
 // Launch shape: an explicit tile (>= 0) / zchunk (> 0) wins, else the
@@ -84,9 +127,14 @@ static void choose_config(const Consts &c, ns_precision prec, int tile_in, int z
     int z = tile_in >= 0 ? zchunk_in : g_zchunk;
     if (zchunk_in > 0) z = zchunk_in;
     // defaults measured on MI355X: FP64 runs fastest with the three-group
-    // 32x8 kernel on grids from 48^3 to 512^3, FP32 storage with the
-    // one-thread 32x8 kernel
-    if (t < 0 || t >= TILE_COUNT) t = (prec == NS_FP64) ? TILE_32x8_2G : TILE_32x8;
+    // kernel on grids from 40^3 to 512^3, FP32 storage with the one-thread
+    // 32x8 kernel
+    if (t < 0 || t >= TILE_COUNT) {
+        if (prec == NS_FP64 && z <= 0)
+            t = default_fp64_tile(c, &z);
+        else
+            t = (prec == NS_FP64) ? TILE_32x8_2G : TILE_32x8;
+    }
     if (z <= 0) z = default_zchunk(c, prec, t);
     if (z < kMinZChunk) z = kMinZChunk;
     if (z > c.nz) z = c.nz;
@@ -97,6 +145,19 @@ static void choose_config(const Consts &c, ns_precision prec, int tile_in, int z
 static void choose_config(const Consts &c, ns_precision prec, int *tile, int *zchunk)
 {
     choose_config(c, prec, -1, 0, tile, zchunk);
+}
+
+// The brick kernel runs small FP64 grids whose launch shape is left to the
+// library (no tile, z-chunk or order asked for by the call or the thread):
+// those that fit the device with one brick per compute unit.  Measured, brick
+// | best march, us per RK3 step: 16^3 16.8 | 21.4, 24^3 17.3 | 22.3, 32^3 (256
+// bricks) 18.4 | 23.5, 36^3 (405) 30.0 | 29.7, 48^3 (864) 53.6 | 33.2.  Its
+// blocks never outnumber those of the one-plane 8x8 march, for which the
+// diagnostic partials of the workspace are sized.
+static bool choose_brick(const Consts &c, ns_precision prec, int tile_in, int zchunk_in)
+{
+    const bool automatic = tile_in < 0 && zchunk_in <= 0 && g_tile < 0 && g_zchunk <= 0 && g_order == 0;
+    return automatic && prec == NS_FP64 && brick_num_blocks(c) <= compute_units();
 }
 
 static int64_t max_partial_blocks(const Consts &c)
@@ -214,7 +275,8 @@ ns_status make_fused_plan(const ns_params *p, ns_precision prec, int tile, int z
     choose_config(c, prec, tile, zchunk, &f.tile, &f.zchunk);
     f.order = g_order;
     if (!fused_order_supported(f.tile, f.order)) return NS_ERR_UNSUPPORTED;
-    f.nblk = fused_num_blocks(c, f.tile, f.zchunk);
+    f.brick = choose_brick(c, prec, tile, zchunk);
+    f.nblk = f.brick ? brick_num_blocks(c) : fused_num_blocks(c, f.tile, f.zchunk);
     f.state = state;
     f.partial = at<double>(work, L.partial);
     f.acc = at<double>(work, L.acc);
@@ -230,6 +292,9 @@ ns_status make_fused_plan(const ns_params *p, ns_precision prec, int tile, int z
 // accumulator in place, stage 3 b2 -> Q^{n+1} in the state buffer.
 hipError_t enqueue_fused_step(const FusedPlan &f, double dt, ns_diag *diag_out, hipStream_t s)
 {
+    auto launch = [&](const StageArgs &a) {
+        return f.brick ? launch_brick_stage(f.c, a, s) : launch_fused_stage(f.c, a, f.prec, f.tile, s);
+    };
     StageArgs a = {};
     a.zchunk = f.zchunk;
     a.order = f.order;
@@ -240,7 +305,7 @@ hipError_t enqueue_fused_step(const FusedPlan &f, double dt, ns_diag *diag_out, 
     a.b_dt = rk_b(0) * dt;
     a.mode = 1;
     a.diag_partial = diag_out ? f.partial : nullptr;
-    hipError_t e = launch_fused_stage(f.c, a, f.prec, f.tile, s);
+    hipError_t e = launch(a);
     if (e != hipSuccess) return e;
     if (diag_out) {
         e = launch_diag_finalize(f.c, f.partial, f.nblk, diag_out, s);
@@ -254,7 +319,7 @@ hipError_t enqueue_fused_step(const FusedPlan &f, double dt, ns_diag *diag_out, 
     a.b_dt = rk_b(1) * dt;
     a.mode = 2;
     a.diag_partial = nullptr;
-    e = launch_fused_stage(f.c, a, f.prec, f.tile, s);
+    e = launch(a);
     if (e != hipSuccess) return e;
     a.qin = f.b2;
     a.acc_in = f.acc;
@@ -263,7 +328,7 @@ hipError_t enqueue_fused_step(const FusedPlan &f, double dt, ns_diag *diag_out, 
     a.a_dt = rk_a(2) * dt;
     a.b_dt = 0.0;
     a.mode = 3;
-    return launch_fused_stage(f.c, a, f.prec, f.tile, s);
+    return launch(a);
 }
 
 }  // namespace ns
@@ -363,7 +428,8 @@ ns_status ns_residual(const ns_params *p, ns_algo algo, const double *Q, double 
         a.rout = R;
         a.mode = 0;
         a.zchunk = zc;
-        NS_HIP_OK(launch_fused_stage(c, a, NS_FP64, tile, s));
+        NS_HIP_OK(choose_brick(c, NS_FP64, -1, 0) ? launch_brick_stage(c, a, s)
+                                                  : launch_fused_stage(c, a, NS_FP64, tile, s));
         return NS_OK;
     }
     const Layout L = layout(c, algo, NS_FP64);

@@ -1,0 +1,409 @@
+// ns_brick.hip -- the fused FP64 stage kernel for small grids.
+//
+// The marching kernels step through at least five planes one after another,
+// each with a barrier and, on a small grid that cannot hide it, a wait for
+// memory: about 5 us a stage at 16^3 whose data would take 0.1 us.  Here a
+// block owns a brick of 8 x 4 x 4 points and stages it whole, with its halo
+// of two, in one round of loads; then three groups of waves evaluate the
+// equations of one point per thread as the groups of ns_trio.hip do (A mass
+// and energy, B momentum and heat conduction, C viscous terms), with the same
+// expressions in the same order, so that the result is the same bit for bit.
+// Three barriers in all: after the staging, after the in-plane gradients that
+// are differentiated along z, and before A and B take over C's values.
+//
+// Bound by latency: of 5.6 us a stage at 16^3 (16.8 us an RK3 step, the
+// march's best shape 21.4), 1.7 us are an empty launch of a chain; one round
+// of loads, one thread's share of the arithmetic (about 140 double
+// operations) and the barriers are the rest.  The price is the halo, six
+// staged points per point of the brick, so grids of more bricks than compute
+// units are left to the march.
+#include "ns_common.hpp"
+#include "ns_fp64.hpp"
+#include "ns_kernels.hpp"
+
+namespace ns {
+
+namespace {
+
+constexpr int BRX = 8, BRY = 4, BRZ = 4;
+
+}  // namespace
+
+template <int MODE, bool DIAG>
+__global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts c, Coef64 k, StageArgs s)
+{
+#pragma clang fp contract(on)
+    static_assert(!DIAG || MODE == 1, "diagnostics of the step's input state are taken in stage 1");
+    constexpr int HX = BRX + 4, HY = BRY + 4, HZ = BRZ + 4, HP = HX * HY, CELLS = HP * HZ;
+    constexpr int NT = BRX * BRY * BRZ, NLOAD = (CELLS + 3 * NT - 1) / (3 * NT);
+    constexpr int GP = BRX * BRY, GC = GP * HZ;      // own columns with their z halo
+    constexpr int NW = 3 * NT / 64;
+    static_assert(NT % 64 == 0, "each group must be whole waves");
+    static_assert(GC <= 3 * NT, "one gradient point per thread");
+    // staged fields: rho - 1, rho u_i, E - E_ref, u, v, w, p - p_ref, T - 1
+    enum { L_R, L_M0, L_M1, L_M2, L_E, L_U, L_V, L_W, L_P, L_T, NF };
+    enum { G_A, G_B, G_C, NG };                      // D_x u + D_y v, D_x w, D_y w
+    enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_HEAT, H_OZ, H_OX, H_OY };
+    __shared__ double lds[NF][CELLS];
+    __shared__ double grad[NG][GC];
+    __shared__ double vbuf[DIAG ? 9 : 6][NT];
+    __shared__ double red[DIAG ? NW : 1][kDiag];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = wave / (NT / 64);
+    const int pt = tid - grp * NT;
+    const int tx = pt % BRX, ty = (pt / BRX) % BRY, tz = pt / GP;
+    int tbx, tby, tbz;
+    xcd_tile(&tbx, &tby, &tbz);
+    const int x0 = tbx * BRX, y0 = tby * BRY, z0 = tbz * BRZ;
+    const bool active = x0 + tx < c.nx && y0 + ty < c.ny && z0 + tz < c.nz;
+    const int own = (tz + 2) * HP + (ty + 2) * HX + tx + 2;
+    const int64_t N = c.N;
+    const int64_t pidx = active ? ((int64_t)(z0 + tz) * c.ny + y0 + ty) * c.nx + x0 + tx : 0;
+    const double *qin = (const double *)s.qin;
+    const double *accsrc = (MODE >= 2) ? s.acc_in : qin;
+    const double c1x = c.c1[0], c1y = c.c1[1], c1z = c.c1[2];
+    const double c2x = c.c2[0], c2y = c.c2[1], c2z = c.c2[2];
+
+    // ---- stage the brick with its halo (wrapped: valid memory everywhere)
+    double q[NLOAD][5];
+#pragma unroll
+    for (int r = 0; r < NLOAD; ++r) {
+        const int cell = min(tid + r * 3 * NT, CELLS - 1);
+        int xx = (x0 + cell % HX - 2) % c.nx, yy = (y0 + (cell / HX) % HY - 2) % c.ny;
+        int zz = (z0 + cell / HP - 2) % c.nz;
+        if (xx < 0) xx += c.nx;
+        if (yy < 0) yy += c.ny;
+        if (zz < 0) zz += c.nz;
+        const double *src = qin + ((int64_t)zz * c.ny + yy) * c.nx + xx;
+#pragma unroll
+        for (int f = 0; f < 5; ++f) q[r][f] = src[f * N];
+    }
+    // accumulator of the own point: group A the mass and energy, B the momenta
+    double acc[3] = {0.0, 0.0, 0.0};
+    if constexpr (MODE >= 1) {
+        if (grp == 0) {
+            acc[0] = accsrc[pidx];
+            acc[1] = accsrc[4 * N + pidx];
+        } else if (grp == 1) {
+#pragma unroll
+            for (int f = 0; f < 3; ++f) acc[f] = accsrc[(1 + f) * N + pidx];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < NLOAD; ++r) {
+        const int cell = tid + r * 3 * NT;
+        if (CELLS % (3 * NT) != 0 && cell >= CELLS) continue;
+        const double rho = q[r][0], m0 = q[r][1], m1 = q[r][2], m2 = q[r][3];
+        const double E = q[r][4] - c.rhoE_ref;
+        const double inv = recip_f64(rho);
+        const double u = m0 * inv, v = m1 * inv, w = m2 * inv;
+        const double p = c.gm1 * (E - 0.5 * (m0 * u + m1 * v + m2 * w));
+        const double rd = rho - 1.0;
+        lds[L_R][cell] = rd;
+        lds[L_M0][cell] = m0;
+        lds[L_M1][cell] = m1;
+        lds[L_M2][cell] = m2;
+        lds[L_E][cell] = E;
+        lds[L_U][cell] = u;
+        lds[L_V][cell] = v;
+        lds[L_W][cell] = w;
+        lds[L_P][cell] = p;
+        lds[L_T][cell] = (c.gM2 * p - rd) * inv;
+    }
+    lds_barrier();
+
+#define AT(f, at) lds[f][at]
+#define LV(f, dz, dy, dx) lds[f][own + (dz) * HP + (dy) * HX + (dx)]
+#define TAPS_X(t, f) const double t[4] = {LV(f, 0, 0, -2), LV(f, 0, 0, -1), LV(f, 0, 0, 1), LV(f, 0, 0, 2)}
+#define TAPS_Y(t, f) const double t[4] = {LV(f, 0, -2, 0), LV(f, 0, -1, 0), LV(f, 0, 1, 0), LV(f, 0, 2, 0)}
+#define TAPS_Z(t, f) const double t[4] = {LV(f, -2, 0, 0), LV(f, -1, 0, 0), LV(f, 1, 0, 0), LV(f, 2, 0, 0)}
+#define D1T(t) d1(t[0], t[1], t[2], t[3])
+#define D2T(t, t0) d2(t[0], t[1], t0, t[2], t[3])
+#define HALF_SUMS(s, u0, t, w4, wh)                                                               \
+    const double s[4] = {(wh) * ((u0) + t[0]), (w4) * ((u0) + t[1]), (w4) * ((u0) + t[2]), (wh) * ((u0) + t[3])}
+
+    // ---- in-plane gradients of the own columns with their z halo
+    if (tid < GC) {
+        const int at = (tid / GP) * HP + ((tid % GP) / BRX + 2) * HX + tid % BRX + 2;
+        const double ux = d1(AT(L_U, at - 2), AT(L_U, at - 1), AT(L_U, at + 1), AT(L_U, at + 2));
+        const double vy = d1(AT(L_V, at - 2 * HX), AT(L_V, at - HX), AT(L_V, at + HX), AT(L_V, at + 2 * HX));
+        const double wx = d1(AT(L_W, at - 2), AT(L_W, at - 1), AT(L_W, at + 1), AT(L_W, at + 2));
+        const double wy = d1(AT(L_W, at - 2 * HX), AT(L_W, at - HX), AT(L_W, at + HX), AT(L_W, at + 2 * HX));
+        const double gxx = c1x * ux, gyy = c1y * vy;
+        grad[G_A][tid] = gxx + gyy;
+        grad[G_B][tid] = c1x * wx;
+        grad[G_C][tid] = c1y * wy;
+    }
+    lds_barrier();
+
+    double R[3] = {0.0, 0.0, 0.0};
+    if (grp == 0) {
+        // ------------------------------------------------------------ group A
+        const double r = LV(L_R, 0, 0, 0), E = LV(L_E, 0, 0, 0), w = LV(L_W, 0, 0, 0);
+        const double p = LV(L_P, 0, 0, 0), u = LV(L_U, 0, 0, 0), v = LV(L_V, 0, 0, 0);
+        double rm = 0.0, re = 0.0;
+        {
+            TAPS_X(ut, L_U);
+            TAPS_X(rt, L_R);
+            TAPS_X(et, L_E);
+            TAPS_X(pt4, L_P);
+            HALF_SUMS(su, u, ut, k.x4, k.xh);
+            rm = conv(rm, r, rt, su);
+            re = conv(re, E, et, su);
+            re = __builtin_fma(-c1x, d1_prod(pt4, ut), re);
+        }
+        {
+            TAPS_Y(vt, L_V);
+            TAPS_Y(rt, L_R);
+            TAPS_Y(et, L_E);
+            TAPS_Y(pt4, L_P);
+            HALF_SUMS(sv, v, vt, k.y4, k.yh);
+            rm = conv(rm, r, rt, sv);
+            re = conv(re, E, et, sv);
+            re = __builtin_fma(-c1y, d1_prod(pt4, vt), re);
+        }
+        {
+            // fluxes between the point's plane and the two below and above,
+            // added in the march's order
+            TAPS_Z(wt, L_W);
+            TAPS_Z(rt, L_R);
+            TAPS_Z(et, L_E);
+            TAPS_Z(pz, L_P);
+            const double q0 = p * w;
+            double mf[4], ef[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const double qt = pz[t] * wt[t];
+                const double st = (t == 1 || t == 2 ? k.z4 : k.zh) * (w + wt[t]);
+                mf[t] = (r + rt[t]) * st;
+                ef[t] = (E + et[t]) * st + (t == 1 || t == 2 ? k.z8 : c1z) * (q0 + qt);
+            }
+            rm = rm + (mf[1] - mf[0]);
+            rm -= mf[2];
+            rm += mf[3];
+            re = re + (ef[1] - ef[0]);
+            re -= ef[2];
+            re += ef[3];
+        }
+        R[0] = rm;
+        R[1] = re;
+    } else if (grp == 1) {
+        // ------------------------------------------------------------ group B
+        const double m[3] = {LV(L_M0, 0, 0, 0), LV(L_M1, 0, 0, 0), LV(L_M2, 0, 0, 0)};
+        const double u = LV(L_U, 0, 0, 0), v = LV(L_V, 0, 0, 0), w = LV(L_W, 0, 0, 0);
+        const double p = LV(L_P, 0, 0, 0), T = LV(L_T, 0, 0, 0);
+        double he, px, py, rr[3];
+        {
+            TAPS_X(ut, L_U);
+            TAPS_X(m0t, L_M0);
+            TAPS_X(m1t, L_M1);
+            TAPS_X(m2t, L_M2);
+            TAPS_X(tt, L_T);
+            TAPS_X(pt4, L_P);
+            HALF_SUMS(su, u, ut, k.x4, k.xh);
+            he = k.kx * D2T(tt, T);
+            rr[0] = conv(0.0, m[0], m0t, su);
+            rr[1] = conv(0.0, m[1], m1t, su);
+            rr[2] = conv(0.0, m[2], m2t, su);
+            px = c1x * D1T(pt4);
+        }
+        {
+            TAPS_Y(vt, L_V);
+            TAPS_Y(m0t, L_M0);
+            TAPS_Y(m1t, L_M1);
+            TAPS_Y(m2t, L_M2);
+            TAPS_Y(tt, L_T);
+            TAPS_Y(pt4, L_P);
+            HALF_SUMS(sv, v, vt, k.y4, k.yh);
+            he += k.ky * D2T(tt, T);
+            rr[0] = conv(rr[0], m[0], m0t, sv);
+            rr[1] = conv(rr[1], m[1], m1t, sv);
+            rr[2] = conv(rr[2], m[2], m2t, sv);
+            py = c1y * D1T(pt4);
+        }
+        {
+            TAPS_Z(wt, L_W);
+            TAPS_Z(tt, L_T);
+            TAPS_Z(pz, L_P);
+            double sz[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) sz[t] = (t == 1 || t == 2 ? k.z4 : k.zh) * (w + wt[t]);
+#pragma unroll
+            for (int f = 0; f < 3; ++f) {
+                TAPS_Z(mt, L_M0 + f);
+                double fl[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    fl[t] = (m[f] + mt[t]) * sz[t];
+                    if (f == 2) fl[t] = __builtin_fma(t == 1 || t == 2 ? k.z8 : c1z, p + pz[t], fl[t]);
+                }
+                double ra = rr[f] + (fl[1] - fl[0]);
+                if (f == 0) ra -= px;
+                if (f == 1) ra -= py;
+                ra -= fl[2];
+                ra += fl[3];
+                R[f] = ra;
+            }
+            double hf[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                // from the lower to the upper plane of the pair
+                const double dT = t < 2 ? T - tt[t] : tt[t] - T;
+                hf[t] = (t == 1 || t == 2 ? k.kz16 : k.kz) * dT;
+            }
+            double rh = he - (hf[1] - hf[0]);
+            rh += hf[2];
+            rh -= hf[3];
+            vbuf[H_HEAT][pt] = rh;
+        }
+    } else {
+        // ------------------------------------------------------------ group C
+        const int gat = (tz + 2) * GP + ty * BRX + tx;
+        const int hx = (tx < 2) ? -2 : (tx >= BRX - 2 ? 2 : 0);
+        double phi, r0, r1, r2, a, bb, cc, oz;
+        const double u = LV(L_U, 0, 0, 0), v = LV(L_V, 0, 0, 0), w = LV(L_W, 0, 0, 0);
+        {
+            TAPS_X(ux, L_U);
+            TAPS_Y(uy, L_U);
+            TAPS_X(vx, L_V);
+            TAPS_Y(vy, L_V);
+            TAPS_X(wx, L_W);
+            TAPS_Y(wy, L_W);
+            const double hu4[4] = {LV(L_U, 0, -2, hx), LV(L_U, 0, -1, hx), LV(L_U, 0, 1, hx), LV(L_U, 0, 2, hx)};
+            const double hv4[4] = {LV(L_V, 0, -2, hx), LV(L_V, 0, -1, hx), LV(L_V, 0, 1, hx), LV(L_V, 0, 2, hx)};
+            const double dyu = D1T(uy), dyv = D1T(vy);
+            const double Gxx = c1x * D1T(ux), Gxy = c1y * dyu;
+            const double Gyx = c1x * D1T(vx), Gyy = c1y * dyv;
+            r0 = k.vx * D2T(ux, u) + c2y * D2T(uy, u);
+            r1 = k.mxy * d1u_x_lanes<BRX>(dyu, D1T(hu4), tx);
+            r1 += c2x * D2T(vx, v) + k.vy * D2T(vy, v);
+            r0 += k.mxy * d1u_x_lanes<BRX>(dyv, D1T(hv4), tx);
+            phi = 2.0 * (Gxx * Gxx + Gyy * Gyy) + Gxy * Gxy + Gyx * Gyx + 2.0 * Gxy * Gyx;
+            const double Gzx = c1x * D1T(wx), Gzy = c1y * D1T(wy);
+            r2 = c2x * D2T(wx, w) + c2y * D2T(wy, w);
+            phi += Gzx * Gzx + Gzy * Gzy;
+            a = Gxx + Gyy;
+            bb = Gzx;
+            cc = Gzy;
+            oz = Gyx - Gxy;
+        }
+        TAPS_Z(uz, L_U);
+        TAPS_Z(vz, L_V);
+        TAPS_Z(wz, L_W);
+#define GZ(f) d1(grad[f][gat - 2 * GP], grad[f][gat - GP], grad[f][gat + GP], grad[f][gat + 2 * GP])
+        const double Gxz = c1z * D1T(uz), Gyz = c1z * D1T(vz), Gzz = c1z * D1T(wz);
+        const double Vx = r0 + (c2z * D2T(uz, u) + k.mz * GZ(G_B));
+        const double Vy = r1 + (c2z * D2T(vz, v) + k.mz * GZ(G_C));
+        const double Vz = r2 + (k.vz * D2T(wz, w) + k.mz * GZ(G_A));
+#undef GZ
+        const double div = a + Gzz;
+        const double phz = Gxz * Gxz + Gyz * Gyz + 2.0 * Gzz * Gzz
+                           + 2.0 * (Gxz * bb + Gyz * cc) - (2.0 / 3.0) * div * div;
+        vbuf[H_VX][pt] = Vx;
+        vbuf[H_VY][pt] = Vy;
+        vbuf[H_VZ][pt] = Vz;
+        vbuf[H_EN][pt] = c.inv_re * (u * Vx + v * Vy + w * Vz + (phi + phz)) - c.H_ref * div;
+        vbuf[H_DIV][pt] = div;
+        if constexpr (DIAG) {
+            vbuf[H_OZ][pt] = oz;
+            vbuf[H_OX][pt] = cc - Gyz;
+            vbuf[H_OY][pt] = Gxz - bb;
+        }
+    }
+    lds_barrier();
+
+    // ---- C's part of the equations, RK update, output
+    double dsum[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (grp < 2 && active) {
+        if (grp == 0) {
+            R[0] = R[0] - vbuf[H_DIV][pt];
+            R[1] = R[1] + (vbuf[H_EN][pt] + vbuf[H_HEAT][pt]);
+        } else {
+#pragma unroll
+            for (int f = 0; f < 3; ++f) R[f] = R[f] + c.inv_re * vbuf[H_VX + f][pt];
+        }
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            if (grp == 0 && f == 2) continue;
+            const int field = grp == 0 ? 4 * f : 1 + f;
+            const int64_t at = field * N + pidx;
+            if constexpr (MODE == 0) {
+                s.rout[at] = R[f];
+            } else {
+                ((double *)s.qout)[at] = acc[f] + s.a_dt * R[f];
+                if constexpr (MODE < 3) s.acc_out[at] = acc[f] + s.b_dt * R[f];
+            }
+        }
+        if constexpr (DIAG) {
+            if (grp == 0) {
+                const double hr = 0.5 * (1.0 + LV(L_R, 0, 0, 0));
+                const double ox = vbuf[H_OX][pt], oy = vbuf[H_OY][pt], oz = vbuf[H_OZ][pt];
+                dsum[0] = acc[0];
+                dsum[4] = acc[1];
+                dsum[6] = hr * (ox * ox + oy * oy + oz * oz);
+            } else {
+                dsum[1] = acc[0];
+                dsum[2] = acc[1];
+                dsum[3] = acc[2];
+                dsum[5] = 0.5 * (LV(L_M0, 0, 0, 0) * LV(L_U, 0, 0, 0) + LV(L_M1, 0, 0, 0) * LV(L_V, 0, 0, 0)
+                                 + LV(L_M2, 0, 0, 0) * LV(L_W, 0, 0, 0));
+            }
+        }
+    }
+#undef AT
+#undef LV
+#undef TAPS_X
+#undef TAPS_Y
+#undef TAPS_Z
+#undef D1T
+#undef D2T
+#undef HALF_SUMS
+
+    if constexpr (DIAG) {
+        // block sum of the diagnostics in a fixed order
+#pragma unroll
+        for (int d = 0; d < 7; ++d) {
+            double vsum = dsum[d];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) vsum += __shfl_xor(vsum, off, 64);
+            if ((tid & 63) == 0) red[tid >> 6][d] = vsum;
+        }
+        lds_barrier();
+        if (tid < 7) {
+            double t = 0.0;
+            for (int wv = 0; wv < NW; ++wv) t += red[wv][tid];
+            const int64_t blin = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+            s.diag_partial[blin * kDiag + tid] = t;
+            if (tid == 0) s.diag_partial[blin * kDiag + 7] = 0.0;
+        }
+    }
+}
+
+int64_t brick_num_blocks(const Consts &c)
+{
+    return (int64_t)((c.nx + BRX - 1) / BRX) * ((c.ny + BRY - 1) / BRY) * ((c.nz + BRZ - 1) / BRZ);
+}
+
+hipError_t launch_brick_stage(const Consts &c, const StageArgs &s, hipStream_t st)
+{
+    const dim3 block(3 * BRX * BRY * BRZ);
+    const dim3 grid((c.nx + BRX - 1) / BRX, (c.ny + BRY - 1) / BRY, (c.nz + BRZ - 1) / BRZ);
+    const Coef64 k = make_coef64(c);
+    switch (s.mode) {
+    case 0: hipLaunchKernelGGL((brick_stage_kernel<0, false>), grid, block, 0, st, c, k, s); break;
+    case 1:
+        if (s.diag_partial != nullptr)
+            hipLaunchKernelGGL((brick_stage_kernel<1, true>), grid, block, 0, st, c, k, s);
+        else
+            hipLaunchKernelGGL((brick_stage_kernel<1, false>), grid, block, 0, st, c, k, s);
+        break;
+    case 2: hipLaunchKernelGGL((brick_stage_kernel<2, false>), grid, block, 0, st, c, k, s); break;
+    case 3: hipLaunchKernelGGL((brick_stage_kernel<3, false>), grid, block, 0, st, c, k, s); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace ns

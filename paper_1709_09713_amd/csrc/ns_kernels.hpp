@@ -48,6 +48,10 @@ int trio_resident_blocks(int tile);
 hipError_t launch_trio_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st);
 // The 32x8 three-group kernel with the velocity gradients taken from s.grad.
 hipError_t launch_trio_grad(const Consts &c, const StageArgs &s, hipStream_t st);
+// The brick kernel of small FP64 grids (ns_brick.hip): same results as tiles
+// 8-10, bit for bit.
+int64_t brick_num_blocks(const Consts &c);
+hipError_t launch_brick_stage(const Consts &c, const StageArgs &s, hipStream_t st);
 // Planes a block marches beyond its chunk (halo and pipeline depth).
 int fused_extra_planes(int tile);
 
@@ -62,6 +66,7 @@ struct FusedPlan {
     Consts c;
     ns_precision prec;
     int tile, zchunk, order;
+    bool brick;          // small grid under the automatic launch shape: brick kernel
     int64_t nblk;
     double *state, *partial, *acc;
     void *b1, *b2;

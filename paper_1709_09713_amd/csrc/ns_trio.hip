@@ -49,82 +49,17 @@
 #include <type_traits>
 
 #include "ns_common.hpp"
+#include "ns_fp64.hpp"
 #include "ns_kernels.hpp"
 
 namespace ns {
 
 namespace {
 
-// Coefficients of the stencils with their weights and physical constants
-// folded in on the host: uniform double products formed in the kernel would
-// be held in two vector registers each for the whole march.
-struct TrioK {
-    double x4, xh, y4, yh, z4, zh;   // 4 c1 and c1 / 2 of each direction
-    double z8;                       // 8 c1_z
-    double kx, ky, kz, kz16;         // kappa c2 of each direction, 16 kappa c2_z
-    double vx, vy, vz;               // 4/3 c2 of each direction
-    double mx, my, mz, mxy;          // c1 / 3 of each direction, c1_x c1_y / 3
-};
-
-TrioK make_k(const Consts &c)
-{
-    TrioK k;
-    k.x4 = 4.0 * c.c1[0];
-    k.xh = 0.5 * c.c1[0];
-    k.y4 = 4.0 * c.c1[1];
-    k.yh = 0.5 * c.c1[1];
-    k.z4 = 4.0 * c.c1[2];
-    k.zh = 0.5 * c.c1[2];
-    k.z8 = 8.0 * c.c1[2];
-    k.kx = c.kappa * c.c2[0];
-    k.ky = c.kappa * c.c2[1];
-    k.kz = c.kappa * c.c2[2];
-    k.kz16 = 16.0 * k.kz;
-    k.vx = 4.0 * c.c2[0] / 3.0;
-    k.vy = 4.0 * c.c2[1] / 3.0;
-    k.vz = 4.0 * c.c2[2] / 3.0;
-    k.mx = c.c1[0] / 3.0;
-    k.my = c.c1[1] / 3.0;
-    k.mxy = c.c1[0] * c.c1[1] / 3.0;
-    k.mz = c.c1[2] / 3.0;
-    return k;
-}
-
 typedef double d2_t __attribute__((ext_vector_type(2)));
 
 template <int V>
 using TIC = std::integral_constant<int, V>;
-
-// Unscaled first- and second-derivative stencils with the multiply-adds
-// written out: a product left to the compiler (30 f_0, say) can be shared
-// with another plane's step, fused in one phase of the march and not in
-// another, and a point's rounding would depend on its place in a z-chunk.
-__device__ __forceinline__ double d1(double fm2, double fm1, double fp1, double fp2)
-{
-    return __builtin_fma(8.0, fp1 - fm1, fm2 - fp2);
-}
-__device__ __forceinline__ double d2(double fm2, double fm1, double f0, double fp1, double fp2)
-{
-    return __builtin_fma(-30.0, f0, __builtin_fma(16.0, fm1 + fp1, -(fm2 + fp2)));
-}
-
-// acc - sum_k c_k (f_0 + f_k) (u_0 + u_k) / 2 over the taps k = -2, -1, 1, 2
-// in t[0..3], with the weighted velocity sums s[k] = |c_k| (u_0 + u_k) / 2.
-__device__ __forceinline__ double conv(double acc, double f0, const double (&t)[4], const double (&s)[4])
-{
-    acc = __builtin_fma(-(f0 + t[0]), s[0], acc);
-    acc = __builtin_fma(f0 + t[1], s[1], acc);
-    acc = __builtin_fma(-(f0 + t[2]), s[2], acc);
-    return __builtin_fma(f0 + t[3], s[3], acc);
-}
-
-// unscaled first derivative of the product of two fields at the taps
-__device__ __forceinline__ double d1_prod(const double (&f)[4], const double (&g)[4])
-{
-    const double far = __builtin_fma(f[0], g[0], -(f[3] * g[3]));
-    const double near = __builtin_fma(f[2], g[2], -(f[1] * g[1]));
-    return __builtin_fma(8.0, near, far);
-}
 
 }  // namespace
 
@@ -135,7 +70,7 @@ __device__ __forceinline__ double d1_prod(const double (&f)[4], const double (&g
 // the stored diagonal ones.
 template <int BX, int BY, int MODE, bool DIAG, bool PAIR, bool GRAD>
 __global__ void __launch_bounds__(3 * BX * BY) __attribute__((amdgpu_waves_per_eu(BX * BY >= 128 ? 3 : 2)))
-trio_stage_kernel(Consts c, TrioK k, StageArgs s)
+trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
 {
     // Multiply-adds are fused only within one expression, never across
     // statements: the march's five phases are compiled separately, and
@@ -886,7 +821,7 @@ hipError_t launch_trio_p(const Consts &c, const StageArgs &s, hipStream_t st)
 {
     const dim3 block(3 * BX * BY, 1, 1);
     const dim3 grid((c.nx + BX - 1) / BX, (c.ny + BY - 1) / BY, (c.nz + s.zchunk - 1) / s.zchunk);
-    const TrioK k = make_k(c);
+    const Coef64 k = make_coef64(c);
     switch (s.mode) {
     case 0: hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 0, false, PAIR, GRAD>), grid, block, 0, st, c, k, s); break;
     case 1:
