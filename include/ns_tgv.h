@@ -207,10 +207,12 @@ ns_status ns_stage_stream(const ns_params *p, int32_t stage, double *state, void
  * minimises (rounds of device-resident blocks) x (planes each block
  * marches, chunk + 4 halo planes; + 5 for tiles 8-10)).  tile = -1
  * restores the automatic choice: for NS_FP64 tile 9, or tile 8 where the grid
- * leaves compute units idle, or, with zchunk 0 and grids of up to one 8x4x4
- * brick per compute unit (32^3), a kernel that stages whole bricks instead of
- * marching (all three give the same bits; per-step diagnostics differ in the
- * order of their sums); tile 0 for NS_FP32_STORE.  For a given tile, residuals and states are bitwise
+ * leaves compute units idle, tile 0 for NS_FP32_STORE, and with zchunk 0, for
+ * grids of few 8x4x4 bricks per compute unit (up to 32^3 in NS_FP64, 48^3 in
+ * NS_FP32_STORE), a kernel that stages whole bricks instead of marching.  The
+ * automatic choices of a precision all give the same bits (per-step
+ * diagnostics differ in the order of their sums).
+ * For a given tile, residuals and states are bitwise
  * independent of zchunk (tiles 8-10 also of the tile among them); different tiles are separate compiled
  * instances and may differ at the rounding level (the compiler can contract
  * a multiply-add differently); per-step diagnostics also differ in the

@@ -147,17 +147,25 @@ static void choose_config(const Consts &c, ns_precision prec, int *tile, int *zc
     choose_config(c, prec, -1, 0, tile, zchunk);
 }
 
-// The brick kernel runs small FP64 grids whose launch shape is left to the
-// library (no tile, z-chunk or order asked for by the call or the thread):
-// those that fit the device with one brick per compute unit.  Measured, brick
-// | best march, us per RK3 step: 16^3 16.8 | 21.4, 24^3 17.3 | 22.3, 32^3 (256
-// bricks) 18.4 | 23.5, 36^3 (405) 30.0 | 29.7, 48^3 (864) 53.6 | 33.2.  Its
-// blocks never outnumber those of the one-plane 8x8 march, for which the
-// diagnostic partials of the workspace are sized.
-static bool choose_brick(const Consts &c, ns_precision prec, int tile_in, int zchunk_in)
+// The brick kernels run small grids whose launch shape is left to the library
+// (no tile, z-chunk or order asked for by the call or the thread); returns the
+// planes of a brick, 0 for the march.  Two planes where that gives at most one
+// brick per compute unit, else four planes up to one brick (FP64, whose brick
+// takes two thirds of a unit's LDS) or four (FP32 storage) per compute unit.
+// Measured, us per RK3 step, FP64 two planes | four | best march: 16^3 14.6 |
+// 16.3 | 21.8, 24^3 15.2 | 17.0 | 22.4, 32^3 19.5 | 18.4 | 23.7, 36^3 - | 29.7
+// | 29.7, 48^3 - | 52.2 | 33.2; FP32 storage: 16^3 13.8 | - | 21.9, 28^3 16.3 |
+// 15.9 | 22.5, 40^3 22.0 | 21.5 | 27.5, 48^3 31.0 | 30.6 | 31.7, 56^3 40.0 |
+// 40.4 | 40.0.  The bricks never outnumber the blocks of the one-plane 8x8
+// march, for which the diagnostic partials of the workspace are sized.
+static int choose_brick(const Consts &c, ns_precision prec, int tile_in, int zchunk_in)
 {
     const bool automatic = tile_in < 0 && zchunk_in <= 0 && g_tile < 0 && g_zchunk <= 0 && g_order == 0;
-    return automatic && prec == NS_FP64 && brick_num_blocks(c) <= compute_units();
+    if (!automatic) return 0;
+    const int64_t cus = compute_units();
+    if (brick_num_blocks(c, 2) <= cus) return 2;
+    if (brick_num_blocks(c, 4) <= (prec == NS_FP64 ? 1 : 4) * cus) return 4;
+    return 0;
 }
 
 static int64_t max_partial_blocks(const Consts &c)
@@ -276,7 +284,7 @@ ns_status make_fused_plan(const ns_params *p, ns_precision prec, int tile, int z
     f.order = g_order;
     if (!fused_order_supported(f.tile, f.order)) return NS_ERR_UNSUPPORTED;
     f.brick = choose_brick(c, prec, tile, zchunk);
-    f.nblk = f.brick ? brick_num_blocks(c) : fused_num_blocks(c, f.tile, f.zchunk);
+    f.nblk = f.brick ? brick_num_blocks(c, f.brick) : fused_num_blocks(c, f.tile, f.zchunk);
     f.state = state;
     f.partial = at<double>(work, L.partial);
     f.acc = at<double>(work, L.acc);
@@ -288,12 +296,13 @@ ns_status make_fused_plan(const ns_params *p, ns_precision prec, int tile, int z
 
 // One RK3 step of the fused class: stage 1 Q^n -> b1 (next stage input)
 // and the accumulator (plus the diagnostics partials of Q^n when diag_out
-// is given, reduced into *diag_out right after), stage 2 b1 -> b2 with the
-// accumulator in place, stage 3 b2 -> Q^{n+1} in the state buffer.
+// is given), stage 2 b1 -> b2 with the accumulator in place (and the partials
+// reduced into *diag_out), stage 3 b2 -> Q^{n+1} in the state buffer.
 hipError_t enqueue_fused_step(const FusedPlan &f, double dt, ns_diag *diag_out, hipStream_t s)
 {
     auto launch = [&](const StageArgs &a) {
-        return f.brick ? launch_brick_stage(f.c, a, s) : launch_fused_stage(f.c, a, f.prec, f.tile, s);
+        if (!f.brick) return launch_fused_stage(f.c, a, f.prec, f.tile, s);
+        return f.prec == NS_FP64 ? launch_brick_stage(f.c, a, f.brick, s) : launch_brick32_stage(f.c, a, f.brick, s);
     };
     StageArgs a = {};
     a.zchunk = f.zchunk;
@@ -307,10 +316,6 @@ hipError_t enqueue_fused_step(const FusedPlan &f, double dt, ns_diag *diag_out, 
     a.diag_partial = diag_out ? f.partial : nullptr;
     hipError_t e = launch(a);
     if (e != hipSuccess) return e;
-    if (diag_out) {
-        e = launch_diag_finalize(f.c, f.partial, f.nblk, diag_out, s);
-        if (e != hipSuccess) return e;
-    }
     a.qin = f.b1;
     a.acc_in = f.acc;
     a.acc_out = f.acc;
@@ -319,8 +324,12 @@ hipError_t enqueue_fused_step(const FusedPlan &f, double dt, ns_diag *diag_out, 
     a.b_dt = rk_b(1) * dt;
     a.mode = 2;
     a.diag_partial = nullptr;
+    a.fin_partial = f.partial;
+    a.fin_blocks = f.nblk;
+    a.fin_out = diag_out;
     e = launch(a);
     if (e != hipSuccess) return e;
+    a.fin_out = nullptr;
     a.qin = f.b2;
     a.acc_in = f.acc;
     a.acc_out = nullptr;
@@ -428,8 +437,8 @@ ns_status ns_residual(const ns_params *p, ns_algo algo, const double *Q, double 
         a.rout = R;
         a.mode = 0;
         a.zchunk = zc;
-        NS_HIP_OK(choose_brick(c, NS_FP64, -1, 0) ? launch_brick_stage(c, a, s)
-                                                  : launch_fused_stage(c, a, NS_FP64, tile, s));
+        const int brick = choose_brick(c, NS_FP64, -1, 0);
+        NS_HIP_OK(brick ? launch_brick_stage(c, a, brick, s) : launch_fused_stage(c, a, NS_FP64, tile, s));
         return NS_OK;
     }
     const Layout L = layout(c, algo, NS_FP64);

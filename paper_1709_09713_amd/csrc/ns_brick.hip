@@ -2,8 +2,8 @@
 //
 // The marching kernels step through at least five planes one after another,
 // each with a barrier and, on a small grid that cannot hide it, a wait for
-// memory: about 5 us a stage at 16^3 whose data would take 0.1 us.  Here a
-// block owns a brick of 8 x 4 x 4 points and stages it whole, with its halo
+// memory: about 7 us a stage at 16^3 whose data would take 0.1 us.  Here a
+// block owns a brick of 8 x 4 x BRZ points and stages it whole, with its halo
 // of two, in one round of loads; then three groups of waves evaluate the
 // equations of one point per thread as the groups of ns_trio.hip do (A mass
 // and energy, B momentum and heat conduction, C viscous terms), with the same
@@ -11,12 +11,15 @@
 // Three barriers in all: after the staging, after the in-plane gradients that
 // are differentiated along z, and before A and B take over C's values.
 //
-// Bound by latency: of 5.6 us a stage at 16^3 (16.8 us an RK3 step, the
-// march's best shape 21.4), 1.7 us are an empty launch of a chain; one round
-// of loads, one thread's share of the arithmetic (about 140 double
-// operations) and the barriers are the rest.  The price is the halo, six
-// staged points per point of the brick, so grids of more bricks than compute
-// units are left to the march.
+// Bound by latency: of 4.9 us a stage at 16^3 (14.6 us an RK3 step, the
+// march's best shape 21.8), 1.7 us are an empty launch of a chain; the round
+// of loads and its share of the conversions (1.8 us), the gradients (0.3 us)
+// and one thread's arithmetic (about 140 double operations, 1.5 us) are the
+// rest.  Two planes put one wave on each of three SIMDs (16^3 16.3 -> 14.6
+// us a step against four planes) but load nine points per point of the brick
+// against six, so they are taken only while each brick has a compute unit.
+// One kernel for all stages and the residual: with the stage known at compile
+// time, each stage fetched its code anew (0.1 us).
 #include "ns_common.hpp"
 #include "ns_fp64.hpp"
 #include "ns_kernels.hpp"
@@ -25,15 +28,14 @@ namespace ns {
 
 namespace {
 
-constexpr int BRX = 8, BRY = 4, BRZ = 4;
+constexpr int BRX = 8, BRY = 4;
 
 }  // namespace
 
-template <int MODE, bool DIAG>
+template <int BRZ, bool DIAG>
 __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts c, Coef64 k, StageArgs s)
 {
 #pragma clang fp contract(on)
-    static_assert(!DIAG || MODE == 1, "diagnostics of the step's input state are taken in stage 1");
     constexpr int HX = BRX + 4, HY = BRY + 4, HZ = BRZ + 4, HP = HX * HY, CELLS = HP * HZ;
     constexpr int NT = BRX * BRY * BRZ, NLOAD = (CELLS + 3 * NT - 1) / (3 * NT);
     constexpr int GP = BRX * BRY, GC = GP * HZ;      // own columns with their z halo
@@ -43,46 +45,47 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
     // staged fields: rho - 1, rho u_i, E - E_ref, u, v, w, p - p_ref, T - 1
     enum { L_R, L_M0, L_M1, L_M2, L_E, L_U, L_V, L_W, L_P, L_T, NF };
     enum { G_A, G_B, G_C, NG };                      // D_x u + D_y v, D_x w, D_y w
-    enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_HEAT, H_OZ, H_OX, H_OY };
+    enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_HEAT, NH };
     __shared__ double lds[NF][CELLS];
     __shared__ double grad[NG][GC];
-    __shared__ double vbuf[DIAG ? 9 : 6][NT];
-    __shared__ double red[DIAG ? NW : 1][kDiag];
+    __shared__ double vbuf[NH][NT];
+    __shared__ double red[DIAG ? NW : 1][4];
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave / (NT / 64);
     const int pt = tid - grp * NT;
     const int tx = pt % BRX, ty = (pt / BRX) % BRY, tz = pt / GP;
+    const int skip = DIAG ? 0 : finalize_layer(c, s);
+    if (skip < 0) return;
     int tbx, tby, tbz;
-    xcd_tile(&tbx, &tby, &tbz);
+    xcd_tile(&tbx, &tby, &tbz, skip);
     const int x0 = tbx * BRX, y0 = tby * BRY, z0 = tbz * BRZ;
     const bool active = x0 + tx < c.nx && y0 + ty < c.ny && z0 + tz < c.nz;
     const int own = (tz + 2) * HP + (ty + 2) * HX + tx + 2;
     const int64_t N = c.N;
     const int64_t pidx = active ? ((int64_t)(z0 + tz) * c.ny + y0 + ty) * c.nx + x0 + tx : 0;
     const double *qin = (const double *)s.qin;
-    const double *accsrc = (MODE >= 2) ? s.acc_in : qin;
+    const double *accsrc = (s.mode >= 2) ? s.acc_in : qin;
     const double c1x = c.c1[0], c1y = c.c1[1], c1z = c.c1[2];
     const double c2x = c.c2[0], c2y = c.c2[1], c2z = c.c2[2];
 
-    // ---- stage the brick with its halo (wrapped: valid memory everywhere)
+    // ---- stage the brick with its halo, wrapped to valid memory everywhere: a
+    // brick starts inside the grid at a multiple of its extent, so that with
+    // five points or more one period each way is enough
     double q[NLOAD][5];
 #pragma unroll
     for (int r = 0; r < NLOAD; ++r) {
         const int cell = min(tid + r * 3 * NT, CELLS - 1);
-        int xx = (x0 + cell % HX - 2) % c.nx, yy = (y0 + (cell / HX) % HY - 2) % c.ny;
-        int zz = (z0 + cell / HP - 2) % c.nz;
-        if (xx < 0) xx += c.nx;
-        if (yy < 0) yy += c.ny;
-        if (zz < 0) zz += c.nz;
+        const int xx = wrap1(x0 + cell % HX - 2, c.nx), yy = wrap1(y0 + (cell / HX) % HY - 2, c.ny);
+        const int zz = wrap1(z0 + cell / HP - 2, c.nz);
         const double *src = qin + ((int64_t)zz * c.ny + yy) * c.nx + xx;
 #pragma unroll
         for (int f = 0; f < 5; ++f) q[r][f] = src[f * N];
     }
     // accumulator of the own point: group A the mass and energy, B the momenta
     double acc[3] = {0.0, 0.0, 0.0};
-    if constexpr (MODE >= 1) {
+    if (s.mode >= 1) {
         if (grp == 0) {
             acc[0] = accsrc[pidx];
             acc[1] = accsrc[4 * N + pidx];
@@ -139,6 +142,9 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
     lds_barrier();
 
     double R[3] = {0.0, 0.0, 0.0};
+    // diagnostics of the point: group A mass and energy, B the momenta and
+    // kinetic energy, C enstrophy
+    double dsum[4] = {0.0, 0.0, 0.0, 0.0};
     if (grp == 0) {
         // ------------------------------------------------------------ group A
         const double r = LV(L_R, 0, 0, 0), E = LV(L_E, 0, 0, 0), w = LV(L_W, 0, 0, 0);
@@ -307,15 +313,13 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
         vbuf[H_EN][pt] = c.inv_re * (u * Vx + v * Vy + w * Vz + (phi + phz)) - c.H_ref * div;
         vbuf[H_DIV][pt] = div;
         if constexpr (DIAG) {
-            vbuf[H_OZ][pt] = oz;
-            vbuf[H_OX][pt] = cc - Gyz;
-            vbuf[H_OY][pt] = Gxz - bb;
+            const double ox = cc - Gyz, oy = Gxz - bb;
+            dsum[0] = 0.5 * (1.0 + LV(L_R, 0, 0, 0)) * (ox * ox + oy * oy + oz * oz);
         }
     }
     lds_barrier();
 
     // ---- C's part of the equations, RK update, output
-    double dsum[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (grp < 2 && active) {
         if (grp == 0) {
             R[0] = R[0] - vbuf[H_DIV][pt];
@@ -329,27 +333,19 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
             if (grp == 0 && f == 2) continue;
             const int field = grp == 0 ? 4 * f : 1 + f;
             const int64_t at = field * N + pidx;
-            if constexpr (MODE == 0) {
+            if (s.mode == 0) {
                 s.rout[at] = R[f];
             } else {
                 ((double *)s.qout)[at] = acc[f] + s.a_dt * R[f];
-                if constexpr (MODE < 3) s.acc_out[at] = acc[f] + s.b_dt * R[f];
+                if (s.mode < 3) s.acc_out[at] = acc[f] + s.b_dt * R[f];
             }
         }
         if constexpr (DIAG) {
-            if (grp == 0) {
-                const double hr = 0.5 * (1.0 + LV(L_R, 0, 0, 0));
-                const double ox = vbuf[H_OX][pt], oy = vbuf[H_OY][pt], oz = vbuf[H_OZ][pt];
-                dsum[0] = acc[0];
-                dsum[4] = acc[1];
-                dsum[6] = hr * (ox * ox + oy * oy + oz * oz);
-            } else {
-                dsum[1] = acc[0];
-                dsum[2] = acc[1];
-                dsum[3] = acc[2];
-                dsum[5] = 0.5 * (LV(L_M0, 0, 0, 0) * LV(L_U, 0, 0, 0) + LV(L_M1, 0, 0, 0) * LV(L_V, 0, 0, 0)
+#pragma unroll
+            for (int f = 0; f < 3; ++f) dsum[f] = acc[f];
+            if (grp == 1)
+                dsum[3] = 0.5 * (LV(L_M0, 0, 0, 0) * LV(L_U, 0, 0, 0) + LV(L_M1, 0, 0, 0) * LV(L_V, 0, 0, 0)
                                  + LV(L_M2, 0, 0, 0) * LV(L_W, 0, 0, 0));
-            }
         }
     }
 #undef AT
@@ -364,46 +360,46 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
     if constexpr (DIAG) {
         // block sum of the diagnostics in a fixed order
 #pragma unroll
-        for (int d = 0; d < 7; ++d) {
-            double vsum = dsum[d];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) vsum += __shfl_xor(vsum, off, 64);
-            if ((tid & 63) == 0) red[tid >> 6][d] = vsum;
+        for (int d = 0; d < 4; ++d) {
+            const double vsum = wave_sum(active ? dsum[d] : 0.0);
+            if ((tid & 63) == 63) red[wave][d] = vsum;
         }
         lds_barrier();
-        if (tid < 7) {
-            double t = 0.0;
-            for (int wv = 0; wv < NW; ++wv) t += red[wv][tid];
+        if (tid < kDiag) {
+            // a record's slots by group: A 0 and 4, B 1, 2, 3 and 5, C 6 and 7 (zero)
+            const int g = (tid & 3) == 0 ? 0 : tid < 6 ? 1 : 2;
+            const int d = g == 0 ? tid >> 2 : g == 1 ? tid - 1 - (tid >> 2) : tid - 6;
             const int64_t blin = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+            double t = 0.0;
+#pragma unroll
+            for (int wv = 0; wv < NW / 3; ++wv) t += red[g * (NW / 3) + wv][d];
             s.diag_partial[blin * kDiag + tid] = t;
-            if (tid == 0) s.diag_partial[blin * kDiag + 7] = 0.0;
         }
     }
 }
 
-int64_t brick_num_blocks(const Consts &c)
+int64_t brick_num_blocks(const Consts &c, int bz)
 {
-    return (int64_t)((c.nx + BRX - 1) / BRX) * ((c.ny + BRY - 1) / BRY) * ((c.nz + BRZ - 1) / BRZ);
+    return (int64_t)((c.nx + BRX - 1) / BRX) * ((c.ny + BRY - 1) / BRY) * ((c.nz + bz - 1) / bz);
 }
 
-hipError_t launch_brick_stage(const Consts &c, const StageArgs &s, hipStream_t st)
+template <int BRZ>
+static hipError_t launch_brick_z(const Consts &c, const StageArgs &s, hipStream_t st)
 {
     const dim3 block(3 * BRX * BRY * BRZ);
-    const dim3 grid((c.nx + BRX - 1) / BRX, (c.ny + BRY - 1) / BRY, (c.nz + BRZ - 1) / BRZ);
+    const dim3 grid((c.nx + BRX - 1) / BRX, (c.ny + BRY - 1) / BRY,
+                    (c.nz + BRZ - 1) / BRZ + (s.fin_out != nullptr));
     const Coef64 k = make_coef64(c);
-    switch (s.mode) {
-    case 0: hipLaunchKernelGGL((brick_stage_kernel<0, false>), grid, block, 0, st, c, k, s); break;
-    case 1:
-        if (s.diag_partial != nullptr)
-            hipLaunchKernelGGL((brick_stage_kernel<1, true>), grid, block, 0, st, c, k, s);
-        else
-            hipLaunchKernelGGL((brick_stage_kernel<1, false>), grid, block, 0, st, c, k, s);
-        break;
-    case 2: hipLaunchKernelGGL((brick_stage_kernel<2, false>), grid, block, 0, st, c, k, s); break;
-    case 3: hipLaunchKernelGGL((brick_stage_kernel<3, false>), grid, block, 0, st, c, k, s); break;
-    default: return hipErrorInvalidValue;
-    }
+    if (s.diag_partial != nullptr)
+        hipLaunchKernelGGL((brick_stage_kernel<BRZ, true>), grid, block, 0, st, c, k, s);
+    else
+        hipLaunchKernelGGL((brick_stage_kernel<BRZ, false>), grid, block, 0, st, c, k, s);
     return hipGetLastError();
+}
+
+hipError_t launch_brick_stage(const Consts &c, const StageArgs &s, int bz, hipStream_t st)
+{
+    return bz == 2 ? launch_brick_z<2>(c, s, st) : launch_brick_z<4>(c, s, st);
 }
 
 }  // namespace ns

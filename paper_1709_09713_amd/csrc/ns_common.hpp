@@ -126,18 +126,54 @@ __device__ __forceinline__ double quotient_f64(double m, double x, double inv)
     return __builtin_fma(__builtin_fma(-q, x, m), inv, q);
 }
 
+// Sum over the 64 lanes of a wave, valid in lane 63, in a fixed order: within
+// rows of 16 lanes by row shifts, then row 0 into 1 and 2 into 3, then the
+// lower half into the upper one.  DPP moves only: six steps of a shuffle
+// through LDS cost about 1 us at the end of a small grid's stage.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
+    return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_sum(double v)
+{
+    v = dpp_add<0x111, 0xF>(v);   // row_shr:1
+    v = dpp_add<0x112, 0xF>(v);   // row_shr:2
+    v = dpp_add<0x114, 0xF>(v);   // row_shr:4
+    v = dpp_add<0x118, 0xF>(v);   // row_shr:8
+    v = dpp_add<0x142, 0xA>(v);   // row_bcast:15
+    return dpp_add<0x143, 0xC>(v);   // row_bcast:31
+}
+
+// A diagnostics record from the sums over the grid: mass, momenta, energy,
+// kinetic energy, enstrophy.
+__device__ __forceinline__ void write_diag(const Consts &c, const double (&v)[7], ns_diag *out)
+{
+    out->mass = c.vol * v[0];
+    out->momentum[0] = c.vol * v[1];
+    out->momentum[1] = c.vol * v[2];
+    out->momentum[2] = c.vol * v[3];
+    out->energy = c.vol * v[4];
+    out->kinetic_energy = v[5] * c.inv_npts;
+    out->enstrophy = v[6] * c.inv_npts;
+    out->dissipation = 2.0 * (v[6] * c.inv_npts) * c.inv_re;
+}
+
 // XCD-aware tile order.  The dispatcher hands workgroups to the 8 XCDs
 // round-robin by linear workgroup id, and each XCD has its own L2.  Remap so
 // that XCD k processes the k-th contiguous run of tiles (x fastest, then y,
 // then z): tiles that share halo rows and columns then run at the same time
-// on the same L2.  Bijective for any grid size.
+// on the same L2.  Bijective for any grid size.  `skip` leading z layers of
+// the launch carry no tiles.
 constexpr int kNumXcd = 8;
 
-__device__ __forceinline__ void xcd_tile(int *bx, int *by, int *bz)
+__device__ __forceinline__ void xcd_tile(int *bx, int *by, int *bz, int skip = 0)
 {
     const int gx = gridDim.x, gy = gridDim.y;
-    const int total = gx * gy * gridDim.z;
-    const int L = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
+    const int total = gx * gy * ((int)gridDim.z - skip);
+    const int L = blockIdx.x + gx * (blockIdx.y + gy * ((int)blockIdx.z - skip));
     const int k = L % kNumXcd, slot = L / kNumXcd;
     const int q = total / kNumXcd, r = total % kNumXcd;
     const int T = k * q + min(k, r) + slot;

@@ -311,14 +311,8 @@ diag_finalize_kernel(Consts c, const double *__restrict__ partial, int64_t nbloc
         __syncthreads();
     }
     if (t == 0) {
-        out->mass = c.vol * red[0][0];
-        out->momentum[0] = c.vol * red[0][1];
-        out->momentum[1] = c.vol * red[0][2];
-        out->momentum[2] = c.vol * red[0][3];
-        out->energy = c.vol * red[0][4];
-        out->kinetic_energy = red[0][5] * c.inv_npts;
-        out->enstrophy = red[0][6] * c.inv_npts;
-        out->dissipation = 2.0 * out->enstrophy * c.inv_re;
+        const double v[7] = {red[0][0], red[0][1], red[0][2], red[0][3], red[0][4], red[0][5], red[0][6]};
+        write_diag(c, v, out);
     }
 }
 

@@ -123,8 +123,13 @@ fused_stage_kernel(Consts c, StageArgs s)
     __shared__ double red[NT / 64 + 1][kDiag];
 
     const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * BX + tx;
+    int skip = 0;
+    if constexpr (std::is_same<TIN, TOUT>::value && !DIAG) {
+        skip = finalize_layer(c, s);
+        if (skip < 0) return;
+    }
     int tbx, tby, tbz;
-    xcd_tile(&tbx, &tby, &tbz);
+    xcd_tile(&tbx, &tby, &tbz, skip);
     const int x0 = tbx * BX, y0 = tby * BY;
     const int z0 = tbz * s.zchunk;
     const int z1 = min(z0 + s.zchunk, c.nz);
@@ -676,7 +681,8 @@ template <int BX, int BY, typename TIN, typename TOUT, typename CT, int ORD>
 static hipError_t launch_o(const Consts &c, const StageArgs &s, hipStream_t st)
 {
     dim3 block(BX, BY, 1);
-    dim3 grid((c.nx + BX - 1) / BX, (c.ny + BY - 1) / BY, (c.nz + s.zchunk - 1) / s.zchunk);
+    dim3 grid((c.nx + BX - 1) / BX, (c.ny + BY - 1) / BY,
+              (c.nz + s.zchunk - 1) / s.zchunk + (s.fin_out != nullptr));
     // per-step diagnostics are only taken in stage 1, which reads the
     // double state
     // paired plane loads need an even x extent; the FP32 stage-1 kernel

@@ -29,7 +29,34 @@ struct StageArgs {
     double *diag_partial;   // per-block diagnostic partial sums, or nullptr
     const double *grad;     // stored velocity gradients (intermediate-storage class)
     int order;              // in-plane evaluation order: 0 by equation, 1 by direction
+    // stage 2 after a stage 1 with diagnostics: reduce its partials
+    const double *fin_partial;
+    int64_t fin_blocks;
+    ns_diag *fin_out;       // nullptr: nothing to reduce
 };
+
+// Stage 2 reduces the partial sums that stage 1 left: its launch has one more
+// z layer, in front, whose first block does it (one wave, fixed order) while
+// the other blocks run the stage.  As a launch of its own between the stages
+// it took 4 us, a fifth of a step at 16^3.  Returns the number of leading
+// layers without tiles, or -1 for a block of that layer, which is done.
+__device__ __forceinline__ int finalize_layer(const Consts &c, const StageArgs &s)
+{
+    if (s.fin_out == nullptr) return 0;
+    if (blockIdx.z != 0) return 1;
+    if ((blockIdx.x | blockIdx.y) == 0 && threadIdx.y * blockDim.x + threadIdx.x < 64) {
+        const int t = threadIdx.y * blockDim.x + threadIdx.x;
+        double v[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+        for (int64_t b = t; b < s.fin_blocks; b += 64)
+#pragma unroll
+            for (int q = 0; q < 7; ++q) v[q] += s.fin_partial[b * kDiag + q];
+#pragma unroll
+        for (int q = 0; q < 7; ++q) v[q] = wave_sum(v[q]);
+        if (t == 63) write_diag(c, v, s.fin_out);
+    }
+    return -1;
+}
 
 void tile_dims(int tile, int *bx, int *by);
 int64_t fused_num_blocks(const Consts &c, int tile, int zchunk);
@@ -48,10 +75,12 @@ int trio_resident_blocks(int tile);
 hipError_t launch_trio_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st);
 // The 32x8 three-group kernel with the velocity gradients taken from s.grad.
 hipError_t launch_trio_grad(const Consts &c, const StageArgs &s, hipStream_t st);
-// The brick kernel of small FP64 grids (ns_brick.hip): same results as tiles
-// 8-10, bit for bit.
-int64_t brick_num_blocks(const Consts &c);
-hipError_t launch_brick_stage(const Consts &c, const StageArgs &s, hipStream_t st);
+// The brick kernels of small grids, bricks of bz = 2 or 4 planes: FP64
+// (ns_brick.hip), same results as tiles 8-10 bit for bit, and FP32 storage
+// (ns_brick32.hip), same results as tiles 0-7 bit for bit.
+int64_t brick_num_blocks(const Consts &c, int bz);
+hipError_t launch_brick_stage(const Consts &c, const StageArgs &s, int bz, hipStream_t st);
+hipError_t launch_brick32_stage(const Consts &c, const StageArgs &s, int bz, hipStream_t st);
 // Planes a block marches beyond its chunk (halo and pipeline depth).
 int fused_extra_planes(int tile);
 
@@ -66,7 +95,7 @@ struct FusedPlan {
     Consts c;
     ns_precision prec;
     int tile, zchunk, order;
-    bool brick;          // small grid under the automatic launch shape: brick kernel
+    int brick;           // planes of a brick, 0: the march of tile and zchunk
     int64_t nblk;
     double *state, *partial, *acc;
     void *b1, *b2;

@@ -120,8 +120,13 @@ split_stage_kernel(Consts c, StageArgs s)
     const bool grp_e = wave >= NT / 64;
     const int pt = (int)threadIdx.x - (grp_e ? NT : 0);
     const int tx = pt % BX, ty = pt / BX;
+    int skip = 0;
+    if constexpr (MODE == 2) {
+        skip = finalize_layer(c, s);
+        if (skip < 0) return;
+    }
     int tbx, tby, tbz;
-    xcd_tile(&tbx, &tby, &tbz);
+    xcd_tile(&tbx, &tby, &tbz, skip);
     const int x0 = tbx * BX, y0 = tby * BY;
     const int z0 = tbz * s.zchunk;
     const int z1 = min(z0 + s.zchunk, c.nz);
@@ -661,7 +666,8 @@ template <int BX, int BY, typename TIN, typename TOUT, typename CT, int MODE, bo
 void launch_one(const Consts &c, const StageArgs &s, hipStream_t st)
 {
     dim3 block(2 * BX * BY, 1, 1);
-    dim3 grid((c.nx + BX - 1) / BX, (c.ny + BY - 1) / BY, (c.nz + s.zchunk - 1) / s.zchunk);
+    dim3 grid((c.nx + BX - 1) / BX, (c.ny + BY - 1) / BY,
+              (c.nz + s.zchunk - 1) / s.zchunk + (s.fin_out != nullptr));
     hipLaunchKernelGGL((split_stage_kernel<BX, BY, TIN, TOUT, CT, MODE, DIAG, PAIR>), grid, block, 0, st,
                        c, s);
 }

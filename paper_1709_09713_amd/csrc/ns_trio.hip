@@ -103,8 +103,13 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
     const int grp = wave / (NT / 64);
     const int pt = (int)threadIdx.x - grp * NT;
     const int tx = pt % BX, ty = pt / BX;
+    int skip = 0;
+    if constexpr (MODE == 2 && !GRAD) {
+        skip = finalize_layer(c, s);
+        if (skip < 0) return;
+    }
     int tbx, tby, tbz;
-    xcd_tile(&tbx, &tby, &tbz);
+    xcd_tile(&tbx, &tby, &tbz, skip);
     const int x0 = tbx * BX, y0 = tby * BY;
     const int z0 = tbz * s.zchunk;
     const int z1 = min(z0 + s.zchunk, c.nz);
@@ -792,24 +797,15 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
         }
 #pragma unroll
         for (int k = 0; k < 7; ++k) {
-            double vsum = dsum[k];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) vsum += __shfl_xor(vsum, off, 64);
-            dsum[k] = vsum;
-        }
-        if ((tid & 63) == 0) {
-#pragma unroll
-            for (int k = 0; k < 7; ++k) red[tid >> 6][k] = dsum[k];
+            const double vsum = wave_sum(dsum[k]);
+            if ((tid & 63) == 63) red[tid >> 6][k] = vsum;
         }
         __syncthreads();
-        if (tid == 0) {
+        if (tid < 8) {
             const int64_t blin = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-            for (int k = 0; k < 7; ++k) {
-                double t = 0.0;
-                for (int wv = 0; wv < NW; ++wv) t += red[wv][k];
-                s.diag_partial[blin * kDiag + k] = t;
-            }
-            s.diag_partial[blin * kDiag + 7] = 0.0;
+            double t = 0.0;
+            for (int wv = 0; wv < NW && tid < 7; ++wv) t += red[wv][tid];
+            s.diag_partial[blin * kDiag + tid] = t;
         }
     }
 }
@@ -820,7 +816,8 @@ template <int BX, int BY, bool PAIR, bool GRAD>
 hipError_t launch_trio_p(const Consts &c, const StageArgs &s, hipStream_t st)
 {
     const dim3 block(3 * BX * BY, 1, 1);
-    const dim3 grid((c.nx + BX - 1) / BX, (c.ny + BY - 1) / BY, (c.nz + s.zchunk - 1) / s.zchunk);
+    const dim3 grid((c.nx + BX - 1) / BX, (c.ny + BY - 1) / BY,
+                    (c.nz + s.zchunk - 1) / s.zchunk + (s.fin_out != nullptr));
     const Coef64 k = make_coef64(c);
     switch (s.mode) {
     case 0: hipLaunchKernelGGL((trio_stage_kernel<BX, BY, 0, false, PAIR, GRAD>), grid, block, 0, st, c, k, s); break;
