@@ -58,19 +58,39 @@ hipError_t launch_tgv_init(const Consts &c, const ns_params *p, double *state, h
 //
 // Bound by memory: 40 B per point must be read; the halo rows and columns add
 // about 30% of L2 reads and the planes above and below a chunk 4 / chunk.
-// Whole diagnostics() calls: 256^3 561 -> 199 us, 512^3 5.03 -> 1.21 ms (4.4
+// Whole diagnostics() calls: 256^3 561 -> 177 us, 512^3 5.03 -> 1.21 ms (4.4
 // TB/s) against one thread per point gathering its neighbours through the
 // caches with a division per velocity.
 constexpr int kDiagBX = 32, kDiagBY = 8, kDiagThreads = kDiagBX * kDiagBY;
 
-// Planes per block: the shortest chunk that still leaves about 2048 blocks (a
-// compute unit holds up to eight), so that large grids read few planes twice
-// and small ones fill the device (16^3: one plane per block).
+// Planes per block of the march.  A block steps through its chunk and four
+// halo planes, and the grid runs in rounds of the 768 blocks that the device
+// holds (three on each of 256 compute units): the chunk with the least rounds x
+// planes, the longest of equals.  Where one layer of tiles is more than that,
+// memory bounds the march whatever the rounds, and about 2048 blocks are as
+// good.  Against about 2048 blocks for every grid, us per diagnostics(): 128^3
+// 62 -> 49, 161x97x119 62 -> 50, 192^3 101 -> 86, 256^3 197 -> 179, 320^3 and
+// above the same.
 static int diag_zchunk(const Consts &c)
 {
-    const int64_t tiles = (int64_t)((c.nx + kDiagBX - 1) / kDiagBX) * ((c.ny + kDiagBY - 1) / kDiagBY);
-    const int64_t chunks = (2048 + tiles - 1) / tiles;
-    return (int)((c.nz + chunks - 1) / chunks);
+    constexpr int kResident = 768;
+    const int tiles = ((c.nx + kDiagBX - 1) / kDiagBX) * ((c.ny + kDiagBY - 1) / kDiagBY);
+    if (tiles > kResident) {
+        const int chunks = (2048 + tiles - 1) / tiles;
+        return (c.nz + chunks - 1) / chunks;
+    }
+    int best = c.nz;
+    int64_t best_cost = INT64_MAX;
+    for (int k = 1; k <= c.nz; ++k) {
+        const int z = (c.nz + k - 1) / k, chunks = (c.nz + z - 1) / z;
+        if (chunks != k) continue;   // the same z as a smaller k
+        const int64_t cost = (int64_t)((tiles * chunks + kResident - 1) / kResident) * (z + 4);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = z;
+        }
+    }
+    return best;
 }
 
 // Grids of fewer points than this take one thread per point instead
@@ -100,23 +120,15 @@ __device__ __forceinline__ void diag_block_sum(double (&s)[7], double *__restric
 {
     __shared__ double red[kDiagThreads / 64][kDiag];
 #pragma unroll
-    for (int q = 0; q < 7; ++q) {
-        double v = s[q];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        s[q] = v;
-    }
+    for (int q = 0; q < 7; ++q) s[q] = wave_sum(s[q]);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0)
+    if (lane == 63)
         for (int q = 0; q < 7; ++q) red[wave][q] = s[q];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int q = 0; q < 7; ++q) {
-            double t = 0.0;
-            for (int wv = 0; wv < kDiagThreads / 64; ++wv) t += red[wv][q];
-            partial[blin * kDiag + q] = t;
-        }
-        partial[blin * kDiag + 7] = 0.0;
+    if (threadIdx.x < kDiag) {
+        double t = 0.0;
+        for (int wv = 0; wv < kDiagThreads / 64 && threadIdx.x < 7; ++wv) t += red[wv][threadIdx.x];
+        partial[blin * kDiag + threadIdx.x] = t;
     }
 }
 
@@ -164,7 +176,9 @@ diag_point_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ p
     diag_block_sum(s, partial, blockIdx.x);
 }
 
-__global__ void __launch_bounds__(kDiagThreads)
+// Three waves per SIMD and no more: a fourth has larger grids' planes leave L2
+// before the neighbouring blocks have read them (512^3 1221 -> 1340 us).
+__global__ void __launch_bounds__(kDiagThreads) __attribute__((amdgpu_waves_per_eu(3, 3)))
 diag_march_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ partial, int zchunk)
 {
     constexpr int BX = kDiagBX, BY = kDiagBY, HX = BX + 4, HY = BY + 4;
