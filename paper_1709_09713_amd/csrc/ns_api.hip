@@ -91,7 +91,7 @@ static int default_zchunk(const Consts &c, ns_precision prec, int tile)
 // three-group kernel, one each.
 static int64_t compute_units()
 {
-    const int r = fused_resident_blocks(NS_FP64, TILE_32x8_2G);
+    const int r = fused_resident_blocks(NS_FP64, TILE_32x8_3G);
     return r > 0 ? r : 256;
 }
 
@@ -106,16 +106,38 @@ static int default_fp64_tile(const Consts &c, int *zchunk)
 {
     const int64_t cus = compute_units();
     int64_t narrow, wide;
-    const int z9 = zchunk_for(c, TILE_32x8_2G, cus, &wide);
-    if (fused_num_blocks(c, TILE_16x8_2G, c.nz) <= cus) {
-        const int z8 = zchunk_for(c, TILE_16x8_2G, cus, &narrow);
-        if (fused_num_blocks(c, TILE_16x8_2G, z8) <= cus && 2 * narrow < 3 * wide) {
+    const int z9 = zchunk_for(c, TILE_32x8_3G, cus, &wide);
+    if (fused_num_blocks(c, TILE_16x8_3G, c.nz) <= cus) {
+        const int z8 = zchunk_for(c, TILE_16x8_3G, cus, &narrow);
+        if (fused_num_blocks(c, TILE_16x8_3G, z8) <= cus && 2 * narrow < 3 * wide) {
             *zchunk = z8;
-            return TILE_16x8_2G;
+            return TILE_16x8_3G;
         }
     }
     *zchunk = z9;
-    return TILE_32x8_2G;
+    return TILE_32x8_3G;
+}
+
+// FP32 storage: a plane of the one-thread 32x8 kernel, two blocks a compute
+// unit, takes 2.0 us, one of the three-group kernel, one block a compute unit,
+// 1.2 us, so that kernel is taken where its longer chunks come to at most 1.8
+// times the planes (not 2.0/1.2: on larger grids, which memory bounds, the
+// one-thread kernel's second block hides more).  Measured, one thread | three
+// groups, us per RK3 step: 56^3 40.9 | 37.7, 64^3 43.3 | 40.4, 80^3 66.3 | 62.8,
+// 101x77x53 69.4 | 64.9, 96^3 85.7 | 82.6, 112^3 134.8 | 139.8, 128^3 175 | 177,
+// 160^3 317 | 340, 256^3 1144 | 1234.  Both give the same bits; the
+// direction-grouped order is compiled for the one-thread kernel only.
+static int default_fp32_tile(const Consts &c, int *zchunk)
+{
+    int64_t one = 0, three = 0;
+    const int z0 = zchunk_for(c, TILE_32x8, resident_blocks(NS_FP32_STORE, TILE_32x8), &one);
+    const int z9 = zchunk_for(c, TILE_32x8_3G, resident_blocks(NS_FP32_STORE, TILE_32x8_3G), &three);
+    if (g_order == 0 && 5 * three <= 9 * one) {
+        *zchunk = z9;
+        return TILE_32x8_3G;
+    }
+    *zchunk = z0;
+    return TILE_32x8;
 }
 
 // Launch shape: an explicit tile (>= 0) / zchunk (> 0) wins, else the
@@ -130,10 +152,10 @@ static void choose_config(const Consts &c, ns_precision prec, int tile_in, int z
     // kernel on grids from 40^3 to 512^3, FP32 storage with the one-thread
     // 32x8 kernel
     if (t < 0 || t >= TILE_COUNT) {
-        if (prec == NS_FP64 && z <= 0)
-            t = default_fp64_tile(c, &z);
+        if (z <= 0)
+            t = prec == NS_FP64 ? default_fp64_tile(c, &z) : default_fp32_tile(c, &z);
         else
-            t = (prec == NS_FP64) ? TILE_32x8_2G : TILE_32x8;
+            t = (prec == NS_FP64) ? TILE_32x8_3G : TILE_32x8;
     }
     if (z <= 0) z = default_zchunk(c, prec, t);
     if (z < kMinZChunk) z = kMinZChunk;
@@ -446,7 +468,7 @@ ns_status ns_residual(const ns_params *p, ns_algo algo, const double *Q, double 
     if (st != NS_OK) return st;
     if (algo == NS_ALGO_SOME) {
         NS_HIP_OK(rs_stage(c, Q, at<double>(work, L.G), nullptr, nullptr, nullptr, R, 0.0, 0.0, 0,
-                           default_zchunk(c, NS_FP64, TILE_32x8_2G), s));
+                           default_zchunk(c, NS_FP64, TILE_32x8_3G), s));
         return NS_OK;
     }
     StageArgs a = {};
@@ -488,7 +510,7 @@ ns_status rk3_step(const ns_params *p, ns_algo algo, ns_precision prec, double d
     if (algo == NS_ALGO_SOME) {
         double *G = at<double>(work, L.G);
         double *q1 = (double *)b1, *q2 = (double *)b2;
-        const int zc = default_zchunk(c, NS_FP64, TILE_32x8_2G);
+        const int zc = default_zchunk(c, NS_FP64, TILE_32x8_3G);
         for (int32_t step = 0; step < nsteps; ++step) {
             if (diag_dev) {
                 NS_HIP_OK(launch_diag_partials(c, state, partial, s));

@@ -746,8 +746,8 @@ void tile_dims(int tile, int *bx, int *by)
     case TILE_32x4: *bx = 32; *by = 4; break;
     case TILE_16x4: *bx = 16; *by = 4; break;
     case TILE_8x8: *bx = 8; *by = 8; break;
-    case TILE_16x8_2G: *bx = 16; *by = 8; break;
-    case TILE_16x4_2G: *bx = 16; *by = 4; break;
+    case TILE_16x8_3G: *bx = 16; *by = 8; break;
+    case TILE_16x4_3G: *bx = 16; *by = 4; break;
     default: *bx = 32; *by = 8; break;
     }
 }
@@ -795,7 +795,7 @@ int fused_resident_blocks(ns_precision prec, int tile)
     int r = cache[dev][q][tile].load();
     if (r == 0) {
         if (split_tile(tile))
-            r = prec == NS_FP64 ? trio_resident_blocks(tile) : split_resident_blocks(tile);
+            r = prec == NS_FP64 ? trio_resident_blocks(tile) : trio32_resident_blocks(tile);
         else
             r = prec == NS_FP64 ? resident_tile<double, double, double>(tile)
                                 : resident_tile<float, float, float>(tile);
@@ -808,6 +808,8 @@ bool fused_order_supported(int tile, int order)
 {
     return order == 0 || (order == 1 && (tile == TILE_16x8 || tile == TILE_32x8));
 }
+
+bool split_tile(int tile) { return tile == TILE_16x8_3G || tile == TILE_32x8_3G || tile == TILE_16x4_3G; }
 
 int fused_extra_planes(int tile) { return split_tile(tile) ? 5 : 4; }
 
@@ -822,7 +824,7 @@ hipError_t launch_fused_stage(const Consts &c, const StageArgs &s, ns_precision 
                               int tile, hipStream_t st)
 {
     if (split_tile(tile))
-        return prec == NS_FP64 ? launch_trio_stage(c, s, tile, st) : launch_split_stage(c, s, tile, st);
+        return prec == NS_FP64 ? launch_trio_stage(c, s, tile, st) : launch_trio32_stage(c, s, tile, st);
     if (prec == NS_FP64)
         return launch_tile<double, double, double>(tile, c, s, st);
     // FP32 storage: stage 1 reads the double state, stage 3 writes it.

@@ -6,14 +6,13 @@
 namespace ns {
 
 // Column-tile shapes of the fused kernel.  Tiles 0-7: threads = BX * BY,
-// one z column each (ns_fused.hip).  Tiles 8-10 (_2G) split each column over
-// groups of waves: FP64 over three (ns_trio.hip), FP32 storage over two
-// (ns_split.hip).  Chosen per problem by the autotuner or by the default
-// rule.
+// one z column each (ns_fused.hip).  Tiles 8-10 (_3G) split each column over
+// three groups of waves (FP64 ns_trio.hip, FP32 storage ns_trio32.hip).  Chosen
+// per problem by the autotuner or by the default rule.
 enum {
     TILE_32x8 = 0, TILE_16x16 = 1, TILE_64x4 = 2, TILE_32x16 = 3,
     TILE_16x8 = 4, TILE_32x4 = 5, TILE_16x4 = 6, TILE_8x8 = 7,
-    TILE_16x8_2G = 8, TILE_32x8_2G = 9, TILE_16x4_2G = 10, TILE_COUNT = 11
+    TILE_16x8_3G = 8, TILE_32x8_3G = 9, TILE_16x4_3G = 10, TILE_COUNT = 11
 };
 
 // One fused launch: residual only (mode 0) or RK stage 1..3.
@@ -66,11 +65,11 @@ bool fused_order_supported(int tile, int order);
 int fused_resident_blocks(ns_precision prec, int tile);
 hipError_t launch_fused_stage(const Consts &c, const StageArgs &s, ns_precision prec,
                               int tile, hipStream_t st);
-// The split-column kernels (tiles 8-10; split_: FP32 storage, trio_: FP64):
+// The split-column kernels (tiles 8-10; trio_: FP64, trio32_: FP32 storage):
 // stage launch and resident blocks.
 bool split_tile(int tile);
-int split_resident_blocks(int tile);
-hipError_t launch_split_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st);
+int trio32_resident_blocks(int tile);
+hipError_t launch_trio32_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st);
 int trio_resident_blocks(int tile);
 hipError_t launch_trio_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st);
 // The 32x8 three-group kernel with the velocity gradients taken from s.grad.

@@ -862,9 +862,9 @@ int resident_trio()
 int trio_resident_blocks(int tile)
 {
     switch (tile) {
-    case TILE_16x8_2G: return resident_trio<16, 8>();
-    case TILE_32x8_2G: return resident_trio<32, 8>();
-    case TILE_16x4_2G: return resident_trio<16, 4>();
+    case TILE_16x8_3G: return resident_trio<16, 8>();
+    case TILE_32x8_3G: return resident_trio<32, 8>();
+    case TILE_16x4_3G: return resident_trio<16, 4>();
     default: return 0;
     }
 }
@@ -877,9 +877,9 @@ hipError_t launch_trio_grad(const Consts &c, const StageArgs &s, hipStream_t st)
 hipError_t launch_trio_stage(const Consts &c, const StageArgs &s, int tile, hipStream_t st)
 {
     switch (tile) {
-    case TILE_16x8_2G: return launch_trio<16, 8>(c, s, st);
-    case TILE_32x8_2G: return launch_trio<32, 8>(c, s, st);
-    case TILE_16x4_2G: return launch_trio<16, 4>(c, s, st);
+    case TILE_16x8_3G: return launch_trio<16, 8>(c, s, st);
+    case TILE_32x8_3G: return launch_trio<32, 8>(c, s, st);
+    case TILE_16x4_3G: return launch_trio<16, 4>(c, s, st);
     default: return hipErrorInvalidValue;
     }
 }
