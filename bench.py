@@ -2,9 +2,9 @@
 path on the 512^3 Taylor-Green vortex (Re = 1600, Pr = 0.71, M = 0.1,
 gamma = 1.4, dt = 4.23125e-4), one MI355X.
 
-A step is one full RK3 time step (three fused stage launches, the
-diagnostics of the step's input state computed inside the first stage, and
-the small fixed-order diagnostics reduction).  Inputs are resident in HBM
+A step is one full RK3 time step (three fused stage launches; the
+diagnostics of the step's input state are computed inside the first stage
+and reduced in a fixed order by a block of the second).  Inputs are resident in HBM
 before the timed region; timing uses HIP events on the stream the kernels
 run on, bracketed by device synchronisation.
 
@@ -592,8 +592,7 @@ def main():
     log(f"bench: {ms_step:.3f} ms/step, {value:.4e} updates/s (wall {wall:.3f} s)")
 
     # Dominant kernel: the fused stage kernel (3 launches per step; the
-    # per-step diagnostics reduction is a one-block kernel of a few us and is
-    # included in the time, so the figure is conservative).
+    # per-step diagnostics reduction is part of the second).
     roofline = None
     if args.algo == "fused":
         bps = BYTES_PER_POINT_STEP[args.precision]
