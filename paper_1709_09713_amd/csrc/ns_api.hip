@@ -169,27 +169,7 @@ static void choose_config(const Consts &c, ns_precision prec, int *tile, int *zc
     choose_config(c, prec, -1, 0, tile, zchunk);
 }
 
-// The brick kernels run small grids whose launch shape is left to the library
-// (no tile, z-chunk or order asked for by the call or the thread); returns the
-// planes of a brick, 0 for the march.  Two planes where that gives at most one
-// brick per compute unit, else four planes up to one brick (FP64, whose brick
-// takes two thirds of a unit's LDS) or four (FP32 storage) per compute unit.
-// Measured, us per RK3 step, FP64 two planes | four | best march: 16^3 14.6 |
-// 16.3 | 21.8, 24^3 15.2 | 17.0 | 22.4, 32^3 19.5 | 18.4 | 23.7, 36^3 - | 29.7
-// | 29.7, 48^3 - | 52.2 | 33.2; FP32 storage: 16^3 13.8 | - | 21.9, 28^3 16.3 |
-// 15.9 | 22.5, 40^3 22.0 | 21.5 | 27.5, 48^3 31.0 | 30.6 | 31.7, 56^3 40.0 |
-// 40.4 | 40.0.  The bricks never outnumber the blocks of the one-plane 8x8
-// march, for which the diagnostic partials of the workspace are sized.
-static int choose_brick(const Consts &c, ns_precision prec, int tile_in, int zchunk_in)
-{
-    const bool automatic = tile_in < 0 && zchunk_in <= 0 && g_tile < 0 && g_zchunk <= 0 && g_order == 0;
-    if (!automatic) return 0;
-    const int64_t cus = compute_units();
-    if (brick_num_blocks(c, 2) <= cus) return 2;
-    if (brick_num_blocks(c, 4) <= (prec == NS_FP64 ? 1 : 4) * cus) return 4;
-    return 0;
-}
-
+// Blocks whose diagnostic partials the workspace has room for.
 static int64_t max_partial_blocks(const Consts &c)
 {
     int64_t m = diag_num_blocks(c);
@@ -198,6 +178,30 @@ static int64_t max_partial_blocks(const Consts &c)
         if (b > m) m = b;
     }
     return m;
+}
+
+// The brick kernels run small grids whose launch shape is left to the library
+// (no tile, z-chunk or order asked for by the call or the thread); returns the
+// planes of a brick, 0 for the march.  Two planes where that gives at most one
+// brick per compute unit, else four planes up to one brick (FP64) or four (FP32
+// storage, whose brick takes half the LDS) per compute unit.
+// Measured, us per RK3 step, FP64 two planes | four | best march: 16^3 14.6 |
+// 16.3 | 21.8, 24^3 15.2 | 17.0 | 22.4, 32^3 19.5 | 18.4 | 23.7, 36^3 - | 29.7
+// | 29.7, 48^3 - | 52.2 | 33.2; FP32 storage: 16^3 13.8 | - | 21.9, 28^3 16.3 |
+// 15.9 | 22.5, 40^3 22.0 | 21.5 | 27.5, 48^3 31.0 | 30.6 | 31.7, 56^3 40.0 |
+// 40.4 | 40.0.  The bricks may not outnumber the blocks that the workspace has
+// diagnostic partials for: those of a march of one-plane chunks, which are fewer
+// on some grids of an odd number of planes (16x165x5: 252 two-plane bricks, 210
+// blocks of 8x8).
+static int choose_brick(const Consts &c, ns_precision prec, int tile_in, int zchunk_in)
+{
+    const bool automatic = tile_in < 0 && zchunk_in <= 0 && g_tile < 0 && g_zchunk <= 0 && g_order == 0;
+    if (!automatic) return 0;
+    const int64_t cus = compute_units(), room = max_partial_blocks(c);
+    const int64_t two = brick_num_blocks(c, 2), four = brick_num_blocks(c, 4);
+    if (two <= cus && two <= room) return 2;
+    if (four <= (prec == NS_FP64 ? 1 : 4) * cus && four <= room) return 4;
+    return 0;
 }
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
