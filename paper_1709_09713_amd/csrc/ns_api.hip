@@ -57,17 +57,18 @@ static int zchunk_for(const Consts &c, int tile, int64_t resident, int64_t *cost
     const int64_t nxy = (int64_t)((c.nx + bx - 1) / bx) * ((c.ny + by - 1) / by);
     int best_z = c.nz;
     int64_t best_cost = -1;
-    for (int k = 1; k <= c.nz / kMinZChunk; ++k) {
+    // k chunks of z planes, for each z the smallest k
+    for (int k = 1;;) {
         const int z = (c.nz + k - 1) / k;
-        const int chunks = (c.nz + z - 1) / z;
-        if (chunks != k) continue;   // the same z as a smaller k
-        const int64_t rounds = (chunks * nxy + resident - 1) / resident;
+        const int64_t rounds = (k * nxy + resident - 1) / resident;
         const int64_t planes = z + fused_extra_planes(tile);
         const int64_t cost = rounds * planes;
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
             best_z = z;
         }
+        if (z <= kMinZChunk) break;
+        k = (c.nz + z - 2) / (z - 1);
     }
     if (cost_out) *cost_out = best_cost;
     return best_z;

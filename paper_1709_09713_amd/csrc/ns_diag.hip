@@ -81,14 +81,16 @@ static int diag_zchunk(const Consts &c)
     }
     int best = c.nz;
     int64_t best_cost = INT64_MAX;
-    for (int k = 1; k <= c.nz; ++k) {
-        const int z = (c.nz + k - 1) / k, chunks = (c.nz + z - 1) / z;
-        if (chunks != k) continue;   // the same z as a smaller k
-        const int64_t cost = (int64_t)((tiles * chunks + kResident - 1) / kResident) * (z + 4);
+    // k chunks of z planes, for each z the smallest k
+    for (int k = 1;;) {
+        const int z = (c.nz + k - 1) / k;
+        const int64_t cost = (int64_t)((tiles * k + kResident - 1) / kResident) * (z + 4);
         if (cost < best_cost) {
             best_cost = cost;
             best = z;
         }
+        if (z <= 1) break;
+        k = (c.nz + z - 2) / (z - 1);
     }
     return best;
 }
