@@ -208,7 +208,7 @@ ns_status ns_stage_stream(const ns_params *p, int32_t stage, double *state, void
  * restores the automatic choice: for NS_FP64 tile 9, or tile 8 where the grid
  * leaves compute units idle; for NS_FP32_STORE tile 0, or tile 9 on grids of
  * about 56^3 to 100^3; and with zchunk 0, for grids of few 8x4x4 bricks per
- * compute unit (up to 32^3 in NS_FP64, 48^3 in NS_FP32_STORE), a kernel that
+ * compute unit (up to 40^3 in NS_FP64, 48^3 in NS_FP32_STORE), a kernel that
  * stages whole bricks instead of marching.  The automatic choices of a
  * precision all give the same bits (per-step diagnostics differ in the order
  * of their sums).

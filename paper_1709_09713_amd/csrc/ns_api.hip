@@ -184,13 +184,14 @@ static int64_t max_partial_blocks(const Consts &c)
 // The brick kernels run small grids whose launch shape is left to the library
 // (no tile, z-chunk or order asked for by the call or the thread); returns the
 // planes of a brick, 0 for the march.  Two planes where that gives at most one
-// brick per compute unit, else four planes up to one brick (FP64) or four (FP32
-// storage, whose brick takes half the LDS) per compute unit.
-// Measured, us per RK3 step, FP64 two planes | four | best march: 16^3 14.6 |
-// 16.3 | 21.8, 24^3 15.2 | 17.0 | 22.4, 32^3 19.5 | 18.4 | 23.7, 36^3 - | 29.7
-// | 29.7, 48^3 - | 52.2 | 33.2; FP32 storage: 16^3 13.8 | - | 21.9, 28^3 16.3 |
-// 15.9 | 22.5, 40^3 22.0 | 21.5 | 27.5, 48^3 31.0 | 30.6 | 31.7, 56^3 40.0 |
-// 40.4 | 40.0.  The bricks may not outnumber the blocks that the workspace has
+// brick per compute unit, else four planes as long as the device holds all
+// bricks at once: two (FP64) or four (FP32 storage) fit the LDS of a compute
+// unit.  Measured, us per RK3 step, bricks | best march: FP64 16^3 14.2 | 21.8,
+// 24^3 14.8 | 22.4, 32^3 17.1 | 23.7, 36^3 27.0 | 29.6, 40^3 27.7 | 30.2, 44^3
+// 37.5 | 32.7, 64x40x28 (560 bricks) 36.8 | 30.5; FP32 storage 16^3 13.8 | 21.9,
+// 32^3 16.1 | 22.9, 40^3 19.8 | 27.5, 48^3 28.9 | 30.4, 60^3 43.6 | 40.7, 64^3
+// 48.7 | 40.4.  Two planes against four: 16^3 FP64 14.6 | 16.3, 32^3 (512 of
+// two) 19.5 | 18.4.  The bricks may not outnumber the blocks that the workspace has
 // diagnostic partials for: those of a march of one-plane chunks, which are fewer
 // on some grids of an odd number of planes (16x165x5: 252 two-plane bricks, 210
 // blocks of 8x8).
@@ -201,7 +202,7 @@ static int choose_brick(const Consts &c, ns_precision prec, int tile_in, int zch
     const int64_t cus = compute_units(), room = max_partial_blocks(c);
     const int64_t two = brick_num_blocks(c, 2), four = brick_num_blocks(c, 4);
     if (two <= cus && two <= room) return 2;
-    if (four <= (prec == NS_FP64 ? 1 : 4) * cus && four <= room) return 4;
+    if (four <= (prec == NS_FP64 ? 2 : 4) * cus && four <= room) return 4;
     return 0;
 }
 

@@ -11,13 +11,15 @@
 // Three barriers in all: after the staging, after the in-plane gradients that
 // are differentiated along z, and before A and B take over C's values.
 //
-// Bound by latency: of 4.9 us a stage at 16^3 (14.6 us an RK3 step, the
+// Bound by latency: of 4.7 us a stage at 16^3 (14.2 us an RK3 step, the
 // march's best shape 21.8), 1.7 us are an empty launch of a chain; the round
 // of loads and its share of the conversions (1.8 us), the gradients (0.3 us)
 // and one thread's arithmetic (about 140 double operations, 1.5 us) are the
-// rest.  Two planes put one wave on each of three SIMDs (16^3 16.3 -> 14.6
-// us a step against four planes) but load nine points per point of the brick
-// against six, so they are taken only while each brick has a compute unit.
+// rest.  Rows of two fields side by side keep a wave's reads on distinct banks
+// (rows of one field: 16^3 14.6 -> 14.2 us a step, 32^3 18.4 -> 17.1).  Two
+// planes put one wave on each of three SIMDs (16^3 16.3 -> 14.6 us a step
+// against four planes) but load nine points per point of the brick against six,
+// so they are taken only while each brick has a compute unit.
 // One kernel for all stages and the residual: with the stage known at compile
 // time, each stage fetched its code anew (0.1 us).
 #include "ns_common.hpp"
@@ -46,7 +48,11 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
     enum { L_R, L_M0, L_M1, L_M2, L_E, L_U, L_V, L_W, L_P, L_T, NF };
     enum { G_A, G_B, G_C, NG };                      // D_x u + D_y v, D_x w, D_y w
     enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_HEAT, NH };
-    __shared__ double lds[NF][CELLS];
+    // Two fields share a row of the array, side by side: with rows of 2 HX cells
+    // the rows that a wave reads at once start in different banks.
+    constexpr int RS = 2 * HX, PS = HY * RS;
+    static_assert(NF % 2 == 0, "fields in pairs");
+    __shared__ double lds[NF / 2][HZ * PS];
     __shared__ double grad[NG][GC];
     __shared__ double vbuf[NH][NT];
     __shared__ double red[DIAG ? NW : 1][4];
@@ -62,13 +68,15 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
     xcd_tile(&tbx, &tby, &tbz, skip);
     const int x0 = tbx * BRX, y0 = tby * BRY, z0 = tbz * BRZ;
     const bool active = x0 + tx < c.nx && y0 + ty < c.ny && z0 + tz < c.nz;
-    const int own = (tz + 2) * HP + (ty + 2) * HX + tx + 2;
+    const int own = (tz + 2) * PS + (ty + 2) * RS + tx + 2;
     const int64_t N = c.N;
     const int64_t pidx = active ? ((int64_t)(z0 + tz) * c.ny + y0 + ty) * c.nx + x0 + tx : 0;
     const double *qin = (const double *)s.qin;
     const double *accsrc = (s.mode >= 2) ? s.acc_in : qin;
     const double c1x = c.c1[0], c1y = c.c1[1], c1z = c.c1[2];
     const double c2x = c.c2[0], c2y = c.c2[1], c2z = c.c2[2];
+
+#define AT(f, at) lds[(f) >> 1][((f) & 1) * HX + (at)]
 
     // ---- stage the brick with its halo, wrapped to valid memory everywhere: a
     // brick starts inside the grid at a multiple of its extent, so that with
@@ -98,27 +106,27 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
     for (int r = 0; r < NLOAD; ++r) {
         const int cell = tid + r * 3 * NT;
         if (CELLS % (3 * NT) != 0 && cell >= CELLS) continue;
+        const int at = (cell / HX) * RS + cell % HX;
         const double rho = q[r][0], m0 = q[r][1], m1 = q[r][2], m2 = q[r][3];
         const double E = q[r][4] - c.rhoE_ref;
         const double inv = recip_f64(rho);
         const double u = m0 * inv, v = m1 * inv, w = m2 * inv;
         const double p = c.gm1 * (E - 0.5 * (m0 * u + m1 * v + m2 * w));
         const double rd = rho - 1.0;
-        lds[L_R][cell] = rd;
-        lds[L_M0][cell] = m0;
-        lds[L_M1][cell] = m1;
-        lds[L_M2][cell] = m2;
-        lds[L_E][cell] = E;
-        lds[L_U][cell] = u;
-        lds[L_V][cell] = v;
-        lds[L_W][cell] = w;
-        lds[L_P][cell] = p;
-        lds[L_T][cell] = (c.gM2 * p - rd) * inv;
+        AT(L_R, at) = rd;
+        AT(L_M0, at) = m0;
+        AT(L_M1, at) = m1;
+        AT(L_M2, at) = m2;
+        AT(L_E, at) = E;
+        AT(L_U, at) = u;
+        AT(L_V, at) = v;
+        AT(L_W, at) = w;
+        AT(L_P, at) = p;
+        AT(L_T, at) = (c.gM2 * p - rd) * inv;
     }
     lds_barrier();
 
-#define AT(f, at) lds[f][at]
-#define LV(f, dz, dy, dx) lds[f][own + (dz) * HP + (dy) * HX + (dx)]
+#define LV(f, dz, dy, dx) AT(f, own + (dz) * PS + (dy) * RS + (dx))
 #define TAPS_X(t, f) const double t[4] = {LV(f, 0, 0, -2), LV(f, 0, 0, -1), LV(f, 0, 0, 1), LV(f, 0, 0, 2)}
 #define TAPS_Y(t, f) const double t[4] = {LV(f, 0, -2, 0), LV(f, 0, -1, 0), LV(f, 0, 1, 0), LV(f, 0, 2, 0)}
 #define TAPS_Z(t, f) const double t[4] = {LV(f, -2, 0, 0), LV(f, -1, 0, 0), LV(f, 1, 0, 0), LV(f, 2, 0, 0)}
@@ -129,11 +137,11 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
 
     // ---- in-plane gradients of the own columns with their z halo
     if (tid < GC) {
-        const int at = (tid / GP) * HP + ((tid % GP) / BRX + 2) * HX + tid % BRX + 2;
+        const int at = (tid / GP) * PS + ((tid % GP) / BRX + 2) * RS + tid % BRX + 2;
         const double ux = d1(AT(L_U, at - 2), AT(L_U, at - 1), AT(L_U, at + 1), AT(L_U, at + 2));
-        const double vy = d1(AT(L_V, at - 2 * HX), AT(L_V, at - HX), AT(L_V, at + HX), AT(L_V, at + 2 * HX));
+        const double vy = d1(AT(L_V, at - 2 * RS), AT(L_V, at - RS), AT(L_V, at + RS), AT(L_V, at + 2 * RS));
         const double wx = d1(AT(L_W, at - 2), AT(L_W, at - 1), AT(L_W, at + 1), AT(L_W, at + 2));
-        const double wy = d1(AT(L_W, at - 2 * HX), AT(L_W, at - HX), AT(L_W, at + HX), AT(L_W, at + 2 * HX));
+        const double wy = d1(AT(L_W, at - 2 * RS), AT(L_W, at - RS), AT(L_W, at + RS), AT(L_W, at + 2 * RS));
         const double gxx = c1x * ux, gyy = c1y * vy;
         grad[G_A][tid] = gxx + gyy;
         grad[G_B][tid] = c1x * wx;

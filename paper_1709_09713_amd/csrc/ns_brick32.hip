@@ -9,9 +9,11 @@
 // term of C's, and go on when C has handed its values over.
 //
 // Bound by latency like the FP64 kernel: 4.6 us a stage at 16^3, 1.7 us of it
-// an empty launch.  us per RK3 step, march (its best tile) -> bricks: 16^3 21.9
-// -> 13.8, 32^3 22.9 -> 16.4, 40^3 27.5 -> 21.4, 48^3 31.7 -> 30.6; one thread
-// per point for all equations 16.0, 17.4, 22.1, 28.9.
+// an empty launch; at 48^3, 3.4 bricks a compute unit, by LDS and vector issue
+// (9.6 us).  us per RK3 step, march (its best tile) -> bricks: 16^3 21.9 -> 13.8,
+// 32^3 22.9 -> 16.1, 40^3 27.5 -> 19.8, 48^3 31.7 -> 28.9.  Rows of one field
+// instead of two: 32^3 16.5, 40^3 21.4, 48^3 30.8 (bank conflicts); one thread per
+// point for all equations: 16.0, 17.4, 22.1, 28.9 at 16^3 to 48^3, before that.
 #include "ns_common.hpp"
 #include "ns_kernels.hpp"
 
@@ -49,7 +51,11 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick32_stage_kernel(Cons
     static_assert(GC <= 3 * NT, "one gradient point per thread");
     enum { L_RHO, L_M0, L_M1, L_M2, L_E, L_U, L_V, L_W, L_P, L_T, NF };
     enum { G_A, G_B, G_C, NG };                      // D_x u + D_y v, D_x w, D_y w
-    __shared__ float lds[NF][CELLS];
+    // Two fields share a row of the array, side by side: with rows of 2 HX cells
+    // the rows that a wave reads at once start in different banks.
+    constexpr int RS = 2 * HX, PS = HY * RS;
+    static_assert(NF % 2 == 0, "fields in pairs");
+    __shared__ float lds[NF / 2][HZ * PS];
     __shared__ float grad[NG][GC];
     // handed over by C: in-plane and z parts of the viscous terms (momentum,
     // then energy) and the in-plane heat conduction
@@ -71,7 +77,7 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick32_stage_kernel(Cons
     xcd_tile(&tbx, &tby, &tbz, skip);
     const int x0 = tbx * BRX, y0 = tby * BRY, z0 = tbz * BRZ;
     const bool active = x0 + tx < c.nx && y0 + ty < c.ny && z0 + tz < c.nz;
-    const int own = (tz + 2) * HP + (ty + 2) * HX + tx + 2;
+    const int own = (tz + 2) * PS + (ty + 2) * RS + tx + 2;
     const int64_t N = c.N;
     const int64_t pidx = active ? ((int64_t)(z0 + tz) * c.ny + y0 + ty) * c.nx + x0 + tx : 0;
     const TIN *qin = (const TIN *)s.qin;
@@ -82,6 +88,8 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick32_stage_kernel(Cons
     const float gm1 = (float)c.gm1, gM2 = (float)c.gM2;
     const float half = 0.5f, third = 1.0f / 3.0f, four3 = 4.0f / 3.0f, two3 = 2.0f / 3.0f;
     const float kz = kappa * c2z;
+
+#define AT(f, at) lds[(f) >> 1][((f) & 1) * HX + (at)]
 
     // ---- stage the brick with its halo, wrapped to valid memory everywhere: a
     // brick starts inside the grid at a multiple of its extent, so that with
@@ -109,6 +117,7 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick32_stage_kernel(Cons
     for (int r = 0; r < NLOAD; ++r) {
         const int cell = tid + r * 3 * NT;
         if (CELLS % (3 * NT) != 0 && cell >= CELLS) continue;
+        const int at = (cell / HX) * RS + cell % HX;
         float rho, m0, m1, m2, E;
         if constexpr (MODE == 1) {
             rho = (float)(q[r][0] - c.rho_ref);
@@ -127,21 +136,21 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick32_stage_kernel(Cons
         const float inv = recip_f32(rhof);
         const float u = m0 * inv, v = m1 * inv, w = m2 * inv;
         const float p = gm1 * (E - half * (m0 * u + m1 * v + m2 * w));
-        lds[L_RHO][cell] = rho;
-        lds[L_M0][cell] = m0;
-        lds[L_M1][cell] = m1;
-        lds[L_M2][cell] = m2;
-        lds[L_E][cell] = E;
-        lds[L_U][cell] = u;
-        lds[L_V][cell] = v;
-        lds[L_W][cell] = w;
-        lds[L_P][cell] = p;
-        lds[L_T][cell] = (gM2 * p - rho) * inv;
+        AT(L_RHO, at) = rho;
+        AT(L_M0, at) = m0;
+        AT(L_M1, at) = m1;
+        AT(L_M2, at) = m2;
+        AT(L_E, at) = E;
+        AT(L_U, at) = u;
+        AT(L_V, at) = v;
+        AT(L_W, at) = w;
+        AT(L_P, at) = p;
+        AT(L_T, at) = (gM2 * p - rho) * inv;
     }
     lds_barrier();
 
-#define LV(f, dy, dx) lds[f][at + (dy) * HX + (dx)]
-#define LZ(f, dz) lds[f][own + (dz) * HP]
+#define LV(f, dy, dx) AT(f, at + (dy) * RS + (dx))
+#define LZ(f, dz) AT(f, own + (dz) * PS)
 #define DX1(f) d1u(LV(f, 0, -2), LV(f, 0, -1), LV(f, 0, 1), LV(f, 0, 2))
 #define DY1(f) d1u(LV(f, -2, 0), LV(f, -1, 0), LV(f, 1, 0), LV(f, 2, 0))
 #define DX1P(f, g)                                                       \
@@ -170,7 +179,7 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick32_stage_kernel(Cons
 
     // ---- in-plane gradients of the own columns with their z halo
     if (tid < GC) {
-        const int at = (tid / GP) * HP + ((tid % GP) / BRX + 2) * HX + tid % BRX + 2;
+        const int at = (tid / GP) * PS + ((tid % GP) / BRX + 2) * RS + tid % BRX + 2;
         const float gxx = c1x * DX1(L_U), gyy = c1y * DY1(L_V);
         grad[G_A][tid] = gxx + gyy;
         grad[G_B][tid] = c1x * DX1(L_W);
@@ -327,6 +336,7 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick32_stage_kernel(Cons
 #undef DZMD
 #undef FLUX_BELOW
 #undef FLUX_ABOVE
+#undef AT
 #undef LV
 #undef LZ
 #undef DX1
