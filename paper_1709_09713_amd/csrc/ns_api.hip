@@ -353,7 +353,7 @@ hipError_t enqueue_fused_step(const FusedPlan &f, double dt, ns_diag *diag_out, 
     a.mode = 2;
     a.diag_partial = nullptr;
     a.fin_partial = f.partial;
-    a.fin_blocks = f.nblk;
+    a.fin_blocks = (int)f.nblk;   // below 2^31 points / 64
     a.fin_out = diag_out;
     e = launch(a);
     if (e != hipSuccess) return e;

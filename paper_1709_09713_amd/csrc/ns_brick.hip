@@ -5,9 +5,9 @@
 // memory: about 7 us a stage at 16^3 whose data would take 0.1 us.  Here a
 // block owns a brick of 8 x 4 x BRZ points and stages it whole, with its halo
 // of two, in one round of loads; then three groups of waves evaluate the
-// equations of one point per thread as the groups of ns_trio.hip do (A mass
-// and energy, B momentum and heat conduction, C viscous terms), with the same
-// expressions in the same order, so that the result is the same bit for bit.
+// equations of one point per thread (A mass, energy and the pressure gradient,
+// B momentum and heat conduction, C viscous terms) with the expressions of
+// ns_trio.hip in the same order, so that the result is the same bit for bit.
 // Three barriers in all: after the staging, after the in-plane gradients that
 // are differentiated along z, and before A and B take over C's values.
 //
@@ -44,10 +44,10 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
     constexpr int NW = 3 * NT / 64;
     static_assert(NT % 64 == 0, "each group must be whole waves");
     static_assert(GC <= 3 * NT, "one gradient point per thread");
-    // staged fields: rho - 1, rho u_i, E - E_ref, u, v, w, p - p_ref, T - 1
-    enum { L_R, L_M0, L_M1, L_M2, L_E, L_U, L_V, L_W, L_P, L_T, NF };
+    // staged fields: rho, rho u_i, E, u, v, w, kinetic energy, e = T / (gamma (gamma - 1) M^2)
+    enum { L_R, L_M0, L_M1, L_M2, L_E, L_U, L_V, L_W, L_K, L_T, NF };
     enum { G_A, G_B, G_C, NG };                      // D_x u + D_y v, D_x w, D_y w
-    enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_HEAT, NH };
+    enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_HEAT, H_PX, H_PY, H_PZ, NH };
     // Two fields share a row of the array, side by side: with rows of 2 HX cells
     // the rows that a wave reads at once start in different banks.
     constexpr int RS = 2 * HX, PS = HY * RS;
@@ -108,12 +108,11 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
         if (CELLS % (3 * NT) != 0 && cell >= CELLS) continue;
         const int at = (cell / HX) * RS + cell % HX;
         const double rho = q[r][0], m0 = q[r][1], m1 = q[r][2], m2 = q[r][3];
-        const double E = q[r][4] - c.rhoE_ref;
+        const double E = q[r][4];
         const double inv = recip_f64(rho);
-        const double u = m0 * inv, v = m1 * inv, w = m2 * inv;
-        const double p = c.gm1 * (E - 0.5 * (m0 * u + m1 * v + m2 * w));
-        const double rd = rho - 1.0;
-        AT(L_R, at) = rd;
+        const double u = quotient_f64(m0, rho, inv), v = quotient_f64(m1, rho, inv), w = quotient_f64(m2, rho, inv);
+        const double ke = 0.5 * (m0 * u + m1 * v + m2 * w);
+        AT(L_R, at) = rho;
         AT(L_M0, at) = m0;
         AT(L_M1, at) = m1;
         AT(L_M2, at) = m2;
@@ -121,8 +120,8 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
         AT(L_U, at) = u;
         AT(L_V, at) = v;
         AT(L_W, at) = w;
-        AT(L_P, at) = p;
-        AT(L_T, at) = (c.gM2 * p - rd) * inv;
+        AT(L_K, at) = ke;
+        AT(L_T, at) = (E - ke) * inv;
     }
     lds_barrier();
 
@@ -149,79 +148,96 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
     }
     lds_barrier();
 
-    double R[3] = {0.0, 0.0, 0.0};
+    // residuals of the own equations; what div u multiplies in them (group A rho
+    // and E + p, B rho u_i); of B the terms with the planes above
+    double R[3] = {0.0, 0.0, 0.0}, car[3] = {0.0, 0.0, 0.0}, up[3][2] = {};
     // diagnostics of the point: group A mass and energy, B the momenta and
     // kinetic energy, C enstrophy
     double dsum[4] = {0.0, 0.0, 0.0, 0.0};
     if (grp == 0) {
         // ------------------------------------------------------------ group A
         const double r = LV(L_R, 0, 0, 0), E = LV(L_E, 0, 0, 0), w = LV(L_W, 0, 0, 0);
-        const double p = LV(L_P, 0, 0, 0), u = LV(L_U, 0, 0, 0), v = LV(L_V, 0, 0, 0);
+        const double ke = LV(L_K, 0, 0, 0), u = LV(L_U, 0, 0, 0), v = LV(L_V, 0, 0, 0);
         double rm = 0.0, re = 0.0;
         {
             TAPS_X(ut, L_U);
             TAPS_X(rt, L_R);
             TAPS_X(et, L_E);
-            TAPS_X(pt4, L_P);
+            TAPS_X(kt, L_K);
             HALF_SUMS(su, u, ut, k.x4, k.xh);
+            double dE[4], dp[4];
+            diffs(E, et, dE);
+            pressure_diffs(dE, ke, kt, dp);
             rm = conv(rm, r, rt, su);
-            re = conv(re, E, et, su);
-            re = __builtin_fma(-c1x, d1_prod(pt4, ut), re);
+            re = conv(re, dE, su);
+            re = __builtin_fma(-k.gx, d1_prod(dp, ut), re);
+            vbuf[H_PX][pt] = k.gx * D1T(dp);
         }
         {
             TAPS_Y(vt, L_V);
             TAPS_Y(rt, L_R);
             TAPS_Y(et, L_E);
-            TAPS_Y(pt4, L_P);
+            TAPS_Y(kt, L_K);
             HALF_SUMS(sv, v, vt, k.y4, k.yh);
+            double dE[4], dp[4];
+            diffs(E, et, dE);
+            pressure_diffs(dE, ke, kt, dp);
             rm = conv(rm, r, rt, sv);
-            re = conv(re, E, et, sv);
-            re = __builtin_fma(-c1y, d1_prod(pt4, vt), re);
+            re = conv(re, dE, sv);
+            re = __builtin_fma(-k.gy, d1_prod(dp, vt), re);
+            vbuf[H_PY][pt] = k.gy * D1T(dp);
         }
         {
-            // fluxes between the point's plane and the two below and above,
-            // added in the march's order
+            // terms between the point's plane and the two below and above, added
+            // in the march's order
             TAPS_Z(wt, L_W);
             TAPS_Z(rt, L_R);
             TAPS_Z(et, L_E);
-            TAPS_Z(pz, L_P);
-            const double q0 = p * w;
-            double mf[4], ef[4];
+            TAPS_Z(kt, L_K);
+            double mf[4], ef[4], pf[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const double qt = pz[t] * wt[t];
-                const double st = (t == 1 || t == 2 ? k.z4 : k.zh) * (w + wt[t]);
-                mf[t] = (r + rt[t]) * st;
-                ef[t] = (E + et[t]) * st + (t == 1 || t == 2 ? k.z8 : c1z) * (q0 + qt);
+                const bool below = t < 2, near = t == 1 || t == 2;
+                const double st = (near ? k.z4 : k.zh) * (w + wt[t]);
+                // from the lower to the upper plane of the pair
+                const double dr = below ? r - rt[t] : rt[t] - r, dE = below ? E - et[t] : et[t] - E;
+                const double dK = below ? ke - kt[t] : kt[t] - ke;
+                mf[t] = dr * st;
+                pf[t] = (near ? k.gz8 : k.gz) * (dE - dK);
+                ef[t] = __builtin_fma(pf[t], wt[t], dE * st);
             }
-            rm = rm + (mf[1] - mf[0]);
+            rm = rm - (mf[1] - mf[0]);
             rm -= mf[2];
             rm += mf[3];
-            re = re + (ef[1] - ef[0]);
+            re = re - (ef[1] - ef[0]);
             re -= ef[2];
             re += ef[3];
+            double pz = pf[1] - pf[0];
+            pz += pf[2];
+            pz -= pf[3];
+            vbuf[H_PZ][pt] = pz;
         }
         R[0] = rm;
         R[1] = re;
+        car[0] = r;
+        car[1] = __builtin_fma(c.gm1, E - ke, E);
     } else if (grp == 1) {
         // ------------------------------------------------------------ group B
         const double m[3] = {LV(L_M0, 0, 0, 0), LV(L_M1, 0, 0, 0), LV(L_M2, 0, 0, 0)};
         const double u = LV(L_U, 0, 0, 0), v = LV(L_V, 0, 0, 0), w = LV(L_W, 0, 0, 0);
-        const double p = LV(L_P, 0, 0, 0), T = LV(L_T, 0, 0, 0);
-        double he, px, py, rr[3];
+        const double T = LV(L_T, 0, 0, 0);
+        double he, rr[3];
         {
             TAPS_X(ut, L_U);
             TAPS_X(m0t, L_M0);
             TAPS_X(m1t, L_M1);
             TAPS_X(m2t, L_M2);
             TAPS_X(tt, L_T);
-            TAPS_X(pt4, L_P);
             HALF_SUMS(su, u, ut, k.x4, k.xh);
             he = k.kx * D2T(tt, T);
             rr[0] = conv(0.0, m[0], m0t, su);
             rr[1] = conv(0.0, m[1], m1t, su);
             rr[2] = conv(0.0, m[2], m2t, su);
-            px = c1x * D1T(pt4);
         }
         {
             TAPS_Y(vt, L_V);
@@ -229,18 +245,15 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
             TAPS_Y(m1t, L_M1);
             TAPS_Y(m2t, L_M2);
             TAPS_Y(tt, L_T);
-            TAPS_Y(pt4, L_P);
             HALF_SUMS(sv, v, vt, k.y4, k.yh);
             he += k.ky * D2T(tt, T);
             rr[0] = conv(rr[0], m[0], m0t, sv);
             rr[1] = conv(rr[1], m[1], m1t, sv);
             rr[2] = conv(rr[2], m[2], m2t, sv);
-            py = c1y * D1T(pt4);
         }
         {
             TAPS_Z(wt, L_W);
             TAPS_Z(tt, L_T);
-            TAPS_Z(pz, L_P);
             double sz[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) sz[t] = (t == 1 || t == 2 ? k.z4 : k.zh) * (w + wt[t]);
@@ -249,16 +262,11 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
                 TAPS_Z(mt, L_M0 + f);
                 double fl[4];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    fl[t] = (m[f] + mt[t]) * sz[t];
-                    if (f == 2) fl[t] = __builtin_fma(t == 1 || t == 2 ? k.z8 : c1z, p + pz[t], fl[t]);
-                }
-                double ra = rr[f] + (fl[1] - fl[0]);
-                if (f == 0) ra -= px;
-                if (f == 1) ra -= py;
-                ra -= fl[2];
-                ra += fl[3];
-                R[f] = ra;
+                for (int t = 0; t < 4; ++t) fl[t] = (t < 2 ? m[f] - mt[t] : mt[t] - m[f]) * sz[t];
+                R[f] = rr[f] - (fl[1] - fl[0]);
+                car[f] = m[f];
+                up[f][0] = fl[2];
+                up[f][1] = fl[3];
             }
             double hf[4];
 #pragma unroll
@@ -318,23 +326,31 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
         vbuf[H_VX][pt] = Vx;
         vbuf[H_VY][pt] = Vy;
         vbuf[H_VZ][pt] = Vz;
-        vbuf[H_EN][pt] = c.inv_re * (u * Vx + v * Vy + w * Vz + (phi + phz)) - c.H_ref * div;
+        vbuf[H_EN][pt] = c.inv_re * (u * Vx + v * Vy + w * Vz + (phi + phz));
         vbuf[H_DIV][pt] = div;
         if constexpr (DIAG) {
             const double ox = cc - Gyz, oy = Gxz - bb;
-            dsum[0] = 0.5 * (1.0 + LV(L_R, 0, 0, 0)) * (ox * ox + oy * oy + oz * oz);
+            dsum[0] = 0.5 * LV(L_R, 0, 0, 0) * (ox * ox + oy * oy + oz * oz);
         }
     }
     lds_barrier();
 
     // ---- C's part of the equations, RK update, output
     if (grp < 2 && active) {
+        const double div = vbuf[H_DIV][pt];
         if (grp == 0) {
-            R[0] = R[0] - vbuf[H_DIV][pt];
-            R[1] = R[1] + (vbuf[H_EN][pt] + vbuf[H_HEAT][pt]);
+            R[0] = __builtin_fma(-car[0], div, R[0]);
+            R[1] = __builtin_fma(-car[1], div, R[1] + (vbuf[H_EN][pt] + vbuf[H_HEAT][pt]));
         } else {
 #pragma unroll
-            for (int f = 0; f < 3; ++f) R[f] = R[f] + c.inv_re * vbuf[H_VX + f][pt];
+            for (int f = 0; f < 3; ++f) {
+                if (f < 2) R[f] -= vbuf[H_PX + f][pt];
+                R[f] -= up[f][0];
+                R[f] += up[f][1];
+                R[f] = __builtin_fma(-car[f], div, R[f]);
+                if (f == 2) R[f] -= vbuf[H_PZ][pt];
+                R[f] = __builtin_fma(c.inv_re, vbuf[H_VX + f][pt], R[f]);
+            }
         }
 #pragma unroll
         for (int f = 0; f < 3; ++f) {

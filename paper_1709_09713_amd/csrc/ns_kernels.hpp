@@ -28,9 +28,11 @@ struct StageArgs {
     double *diag_partial;   // per-block diagnostic partial sums, or nullptr
     const double *grad;     // stored velocity gradients (intermediate-storage class)
     int order;              // in-plane evaluation order: 0 by equation, 1 by direction
-    // stage 2 after a stage 1 with diagnostics: reduce its partials
+    // stage 2 after a stage 1 with diagnostics: reduce its partials (the count
+    // beside the other ints: eight bytes more put the grid's size, which follows
+    // the arguments, on a cache line of its own, 0.2 us a stage at 16^3)
+    int fin_blocks;
     const double *fin_partial;
-    int64_t fin_blocks;
     ns_diag *fin_out;       // nullptr: nothing to reduce
 };
 
@@ -47,9 +49,9 @@ __device__ __forceinline__ int finalize_layer(const Consts &c, const StageArgs &
         const int t = threadIdx.y * blockDim.x + threadIdx.x;
         double v[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll 2
-        for (int64_t b = t; b < s.fin_blocks; b += 64)
+        for (int b = t; b < s.fin_blocks; b += 64)
 #pragma unroll
-            for (int q = 0; q < 7; ++q) v[q] += s.fin_partial[b * kDiag + q];
+            for (int q = 0; q < 7; ++q) v[q] += s.fin_partial[(int64_t)b * kDiag + q];
 #pragma unroll
         for (int q = 0; q < 7; ++q) v[q] = wave_sum(v[q]);
         if (t == 63) write_diag(c, v, s.fin_out);

@@ -8,8 +8,8 @@
 // low-storage RK3 update of the generic-algorithm figure in the same pass),
 // but a block holds three threads per column of its tile:
 //  * group A (threads [0, NT)) loads and stages each plane and evaluates the
-//    mass and energy equations and the in-plane pressure gradient;
-//  * group B evaluates the three momentum equations and heat conduction;
+//    energy equation and the pressure gradient;
+//  * group B evaluates the mass and momentum equations and heat conduction;
 //  * group C evaluates div u, the viscous vector V_i = lap u_i + (1/3) d_i
 //    div u and the viscous work and dissipation.
 // The groups hand values over through vbuf, double buffered like the planes:
@@ -17,22 +17,31 @@
 // after the plane barrier.  C finishes plane zp - 2 in that step, A and B
 // finish plane zp - 3.
 //
-// Arithmetic.  The skew-symmetric convective terms are taken pair by pair:
-// with the first-derivative weights c_k (odd in k, so they sum to zero)
-//   1/2 [D(f u) + f D u + u D f] = sum_k c_k (f_0 + f_k) (u_0 + u_k) / 2,
-// one addition and one multiply-add per tap where the three stencils of the
-// left side take about twice that; along z the term of a pair of planes is
-// formed once and added to one plane and taken from the other, so a residual
-// is complete two planes on and no ring of five planes is needed (the viscous
-// vector and the velocity gradient still gather from one).  Density, energy,
-// pressure and temperature are staged as deviations from the uniform
-// reference state (rho = 1, p = 1 / (gamma M^2)), whose share of the mass
-// and energy equations is -div u and -H_ref div u: the sums of a pair then
-// lose nothing to the large means.  Relative rms error of the residual
-// against 80-bit arithmetic (64^3, M = 0.1; stencils of the full fields ->
-// here): mass 3.7e-15 -> 3.6e-15, momentum 5.4e-13 .. 7.3e-13 -> 2.5e-15 ..
-// 5.7e-15, energy 4.9e-15 -> 3.6e-15; the same order of gains for M = 0.05
-// to 0.4 and on 161x97x31 and 20x17x24.
+// Arithmetic.  The skew-symmetric convective terms are taken in differences to
+// the point's own value: with the first-derivative weights c_k (odd in k, so
+// they sum to zero)
+//   1/2 [D(f u) + f D u + u D f] = f_0 D u + sum_k c_k (f_k - f_0) (u_0 + u_k) / 2,
+// one subtraction and one multiply-add per tap where the three stencils of the
+// left side take about twice that, and f_0 div u once per point.  Along z the
+// term of a pair of planes is formed once and added to both, so a residual is
+// complete two planes on and no ring of five planes is needed (the viscous
+// vector and the velocity gradient still gather from one).  Pressure enters by
+// its differences too, formed from those of energy and kinetic energy:
+//   D(p u) = p_0 D u + sum_k c_k (p_k - p_0) u_k.
+// Differences lose nothing to a large mean, whatever it is.  No reference state
+// is taken out: a caller's density and energy need not be near any, and those
+// below it would lose their low bits.  Temperature is staged as the specific
+// internal energy e, one rounding less.  Relative rms error of the residual
+// (mass, worst momentum, energy) against 80-bit arithmetic, 64x40x28, the
+// two-group kernel that formed the stencils of the full fields -> deviations
+// from a reference state -> here: random state at M = 0.1 1.8e-16 2.2e-13
+// 2.4e-16 -> 1.9e-16 1.7e-15 2.0e-16 -> 1.6e-16 2.0e-16 1.7e-16; the same with
+// density and energy times 1e-4 1.8e-16 6.7e-16 3.9e-14 -> 3.8e-12 6.6e-12
+// 3.0e-10 -> 1.6e-16 4.5e-16 3.4e-14; inviscid, p = 1 at M = 1e-3 1.8e-16 6.0e-15
+// 2.1e-16 -> 1.9e-16 2.1e-9 1.2e-10 -> 1.6e-16 1.6e-16 1.7e-16; mean flow 4.8e-15
+// 1.2e-14 5.7e-15 -> 4.6e-15 1.7e-14 1.1e-14 -> 3.3e-15 2.7e-15 3.3e-15.  Against
+// the deviations a step costs 0.7% (256^3) to 3.5% (101x77x53) more: one addition
+// per pressure tap, and div u times the point's own values.
 //
 // What bounds it: at 512^3 a stage moves 19-26 GB (4.3 ms at the rate of a
 // plain kernel of the same access pattern for stage 2, 3.1 ms for stages 1
@@ -84,15 +93,15 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
     constexpr int NLOAD = (HP + PW * NT - 1) / (PW * NT);
     constexpr int NW = 3 * NT / 64;
     static_assert(NT % 64 == 0, "each group must be whole waves");
-    // staged fields: rho - 1, rho u_i, E - E_ref, u, v, w, p - p_ref, T - 1
-    enum { L_R, L_M0, L_M1, L_M2, L_E, L_U, L_V, L_W, L_P, L_T, NF };
+    // staged fields: rho, rho u_i, E, u, v, w, kinetic energy, e = T / (gamma (gamma - 1) M^2)
+    enum { L_R, L_M0, L_M1, L_M2, L_E, L_U, L_V, L_W, L_K, L_T, NF };
     // handed over: V, dissipative energy terms and div u of plane zp - 2 (C),
-    // heat conduction of plane zp - 2 (B), in-plane pressure gradient of
-    // plane zp (A); with diagnostics omega_z of plane zp and omega_x, omega_y
-    // of plane zp - 2 (C)
-    enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_HEAT, H_PX, H_PY, H_OZ, H_OX, H_OY };
+    // heat conduction of plane zp - 2 (B), pressure gradient, in-plane of plane
+    // zp and along z of plane zp - 2 (A); with diagnostics omega_z of plane zp
+    // and omega_x, omega_y of plane zp - 2 (C)
+    enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_HEAT, H_PX, H_PY, H_PZ, H_OZ, H_OX, H_OY };
     __shared__ __attribute__((aligned(16))) double lds[2][NF][HP];
-    __shared__ double vbuf[2][DIAG ? 11 : 8][NT];
+    __shared__ double vbuf[2][DIAG ? 12 : 9][NT];
     __shared__ double red[NW][kDiag];
     __shared__ double sbuf[GRAD ? 2 : 1][GRAD ? HY : 1][BX];   // GRAD: D_x u + D_z w with two halo rows each side
 
@@ -124,8 +133,8 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
     const double inv_re = c.inv_re;
 
     // per-column diagnostic sums of stage 1, added in program order
-    // (deterministic): group A mass, energy and enstrophy, group B the
-    // momenta and kinetic energy
+    // (deterministic): group A energy, kinetic energy and enstrophy, group B
+    // mass and momenta
     double dr[4] = {0.0, 0.0, 0.0, 0.0};
 
     // The march covers planes z0-2 .. z1+2 (A and B finish a plane three
@@ -184,11 +193,11 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
         // Group A alone loads: pairs of points with one 16-byte load each
         // (even nx).  Sharing the loads between A and B, one point per
         // thread, balances the arithmetic better but was 10% slower.
-        enum { Z_R, Z_E, Z_W, Z_Q, NZ };
-        enum { R_MASS, R_EN, NR };
-        double qz[5][NZ];      // rho', E', w, p' w of planes zp .. zp - 2 (zp - 3 with diagnostics)
-        double ra[5][NR];      // pending mass and energy residuals
-        double acc[2] = {0.0, 0.0}, accn[2] = {0.0, 0.0};   // of this and the next step's point
+        enum { Z_E, Z_K, Z_W, Z_R, NZ };
+        enum { R_EN, R_PZ, NR };
+        double qz[5][NZ];      // E, kinetic energy (with diagnostics rho) of planes zp .. zp - 3, w of zp .. zp - 2
+        double ra[5][NR];      // pending energy residual and pressure gradient along z
+        double acc = 0.0, accn = 0.0;   // of this and the next step's point
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
 #pragma unroll
@@ -240,18 +249,13 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
 #pragma unroll
                 for (int j = 0; j < PW; ++j) {
                     const double rho = pf[r][0][j], m0 = pf[r][1][j], m1 = pf[r][2][j], m2 = pf[r][3][j];
-                    const double E = pf[r][4][j] - c.rhoE_ref;
+                    const double E = pf[r][4][j];
                     const double inv = recip_f64(rho);
-                    // The correction of the quotients is kept where it costs
-                    // nothing (GRAD, bound by memory); the fused form is 1%
-                    // slower with it, and has a smaller error than the full
-                    // stencils without it.
-                    const double u = GRAD ? quotient_f64(m0, rho, inv) : m0 * inv;
-                    const double v = GRAD ? quotient_f64(m1, rho, inv) : m1 * inv;
-                    const double w = GRAD ? quotient_f64(m2, rho, inv) : m2 * inv;
-                    const double p = c.gm1 * (E - 0.5 * (m0 * u + m1 * v + m2 * w));
-                    const double rd = rho - 1.0;
-                    val[L_R][j] = rd;
+                    const double u = quotient_f64(m0, rho, inv);
+                    const double v = quotient_f64(m1, rho, inv);
+                    const double w = quotient_f64(m2, rho, inv);
+                    const double ke = 0.5 * (m0 * u + m1 * v + m2 * w);
+                    val[L_R][j] = rho;
                     val[L_M0][j] = m0;
                     val[L_M1][j] = m1;
                     val[L_M2][j] = m2;
@@ -259,8 +263,8 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                     val[L_U][j] = u;
                     val[L_V][j] = v;
                     val[L_W][j] = w;
-                    val[L_P][j] = p;
-                    val[L_T][j] = (c.gM2 * p - rd) * inv;
+                    val[L_K][j] = ke;
+                    val[L_T][j] = (E - ke) * inv;
                 }
                 const int i = lcell[r];
 #pragma unroll
@@ -299,62 +303,65 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
             load_plane(zp + 2, pg);
             if constexpr (MODE >= 1) {
                 const int64_t pn = acc_point(zf + 1);
-                acc[0] = accn[0];
-                acc[1] = accn[1];
-                accn[0] = __builtin_nontemporal_load(accsrc + pn);
-                accn[1] = __builtin_nontemporal_load(accsrc + 4 * N + pn);
+                acc = accn;
+                accn = __builtin_nontemporal_load(accsrc + 4 * N + pn);
             }
-            const double r = LV(L_R, 0, 0), E = LV(L_E, 0, 0), w = LV(L_W, 0, 0);
-            const double p = LV(L_P, 0, 0);
-            double rm = 0.0, re = 0.0;
+            const double E = LV(L_E, 0, 0), ke = LV(L_K, 0, 0), w = LV(L_W, 0, 0);
+            double re = 0.0;
             if (do_plane) {
                 const double u = LV(L_U, 0, 0), v = LV(L_V, 0, 0);
                 {
                     TAPS_X(ut, L_U);
-                    TAPS_X(rt, L_R);
                     TAPS_X(et, L_E);
-                    TAPS_X(pt4, L_P);
+                    TAPS_X(kt, L_K);
                     HALF_SUMS(su, u, ut, k.x4, k.xh);
-                    rm = conv(rm, r, rt, su);
-                    re = conv(re, E, et, su);
-                    re = __builtin_fma(-c1x, d1_prod(pt4, ut), re);
-                    vbuf[b][H_PX][pt] = c1x * D1T(pt4);
+                    double dE[4], dp[4];
+                    diffs(E, et, dE);
+                    pressure_diffs(dE, ke, kt, dp);
+                    re = conv(re, dE, su);
+                    re = __builtin_fma(-k.gx, d1_prod(dp, ut), re);
+                    vbuf[b][H_PX][pt] = k.gx * D1T(dp);
                 }
                 {
                     TAPS_Y(vt, L_V);
-                    TAPS_Y(rt, L_R);
                     TAPS_Y(et, L_E);
-                    TAPS_Y(pt4, L_P);
+                    TAPS_Y(kt, L_K);
                     HALF_SUMS(sv, v, vt, k.y4, k.yh);
-                    rm = conv(rm, r, rt, sv);
-                    re = conv(re, E, et, sv);
-                    re = __builtin_fma(-c1y, d1_prod(pt4, vt), re);
-                    vbuf[b][H_PY][pt] = c1y * D1T(pt4);
+                    double dE[4], dp[4];
+                    diffs(E, et, dE);
+                    pressure_diffs(dE, ke, kt, dp);
+                    re = conv(re, dE, sv);
+                    re = __builtin_fma(-k.gy, d1_prod(dp, vt), re);
+                    vbuf[b][H_PY][pt] = k.gy * D1T(dp);
+                }
+                if constexpr (DIAG) {
+                    if (active) dr[1] += ke;
                 }
             }
-            // fluxes between plane zp and planes zp - 1, zp - 2
+            // terms between plane zp and planes zp - 1, zp - 2
             {
-                const double q = p * w;
-                const double s1 = k.z4 * (w + qz[SM1][Z_W]), s2 = k.zh * (w + qz[SM2][Z_W]);
-                const double m1 = (r + qz[SM1][Z_R]) * s1, m2 = (r + qz[SM2][Z_R]) * s2;
-                const double e1 = (E + qz[SM1][Z_E]) * s1 + k.z8 * (q + qz[SM1][Z_Q]);
-                const double e2 = (E + qz[SM2][Z_E]) * s2 + c1z * (q + qz[SM2][Z_Q]);
-                ra[S0][R_MASS] = rm + (m1 - m2);
-                ra[SM1][R_MASS] -= m1;
-                ra[SM2][R_MASS] += m2;
-                ra[S0][R_EN] = re + (e1 - e2);
-                ra[SM1][R_EN] -= e1;
-                ra[SM2][R_EN] += e2;
+                const double w1 = qz[SM1][Z_W], w2 = qz[SM2][Z_W];
+                const double s1 = k.z4 * (w + w1), s2 = k.zh * (w + w2);
+                const double dE1 = E - qz[SM1][Z_E], dE2 = E - qz[SM2][Z_E];
+                const double p1 = k.gz8 * (dE1 - (ke - qz[SM1][Z_K])), p2 = k.gz * (dE2 - (ke - qz[SM2][Z_K]));
+                const double e1 = dE1 * s1, e2 = dE2 * s2;
+                ra[S0][R_EN] = re - (__builtin_fma(p1, w1, e1) - __builtin_fma(p2, w2, e2));
+                ra[SM1][R_EN] -= __builtin_fma(p1, w, e1);
+                ra[SM2][R_EN] += __builtin_fma(p2, w, e2);
+                ra[S0][R_PZ] = p1 - p2;
+                ra[SM1][R_PZ] += p1;
+                ra[SM2][R_PZ] -= p2;
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
+                for (int q = 0; q < NR; ++q) {
                     KEEP(ra[S0][q]);
                     KEEP(ra[SM1][q]);
                     KEEP(ra[SM2][q]);
                 }
-                qz[S0][Z_R] = r;
+                vbuf[b][H_PZ][pt] = ra[SM2][R_PZ];
                 qz[S0][Z_E] = E;
+                if constexpr (DIAG) qz[S0][Z_R] = LV(L_R, 0, 0);
+                qz[S0][Z_K] = ke;
                 qz[S0][Z_W] = w;
-                qz[S0][Z_Q] = q;
             }
 
             // stage plane zp + 1 into the other buffer (last read in the
@@ -364,26 +371,22 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
             // finish plane zp - 3: group C's part, RK update, output
             if (do_fin) {
                 const int64_t pidx = (int64_t)zf * c.nxy + col;
-                const double R0 = ra[SM3][R_MASS] - vbuf[b ^ 1][H_DIV][pt];
-                const double R4 = ra[SM3][R_EN] + (vbuf[b ^ 1][H_EN][pt] + vbuf[b ^ 1][H_HEAT][pt]);
+                const double E3 = qz[SM3][Z_E];
+                const double H = __builtin_fma(c.gm1, E3 - qz[SM3][Z_K], E3);   // E + p
+                const double R = __builtin_fma(-H, vbuf[b ^ 1][H_DIV][pt],
+                                               ra[SM3][R_EN] + (vbuf[b ^ 1][H_EN][pt] + vbuf[b ^ 1][H_HEAT][pt]));
                 if (active) {
                     if constexpr (MODE == 0) {
-                        s.rout[pidx] = R0;
-                        s.rout[4 * N + pidx] = R4;
+                        s.rout[4 * N + pidx] = R;
                     } else {
                         if constexpr (DIAG) {
-                            dr[0] += acc[0];
-                            dr[1] += acc[1];
+                            dr[0] += acc;
                             const double ox = vbuf[b ^ 1][H_OX][pt], oy = vbuf[b ^ 1][H_OY][pt];
-                            dr[2] += (0.5 * (1.0 + qz[SM3][Z_R])) * (ox * ox + oy * oy);
+                            dr[2] += (0.5 * qz[SM3][Z_R]) * (ox * ox + oy * oy);
                         }
-                        double *qo = (double *)s.qout;
-                        __builtin_nontemporal_store(acc[0] + s.a_dt * R0, qo + pidx);
-                        __builtin_nontemporal_store(acc[1] + s.a_dt * R4, qo + 4 * N + pidx);
-                        if constexpr (MODE < 3) {
-                            __builtin_nontemporal_store(acc[0] + s.b_dt * R0, s.acc_out + pidx);
-                            __builtin_nontemporal_store(acc[1] + s.b_dt * R4, s.acc_out + 4 * N + pidx);
-                        }
+                        __builtin_nontemporal_store(acc + s.a_dt * R, (double *)s.qout + 4 * N + pidx);
+                        if constexpr (MODE < 3)
+                            __builtin_nontemporal_store(acc + s.b_dt * R, s.acc_out + 4 * N + pidx);
                     }
                 }
             }
@@ -391,7 +394,7 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                 // omega_z is complete in its plane
                 if (active && zp - 1 >= z0 && zp - 1 < z1) {
                     const double oz = vbuf[b ^ 1][H_OZ][pt];
-                    dr[2] += (0.5 * (1.0 + qz[SM1][Z_R])) * (oz * oz);
+                    dr[2] += (0.5 * qz[SM1][Z_R]) * (oz * oz);
                 }
             }
             next_plane();
@@ -405,17 +408,18 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
         MARCH(step)
     } else if (grp == 1) {
         // ------------------------------------------------------------ group B
-        enum { Z_M0, Z_M1, Z_M2, Z_W, Z_P, Z_T, NZ };
-        double qz[5][NZ];      // rho u, rho v, rho w, w, p' and T' of planes zp .. zp - 2
-        double ra[5][3];       // pending momentum residuals
+        // the fields carried with the flow: density and momenta (the first four)
+        enum { Z_W = 4, Z_T, NZ };
+        double qz[5][NZ];      // rho and rho u_i of planes zp .. zp - 3, w and T of zp .. zp - 2
+        double ra[5][4];       // pending mass and momentum residuals
         double rh[5] = {0.0, 0.0, 0.0, 0.0, 0.0};   // pending heat conduction
-        double acc[3] = {0.0, 0.0, 0.0}, accn[3] = {0.0, 0.0, 0.0};
+        double acc[4] = {0.0, 0.0, 0.0, 0.0}, accn[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
 #pragma unroll
             for (int f = 0; f < NZ; ++f) qz[q][f] = 0.0;
 #pragma unroll
-            for (int f = 0; f < 3; ++f) ra[q][f] = 0.0;
+            for (int f = 0; f < 4; ++f) ra[q][f] = 0.0;
         }
 
         auto step = [&](auto phc, int zp) {
@@ -427,67 +431,80 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
             if constexpr (MODE >= 1) {
                 const int64_t pn = acc_point(zf + 1);
 #pragma unroll
-                for (int f = 0; f < 3; ++f) {
+                for (int f = 0; f < 4; ++f) {
                     acc[f] = accn[f];
-                    accn[f] = __builtin_nontemporal_load(accsrc + (1 + f) * N + pn);
+                    accn[f] = __builtin_nontemporal_load(accsrc + f * N + pn);
                 }
             }
-            const double m[3] = {LV(L_M0, 0, 0), LV(L_M1, 0, 0), LV(L_M2, 0, 0)};
-            const double w = LV(L_W, 0, 0), p = LV(L_P, 0, 0), T = LV(L_T, 0, 0);
+            // Residuals of plane zp - 3: pressure gradient along z from A, div u
+            // and the viscous vector from C.  Before the taps of this plane are
+            // read, so that its terms do not occupy registers beside them; the
+            // update is left to the step's end, where the accumulator has had
+            // two steps to arrive.
+            double R[4] = {0.0, 0.0, 0.0, 0.0};
+            if (do_fin) {
+                const double div = vbuf[b ^ 1][H_DIV][pt];
+#pragma unroll
+                for (int f = 0; f < 4; ++f) {
+                    R[f] = __builtin_fma(-qz[SM3][f], div, ra[SM3][f]);
+                    if (f == 3) R[f] -= vbuf[b ^ 1][H_PZ][pt];
+                    if (f > 0) R[f] = __builtin_fma(inv_re, vbuf[b ^ 1][H_VX + f - 1][pt], R[f]);
+                    KEEP(R[f]);
+                }
+            }
+            const double m[4] = {LV(L_R, 0, 0), LV(L_M0, 0, 0), LV(L_M1, 0, 0), LV(L_M2, 0, 0)};
+            const double w = LV(L_W, 0, 0), T = LV(L_T, 0, 0);
             double he = 0.0;
-            double rr[3] = {0.0, 0.0, 0.0};
+            double rr[4] = {0.0, 0.0, 0.0, 0.0};
             if (do_plane) {
                 const double u = LV(L_U, 0, 0), v = LV(L_V, 0, 0);
                 {
                     TAPS_X(ut, L_U);
+                    TAPS_X(rt, L_R);
                     TAPS_X(m0t, L_M0);
                     TAPS_X(m1t, L_M1);
                     TAPS_X(m2t, L_M2);
                     TAPS_X(tt, L_T);
                     HALF_SUMS(su, u, ut, k.x4, k.xh);
                     he = k.kx * D2T(tt, T);
-                    rr[0] = conv(0.0, m[0], m0t, su);
-                    rr[1] = conv(0.0, m[1], m1t, su);
-                    rr[2] = conv(0.0, m[2], m2t, su);
+                    rr[0] = conv(0.0, m[0], rt, su);
+                    rr[1] = conv(0.0, m[1], m0t, su);
+                    rr[2] = conv(0.0, m[2], m1t, su);
+                    rr[3] = conv(0.0, m[3], m2t, su);
                 }
                 {
                     TAPS_Y(vt, L_V);
+                    TAPS_Y(rt, L_R);
                     TAPS_Y(m0t, L_M0);
                     TAPS_Y(m1t, L_M1);
                     TAPS_Y(m2t, L_M2);
                     TAPS_Y(tt, L_T);
                     HALF_SUMS(sv, v, vt, k.y4, k.yh);
                     he += k.ky * D2T(tt, T);
-                    rr[0] = conv(rr[0], m[0], m0t, sv);
-                    rr[1] = conv(rr[1], m[1], m1t, sv);
-                    rr[2] = conv(rr[2], m[2], m2t, sv);
-                }
-                if constexpr (DIAG) {
-                    if (active) dr[3] += 0.5 * (m[0] * u + m[1] * v + m[2] * w);
+                    rr[0] = conv(rr[0], m[0], rt, sv);
+                    rr[1] = conv(rr[1], m[1], m0t, sv);
+                    rr[2] = conv(rr[2], m[2], m1t, sv);
+                    rr[3] = conv(rr[3], m[3], m2t, sv);
                 }
             }
             // the in-plane pressure gradient of plane zp - 1, from A's last
             // step (outside the chunk an undefined value, in a residual that
             // is never output)
-            ra[SM1][0] -= vbuf[b ^ 1][H_PX][pt];
-            ra[SM1][1] -= vbuf[b ^ 1][H_PY][pt];
-            // fluxes between plane zp and planes zp - 1, zp - 2
+            ra[SM1][1] -= vbuf[b ^ 1][H_PX][pt];
+            ra[SM1][2] -= vbuf[b ^ 1][H_PY][pt];
+            // terms between plane zp and planes zp - 1, zp - 2
             {
                 const double s1 = k.z4 * (w + qz[SM1][Z_W]), s2 = k.zh * (w + qz[SM2][Z_W]);
 #pragma unroll
-                for (int f = 0; f < 3; ++f) {
-                    double f1 = (m[f] + qz[SM1][Z_M0 + f]) * s1, f2 = (m[f] + qz[SM2][Z_M0 + f]) * s2;
-                    if (f == 2) {
-                        f1 = __builtin_fma(k.z8, p + qz[SM1][Z_P], f1);
-                        f2 = __builtin_fma(c1z, p + qz[SM2][Z_P], f2);
-                    }
-                    ra[S0][f] = rr[f] + (f1 - f2);
+                for (int f = 0; f < 4; ++f) {
+                    const double f1 = (m[f] - qz[SM1][f]) * s1, f2 = (m[f] - qz[SM2][f]) * s2;
+                    ra[S0][f] = rr[f] - (f1 - f2);
                     ra[SM1][f] -= f1;
                     ra[SM2][f] += f2;
                     KEEP(ra[S0][f]);
                     KEEP(ra[SM1][f]);
                     KEEP(ra[SM2][f]);
-                    qz[S0][Z_M0 + f] = m[f];
+                    qz[S0][f] = m[f];
                 }
                 const double h1 = k.kz16 * (T - qz[SM1][Z_T]), h2 = k.kz * (T - qz[SM2][Z_T]);
                 rh[S0] = he - (h1 - h2);
@@ -497,32 +514,25 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                 KEEP(rh[SM1]);
                 vbuf[b][H_HEAT][pt] = rh[SM2];
                 qz[S0][Z_W] = w;
-                qz[S0][Z_P] = p;
                 qz[S0][Z_T] = T;
             }
-
-            // finish plane zp - 3: viscous vector from C, RK update, output
-            if (do_fin) {
+            // RK update and output of plane zp - 3
+            if (do_fin && active) {
                 const int64_t pidx = (int64_t)zf * c.nxy + col;
-                double R[3];
+                if constexpr (MODE == 0) {
 #pragma unroll
-                for (int f = 0; f < 3; ++f) R[f] = ra[SM3][f] + inv_re * vbuf[b ^ 1][H_VX + f][pt];
-                if (active) {
-                    if constexpr (MODE == 0) {
+                    for (int f = 0; f < 4; ++f) s.rout[f * N + pidx] = R[f];
+                } else {
+                    if constexpr (DIAG) {
 #pragma unroll
-                        for (int f = 0; f < 3; ++f) s.rout[(1 + f) * N + pidx] = R[f];
-                    } else {
-                        if constexpr (DIAG) {
+                        for (int f = 0; f < 4; ++f) dr[f] += acc[f];
+                    }
+                    double *qo = (double *)s.qout;
 #pragma unroll
-                            for (int f = 0; f < 3; ++f) dr[f] += acc[f];
-                        }
-                        double *qo = (double *)s.qout;
-#pragma unroll
-                        for (int f = 0; f < 3; ++f) {
-                            __builtin_nontemporal_store(acc[f] + s.a_dt * R[f], qo + (1 + f) * N + pidx);
-                            if constexpr (MODE < 3)
-                                __builtin_nontemporal_store(acc[f] + s.b_dt * R[f], s.acc_out + (1 + f) * N + pidx);
-                        }
+                    for (int f = 0; f < 4; ++f) {
+                        __builtin_nontemporal_store(acc[f] + s.a_dt * R[f], qo + f * N + pidx);
+                        if constexpr (MODE < 3)
+                            __builtin_nontemporal_store(acc[f] + s.b_dt * R[f], s.acc_out + f * N + pidx);
                     }
                 }
             }
@@ -646,7 +656,7 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                 vbuf[b][H_VX][pt] = Vx;
                 vbuf[b][H_VY][pt] = Vy;
                 vbuf[b][H_VZ][pt] = Vz;
-                vbuf[b][H_EN][pt] = inv_re * (u * Vx + v * Vy + w * Vz + rp[SM2]) - c.H_ref * rd[SM2];
+                vbuf[b][H_EN][pt] = inv_re * (u * Vx + v * Vy + w * Vz + rp[SM2]);
                 vbuf[b][H_DIV][pt] = rd[SM2];
             }
             take_grad(TIC<SM4>{}, b ^ 1);   // plane zp + 1's slot
@@ -752,7 +762,7 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                 vbuf[b][H_VX][pt] = Vx;
                 vbuf[b][H_VY][pt] = Vy;
                 vbuf[b][H_VZ][pt] = Vz;
-                vbuf[b][H_EN][pt] = inv_re * (u * Vx + v * Vy + w * Vz + (rp[SM2] + phi)) - c.H_ref * div;
+                vbuf[b][H_EN][pt] = inv_re * (u * Vx + v * Vy + w * Vz + (rp[SM2] + phi));
                 vbuf[b][H_DIV][pt] = div;
                 if constexpr (DIAG) {
                     vbuf[b][H_OX][pt] = cc - Gyz;
@@ -786,14 +796,12 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
         __syncthreads();
         double dsum[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         if (grp == 0) {
-            dsum[0] = dr[0];
-            dsum[4] = dr[1];
+            dsum[4] = dr[0];
+            dsum[5] = dr[1];
             dsum[6] = dr[2];
         } else if (grp == 1) {
-            dsum[1] = dr[0];
-            dsum[2] = dr[1];
-            dsum[3] = dr[2];
-            dsum[5] = dr[3];
+#pragma unroll
+            for (int f = 0; f < 4; ++f) dsum[f] = dr[f];
         }
 #pragma unroll
         for (int k = 0; k < 7; ++k) {
