@@ -248,7 +248,7 @@ int32_t ns_get_fused_order(void);
  * (residual of the governing-equations section, RK3 of the time-advancement
  * section) under its own launch shape; a batch step queues one RK3 step of
  * every member with steps left (largest grids first), members spread over
- * up to 8 internal HIP streams (balanced by grid points) that fork from and
+ * up to 8 internal HIP streams (balanced per call) that fork from and
  * join back into the caller's stream, so small grids overlap on the device.
  * With the caller's stream that is up to 5 streams: on a device with 4
  * hardware queues per process, 3 internal streams measured fastest.  Per-point
@@ -304,7 +304,8 @@ ns_status ns_batch_remove(ns_batch *b, int32_t slot);
 
 /* Queue nsteps RK3 steps of every member with steps left (a member stops at
  * its own budget), ordered after earlier work on `stream`; later work on
- * `stream` sees the results.  Asynchronous. */
+ * `stream` sees the results.  Successive calls may be given different streams:
+ * each member's steps follow each other all the same.  Asynchronous. */
 ns_status ns_batch_step(ns_batch *b, int32_t nsteps, void *stream);
 
 /* Run later ns_batch_step calls through HIP graphs (enable = 1) or eagerly

@@ -4,10 +4,12 @@
 // (grid, physics, launch shape, workspace carve-up) and a batch step
 // enqueues one RK3 step of each member that still has steps left.  Members
 // are spread over a few internal streams (balanced anew by each call over the
-// members that step), so the small grids' launches overlap on the device; the internal streams fork
-// from and join back into the caller's stream, so the batch is ordered like
-// any other stream work.  The launches are exactly rk3_step's, so a
-// member's result does not depend on which other members share the batch.
+// members that step), so the small grids' launches overlap on the device; the
+// internal streams fork from and join back into the caller's stream, so the
+// batch is ordered like any other stream work, and a member's steps follow each
+// other whatever streams successive calls are given.  The launches are exactly
+// rk3_step's, so a member's result does not depend on which other members share
+// the batch.
 //
 // Optionally (ns_batch_set_graphs) kGraphSteps batch steps -- every
 // stepping member's stage launches on their streams, forked from and joined
@@ -31,6 +33,7 @@ namespace ns {
 constexpr int kMaxStreams = 8;
 constexpr int32_t kGraphSteps = 8;   // steps per captured graph
 constexpr int kMaxInstances = 4096;
+constexpr int kNoQueue = -1, kAnyQueue = -2;
 // A step's fixed time (three launches and their latency) in points of a large
 // grid's step: beside two other streams' kernels a 32^3 FP32 step takes 13 us, a
 // 128^3 step 170 us.
@@ -42,6 +45,9 @@ struct Member {
     double dt = 0.0;
     int steps_left = -1, steps_done = 0;
     int stream = 0;                     // of the present ns_batch_step call
+    // What holds the slot's latest steps: an internal stream, nstreams for the
+    // origin stream, kNoQueue, or kAnyQueue after a call that failed.
+    int queue = kNoQueue;
     int64_t points = 0;
     const char *state_lo = nullptr, *state_hi = nullptr;
     const char *work_lo = nullptr, *work_hi = nullptr;
@@ -55,6 +61,7 @@ struct Batch {
     hipStream_t streams[kMaxStreams] = {};
     hipEvent_t fork = nullptr;
     hipEvent_t join[kMaxStreams] = {};
+    hipEvent_t order = nullptr;         // between the internal streams
     std::vector<Member> m;
     // graph replay
     bool graphs = false;
@@ -86,6 +93,7 @@ static void destroy(Batch *b)
         if (b->join[i]) (void)hipEventDestroy(b->join[i]);
     }
     if (b->fork) (void)hipEventDestroy(b->fork);
+    if (b->order) (void)hipEventDestroy(b->order);
     if (b->d_diag) (void)hipFree(b->d_diag);
 }
 
@@ -98,8 +106,8 @@ static bool overlaps(const char *a0, const char *a1, const char *b0, const char 
 // which cannot fill the device alone, run beside large ones on the other
 // streams; each is given the stream with the least work so far.  Streams are
 // chosen per call, whose steps are forked from and joined into the caller's
-// stream, so a member may change stream between calls.  Chosen once when a
-// member was added, by points alone, one stream got the small grids and two
+// stream, so a member may change stream between calls (order_queues).  Chosen
+// once when a member was added, by points alone, one stream got the small grids and two
 // thirds more time than the others: 20 FP32 members of 32^3 to 128^3, 8 steps,
 // 11.0 -> 9.9 ms.
 static std::vector<int> stepping_order(Batch *b)
@@ -115,6 +123,33 @@ static std::vector<int> stepping_order(Batch *b)
         load[b->m[i].stream] += b->m[i].points + kStepPoints;
     }
     return order;
+}
+
+// A call's steps are ordered after the steps of the calls before it only
+// through the caller's streams, which may differ, or through the queue that both
+// are in.  Where a member is about to change queue, the batch's streams first
+// wait for one another (the origin stream only where it is one of the queues: it
+// need not be under a capture of the caller's that the others are in).  A slot's
+// diagnostics record follows its members the same way.
+static hipError_t order_queues(Batch *b, const std::vector<int> &order, bool graph)
+{
+    bool moved = false, origin = graph;
+    for (int i : order) {
+        const Member &m = b->m[i];
+        moved = moved || (m.queue != kNoQueue && m.queue != (graph ? b->nstreams : m.stream));
+        origin = origin || m.queue == b->nstreams || (m.queue == kAnyQueue && b->origin);
+    }
+    if (!moved) return hipSuccess;
+    std::vector<hipStream_t> q(b->streams, b->streams + b->nstreams);
+    if (origin) q.push_back(b->origin);
+    hipError_t e = hipSuccess;
+    for (size_t k = 1; e == hipSuccess && k < q.size(); ++k) {
+        e = hipEventRecord(b->order, q[k]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(q[0], b->order, 0);
+    }
+    if (e == hipSuccess) e = hipEventRecord(b->order, q[0]);
+    for (size_t k = 1; e == hipSuccess && k < q.size(); ++k) e = hipStreamWaitEvent(q[k], b->order, 0);
+    return e;
 }
 
 // Queue nsteps steps of the members in `order`, forked once from `s` and
@@ -179,7 +214,8 @@ ns_status ns_batch_create(int32_t max_instances, ns_precision prec, int32_t nstr
     b->prec = prec;
     b->diag = with_diagnostics != 0;
     b->m.resize(max_instances);
-    bool ok = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess;
+    bool ok = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess &&
+              hipEventCreateWithFlags(&b->order, hipEventDisableTiming) == hipSuccess;
     for (int i = 0; ok && i < nstreams; ++i) {
         // default priority; does not synchronise with the null stream
         ok = hipStreamCreateWithFlags(&b->streams[i], hipStreamNonBlocking) == hipSuccess &&
@@ -254,7 +290,9 @@ ns_status ns_batch_add(ns_batch *b, const ns_instance *inst, int32_t *slot)
 ns_status ns_batch_remove(ns_batch *b, int32_t slot)
 {
     if (!b || slot < 0 || slot >= b->max_inst || !b->m[slot].used) return NS_ERR_ARG;
+    const int queue = b->m[slot].queue;
     b->m[slot] = Member();
+    b->m[slot].queue = queue;
     drop_graph(b);
     return NS_OK;
 }
@@ -263,6 +301,9 @@ ns_status ns_batch_step(ns_batch *b, int32_t nsteps, void *stream)
 {
     if (!b || nsteps < 0) return NS_ERR_ARG;
     hipStream_t caller = (hipStream_t)stream;
+    // the first steps of the call are ordered after former calls'; the members
+    // that go on are ordered by the caller's stream from then on
+    bool first = true;
     while (nsteps > 0) {
         const std::vector<int> order = stepping_order(b);
         if (order.empty()) break;
@@ -270,7 +311,11 @@ ns_status ns_batch_step(ns_batch *b, int32_t nsteps, void *stream)
         int32_t k = nsteps;
         for (int i : order) k = std::min(k, (int32_t)b->m[i].steps_left);
         int32_t eager = k;
-        if (b->graphs && k >= kGraphSteps) {
+        const bool graph = b->graphs && k >= kGraphSteps;
+        if (first) NS_HIP_OK(order_queues(b, order, graph));
+        first = false;
+        for (int i : order) b->m[i].queue = kAnyQueue;
+        if (graph) {
             // whole graphs of kGraphSteps steps on the origin stream, ordered
             // between the caller's earlier and later work
             if (!b->gexec) NS_HIP_OK(capture_steps(b, order));
@@ -286,6 +331,7 @@ ns_status ns_batch_step(ns_batch *b, int32_t nsteps, void *stream)
         bool finished = false;
         for (int i : order) {
             Member &m = b->m[i];
+            m.queue = eager > 0 ? m.stream : b->nstreams;
             m.steps_left -= k;
             m.steps_done += k;
             finished = finished || m.steps_left == 0;

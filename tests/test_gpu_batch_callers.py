@@ -1,0 +1,44 @@
+"""Successive batch steps on different caller streams that nothing orders:
+members that end, join or leave between the calls move the others to another
+internal stream, and every member still ends with the bits of its own rk3_step
+(the scheduler's ordering itself is checked on the host, in
+test_batch_order.py)."""
+import pytest
+import torch
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ns():
+    import paper_1709_09713_amd as ns
+    assert torch.cuda.is_available()
+    return ns
+
+
+@pytest.mark.parametrize("nstreams", [2, 3])
+@pytest.mark.parametrize("graphs", [False])
+def test_members_keep_their_bits_on_any_caller_stream(ns, nstreams, graphs):
+    print(f"callers streams={nstreams} graphs={graphs}", flush=True)
+    # (extent, steps, the call before which it is added)
+    plan = [(64, 1, 0), (48, 31, 0), (40, 10, 0), (24, 31, 0), (56, 21, 1), (32, 20, 1)]
+    calls = (1, 9, 3, 8, 10)
+    b = ns.Batch(len(plan), "fp64", nstreams=nstreams, graphs=graphs)
+    states = [torch.as_tensor(synth.random_state((n,) * 3, seed=n), device="cuda") for n, _, _ in plan]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for call, k in enumerate(calls):
+        for (n, steps, when), Q in zip(plan, states):
+            if when == call:
+                b.add(n, reynolds=700.0, mach=0.25, dt=2e-4, steps=steps, state=Q, init_tgv=False)
+        b.step(k, streams[call % 2])
+    torch.cuda.synchronize()
+    for (n, steps, when), Q in zip(plan, states):
+        p = ns.make_params((n,) * 3, reynolds=700.0, mach=0.25)
+        S = torch.as_tensor(synth.random_state((n,) * 3, seed=n), device="cuda")
+        work = torch.empty(ns.ns_workspace_bytes(p, ns.NS_ALGO_FUSED, ns.NS_FP64), dtype=torch.uint8, device="cuda")
+        ns.rk3_step(p, ns.NS_ALGO_FUSED, ns.NS_FP64, 2e-4, min(steps, sum(calls[when:])), S, work)
+        torch.cuda.synchronize()
+        assert torch.equal(Q, S), n
