@@ -34,6 +34,7 @@ constexpr int kMaxStreams = 8;
 constexpr int32_t kGraphSteps = 8;   // steps per captured graph
 constexpr int kMaxInstances = 4096;
 constexpr int kNoQueue = -1, kAnyQueue = -2;
+constexpr size_t kMaxRetired = 16;   // graph executables that wait to be destroyed
 // A step's fixed time (three launches and their latency) in points of a large
 // grid's step: beside two other streams' kernels a 32^3 FP32 step takes 13 us, a
 // 128^3 step 170 us.
@@ -67,21 +68,41 @@ struct Batch {
     bool graphs = false;
     hipStream_t origin = nullptr;       // capture and replay stream
     hipEvent_t gin = nullptr, gout = nullptr;
-    hipGraphExec_t gexec = nullptr;     // one step of the current stepping set
+    hipGraphExec_t gexec = nullptr;     // kGraphSteps steps of the current stepping set
+    // Executables that are not replayed any more but may still run; gout is
+    // recorded behind the last of their replays.
+    std::vector<hipGraphExec_t> retired;
 };
 
+// The stepping set changes: the executable is not replayed again.  It is
+// destroyed once its replays have ended (free_retired).
 static void drop_graph(Batch *b)
 {
     if (b->gexec) {
-        (void)hipGraphExecDestroy(b->gexec);
+        b->retired.push_back(b->gexec);
         b->gexec = nullptr;
     }
+}
+
+// Destroys the retired executables if the origin stream has run their replays;
+// with `wait`, or where kMaxRetired of them have gathered, after waiting for it.
+static void free_retired(Batch *b, bool wait)
+{
+    if (b->retired.empty()) return;
+    if (wait || b->retired.size() >= kMaxRetired ? hipStreamSynchronize(b->origin) != hipSuccess
+                                                 : hipEventQuery(b->gout) != hipSuccess) {
+        (void)hipGetLastError();   // not ready: no error of the caller's
+        return;
+    }
+    for (hipGraphExec_t x : b->retired) (void)hipGraphExecDestroy(x);
+    b->retired.clear();
 }
 
 static void destroy(Batch *b)
 {
     if (b->origin) (void)hipStreamSynchronize(b->origin);
     drop_graph(b);
+    free_retired(b, true);
     if (b->origin) (void)hipStreamDestroy(b->origin);
     if (b->gin) (void)hipEventDestroy(b->gin);
     if (b->gout) (void)hipEventDestroy(b->gout);
@@ -318,6 +339,7 @@ ns_status ns_batch_step(ns_batch *b, int32_t nsteps, void *stream)
         if (graph) {
             // whole graphs of kGraphSteps steps on the origin stream, ordered
             // between the caller's earlier and later work
+            free_retired(b, false);
             if (!b->gexec) NS_HIP_OK(capture_steps(b, order));
             NS_HIP_OK(hipEventRecord(b->gin, caller));
             NS_HIP_OK(hipStreamWaitEvent(b->origin, b->gin, 0));

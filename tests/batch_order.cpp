@@ -3,7 +3,8 @@
 // events and captures are tracked as vector clocks, and every step of a member
 // has to be ordered after the member's step before it, whatever streams the
 // caller passes, which members come and go between calls, and whether steps run
-// eagerly, from graphs or inside a capture of the caller's.
+// eagerly, from graphs or inside a capture of the caller's; and no graph may be
+// destroyed before its last replay is known to have run.
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -41,11 +42,14 @@ struct Capture {
 };
 struct Graph {
     std::set<const void *> states;
+    Step replay{0, 0};                   // the last one
 };
 
 int g_next = 1;
 long g_seq = 0;
 std::map<const void *, Step> g_last;
+Clock g_done;                         // what the host knows to have run
+std::mt19937 g_query(1);
 int g_errors = 0;
 const char *g_what = "";
 
@@ -90,7 +94,18 @@ hipError_t hipStreamDestroy(hipStream_t s)
     delete (Stream *)s;
     return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s)
+{
+    merge(g_done, str(s)->clk);
+    return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t e)
+{
+    if (g_query() % 2) return hipErrorNotReady;
+    merge(g_done, ((Event *)e)->clk);
+    return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned int)
 {
     *e = (hipEvent_t) new Event;
@@ -166,12 +181,15 @@ hipError_t hipGraphDestroy(hipGraph_t g)
 }
 hipError_t hipGraphExecDestroy(hipGraphExec_t g)
 {
+    const Step r = ((Graph *)g)->replay;
+    if (g_done[r.stream] < r.seq) fail("a graph is destroyed before its replay has run");
     delete (Graph *)g;
     return hipSuccess;
 }
 hipError_t hipGraphLaunch(hipGraphExec_t g, hipStream_t s)
 {
     for (const void *state : ((Graph *)g)->states) operate(state, str(s));
+    ((Graph *)g)->replay = Step{str(s)->id, g_seq};
     return hipSuccess;
 }
 hipError_t hipMalloc(void **p, size_t n)

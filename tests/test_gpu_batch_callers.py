@@ -19,7 +19,7 @@ def ns():
 
 
 @pytest.mark.parametrize("nstreams", [2, 3])
-@pytest.mark.parametrize("graphs", [False])
+@pytest.mark.parametrize("graphs", [False, True])
 def test_members_keep_their_bits_on_any_caller_stream(ns, nstreams, graphs):
     print(f"callers streams={nstreams} graphs={graphs}", flush=True)
     # (extent, steps, the call before which it is added)
