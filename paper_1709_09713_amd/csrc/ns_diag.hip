@@ -3,7 +3,7 @@
 // tgv_init writes the initial condition of the results section.
 // The diagnostics are the kinetic-energy / enstrophy quantities of the
 // validation data set that the results section compares against, plus the
-// conserved totals: per-block partial sums (wave64 shuffle reduction, then
+// conserved totals: per-block partial sums (wave64 reduction by DPP moves, then
 // LDS across waves) and a one-block final pass in a fixed order, so the
 // result is bitwise reproducible for a given grid.
 #include "ns_common.hpp"
@@ -157,9 +157,9 @@ diag_point_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ p
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int64_t at = idx + (int64_t)(wrap1(co[d] + off[q], nn[d]) - co[d]) * st[d];
-                const double inv = recip_f64(Q[at]);
+                const double rho = Q[at], inv = recip_f64(rho);
 #pragma unroll
-                for (int e = 0; e < 2; ++e) t[e][q] = Q[(1 + (d + 1 + e) % 3) * N + at] * inv;
+                for (int e = 0; e < 2; ++e) t[e][q] = quotient_f64(Q[(1 + (d + 1 + e) % 3) * N + at], rho, inv);
             }
 #pragma unroll
             for (int e = 0; e < 2; ++e) G[d][e] = c.c1[d] * d1u(t[e][0], t[e][1], t[e][2], t[e][3]);
@@ -243,17 +243,18 @@ diag_march_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ p
         const int b = (zp - z0) & 1;
         const double rho = p0[0], m0 = p0[1], m1 = p0[2], m2 = p0[3], E = p0[4];
         const double inv = recip_f64(rho);
-        const double u = m0 * inv, v = m1 * inv, w = m2 * inv;
+        const double u = quotient_f64(m0, rho, inv), v = quotient_f64(m1, rho, inv), w = quotient_f64(m2, rho, inv);
         lu[b][ty + 2][tx] = u;
         lv[b][ty][tx + 2] = v;
         lw[b][ty + 2][tx + 2] = w;
         if (yhalo || xhalo) {
             const double hinv = recip_f64(ph[0]);
+            const double hv = quotient_f64(ph[1], ph[0], hinv);
             if (yhalo)
-                lu[b][hy][hx - 2] = ph[1] * hinv;
+                lu[b][hy][hx - 2] = hv;
             else
-                lv[b][hy - 2][hx] = ph[1] * hinv;
-            lw[b][hy][hx] = ph[2] * hinv;
+                lv[b][hy - 2][hx] = hv;
+            lw[b][hy][hx] = quotient_f64(ph[2], ph[0], hinv);
         }
         lds_barrier();
         if (zp + 1 < z1 + 2) load(zp + 1);
