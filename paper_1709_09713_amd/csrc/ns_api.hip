@@ -209,7 +209,7 @@ static int choose_brick(const Consts &c, ns_precision prec, int tile_in, int zch
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-    size_t partial, rec, acc, b1, b2, R, stored, G, total;
+    size_t partial, rec, acc, b1, b2, stored, G, total;
 };
 
 // Scratch layout.  The diagnostic partials and one ns_diag record come
@@ -231,14 +231,13 @@ static Layout layout(const Consts &c, ns_algo algo, ns_precision prec)
     off = align256(off + n5 * stage_elt);
     L.b2 = off;
     off = align256(off + n5 * stage_elt);
-    L.R = L.stored = L.G = 0;
+    L.stored = L.G = 0;
     if (algo == NS_ALGO_SOME) {
         L.G = off;
         off = align256(off + rs_workspace_doubles(c) * sizeof(double));
     }
     if (algo == NS_ALGO_STORED) {
-        L.R = off;
-        off = align256(off + n5 * sizeof(double));
+        off = align256(off + n5 * sizeof(double));   // a residual array, unused now: the size stays
         L.stored = off;
         off = align256(off + stored_workspace_doubles(c) * sizeof(double));
     }

@@ -12,8 +12,9 @@
 
 namespace ns {
 
-// Derivative arrays (units of N doubles).  The work space also has room for
-// the primitives and products, which are formed on chip.
+// Derivative arrays (units of N doubles).  The work space has room for 20 more,
+// the primitives and products of the former sweeps, which are formed on chip
+// now: ns_workspace_bytes keeps the size that callers were told.
 enum { W_TOTAL = 80 };
 enum {
     D_RHO = 0,    // d rho / dx_j                      (3)
