@@ -5,14 +5,18 @@ For one grid size and storage precision, times every candidate launch shape
 Taylor-Green solve running the real RK3 launches (one member of a
 one-stream batch), and keeps the fastest.  Results are cached per
 (grid, precision) in memory and optionally in a JSON file, so a serving
-process tunes each grid size once.  Every candidate computes the same
+process tunes each grid size once; a file's entry holds for the build of the
+library that it was tuned with.  Every candidate computes the same
 result (the tiling only changes which block computes which point), so the
 choice affects speed only.
 """
 from __future__ import annotations
 
+import functools
+import hashlib
 import json
 import os
+import threading
 import time
 
 import torch
@@ -28,12 +32,23 @@ def _key(n, precision):
     return n, f"{n[0]}x{n[1]}x{n[2]}:{precision}"
 
 
+@functools.lru_cache(maxsize=None)
+def _library_id(path: str) -> str:
+    """Digest of the built library: another build may have other kernels behind
+    the same tile numbers."""
+    h = hashlib.sha256()
+    with open(path, "rb") as f:
+        while block := f.read(1 << 20):
+            h.update(block)
+    return h.hexdigest()[:16]
+
+
 class Autotuner:
     def __init__(self, cache_path: str | None = None, tiles=None, zchunks=DEFAULT_ZCHUNKS,
                  steps: int = 3, reps: int = 3):
         self.cache_path = cache_path
-        # -1 with chunk 0: the library's own choice, which on small FP64 grids
-        # is a kernel that no tile names
+        # -1 with chunk 0: the library's own choice, which on small grids is a
+        # kernel that no tile names
         self.tiles = (-1, *nat.TILES) if tiles is None else tuple(tiles)
         self.zchunks = tuple(zchunks)
         self.steps = steps
@@ -46,10 +61,11 @@ class Autotuner:
     def lookup(self, n, precision):
         """(tile, zchunk) for this grid, tuning it on first use."""
         n, key = _key(n, precision)
-        if key not in self.table:
-            self.table[key] = self.tune(n, precision)
+        library = _library_id(nat.LIB_PATH)
+        e = self.table.get(key)
+        if e is None or e.get("library") != library:
+            e = self.table[key] = {**self.tune(n, precision), "library": library}
             self.save()
-        e = self.table[key]
         return e["tile"], e["zchunk"]
 
     def save(self):
@@ -60,8 +76,27 @@ class Autotuner:
             os.replace(tmp, self.cache_path)
 
     def tune(self, n, precision):
+        """Time the candidates in a thread of their own: launch settings are per
+        thread, and a caller's would stand in for the library's choice."""
         n, _ = _key(n, precision)
         stream = torch.cuda.current_stream()
+        out = {}
+
+        def run():
+            try:
+                with torch.cuda.device(stream.device), torch.cuda.stream(stream):
+                    out["entry"] = self._tune(n, precision, stream)
+            except BaseException as e:   # raised again in the caller's thread
+                out["error"] = e
+
+        t = threading.Thread(target=run)
+        t.start()
+        t.join()
+        if "error" in out:
+            raise out["error"]
+        return out["entry"]
+
+    def _tune(self, n, precision, stream):
         state = torch.empty((5, n[2], n[1], n[0]), dtype=torch.float64, device="cuda")
         p = nat.make_params(n)
         work = torch.empty(nat.ns_workspace_bytes(p, nat.NS_ALGO_FUSED, nat.PRECS[precision]),
