@@ -201,13 +201,14 @@ ns_status ns_stage_stream(const ns_params *p, int32_t stage, double *state, void
  * (x, y) column tile of one block: 0 = 32x8, 1 = 16x16, 2 = 64x4,
  * 3 = 32x16, 4 = 16x8, 5 = 32x4, 6 = 16x4, 7 = 8x8 (threads = product, one
  * z column each); 8 = 16x8, 9 = 32x8, 10 = 16x4 with each column split over
- * three threads (mass and energy; momentum; viscous terms); zchunk is the number of
+ * three threads (by equation; viscous terms apart); zchunk is the number of
  * z planes one block marches through (>= 1; 0 = automatic: the length that
  * minimises (rounds of device-resident blocks) x (planes each block
  * marches, chunk + 4 halo planes; + 5 for tiles 8-10)).  tile = -1
  * restores the automatic choice: for NS_FP64 tile 9, or tile 8 where the grid
  * leaves compute units idle; for NS_FP32_STORE tile 0, or tile 9 on grids of
- * about 56^3 to 100^3; and with zchunk 0, for grids of few 8x4x4 bricks per
+ * 49^3 to 96^3, 113^3 to 116^3 and 121^3 to 124^3 (and others of about a block
+ * a compute unit); and with zchunk 0, for grids of few 8x4x4 bricks per
  * compute unit (up to 40^3 in NS_FP64, 48^3 in NS_FP32_STORE), a kernel that
  * stages whole bricks instead of marching.  The automatic choices of a
  * precision all give the same bits (per-step diagnostics differ in the order

@@ -123,10 +123,12 @@ static int default_fp64_tile(const Consts &c, int *zchunk)
 // unit, takes 2.0 us, one of the three-group kernel, one block a compute unit,
 // 1.2 us, so that kernel is taken where its longer chunks come to at most 1.8
 // times the planes (not 2.0/1.2: on larger grids, which memory bounds, the
-// one-thread kernel's second block hides more).  Measured, one thread | three
-// groups, us per RK3 step: 56^3 40.9 | 37.7, 64^3 43.3 | 40.4, 80^3 66.3 | 62.8,
-// 101x77x53 69.4 | 64.9, 96^3 85.7 | 82.6, 112^3 134.8 | 139.8, 128^3 175 | 177,
-// 160^3 317 | 340, 256^3 1144 | 1234.  Both give the same bits; the
+// one-thread kernel's second block hides more).  Of the cubes that bricks do not
+// take, 49^3 to 96^3, 113^3 to 116^3 and 121^3 to 124^3.  Measured, one thread |
+// three groups, us per RK3 step: 56^3 40.1 | 37.4, 64^3 42.7 | 40.2, 80^3 63.9 |
+// 62.2, 88^3 76.3 | 79.0, 101x77x53 66.5 | 63.0, 96^3 84.3 | 82.1, 104^3 126.0 |
+// 125.1, 112^3 131.0 | 136.1, 114^3 160.6 | 151.8, 122^3 187 | 179, 128^3 168.4 |
+// 171.3, 144^3 279 | 297, 160^3 298 | 340, 256^3 1113 | 1234.  Both give the same bits; the
 // direction-grouped order is compiled for the one-thread kernel only.
 static int default_fp32_tile(const Consts &c, int *zchunk)
 {
@@ -150,8 +152,8 @@ static void choose_config(const Consts &c, ns_precision prec, int tile_in, int z
     int z = tile_in >= 0 ? zchunk_in : g_zchunk;
     if (zchunk_in > 0) z = zchunk_in;
     // defaults measured on MI355X: FP64 runs fastest with the three-group
-    // kernel on grids from 40^3 to 512^3, FP32 storage with the one-thread
-    // 32x8 kernel
+    // kernel on grids from 40^3 to 512^3; FP32 storage takes it on grids of about
+    // a block a compute unit (default_fp32_tile), else the one-thread 32x8 kernel
     if (t < 0 || t >= TILE_COUNT) {
         if (z <= 0)
             t = prec == NS_FP64 ? default_fp64_tile(c, &z) : default_fp32_tile(c, &z);
