@@ -6,13 +6,13 @@
 // block owns a brick of 8 x 4 x BRZ points and stages it whole, with its halo
 // of two, in one round of loads; then three groups of waves evaluate the
 // equations of one point per thread (A mass, energy and the pressure gradient,
-// B momentum and heat conduction, C viscous terms) with the expressions of
-// ns_trio.hip in the same order, so that the result is the same bit for bit.
+// B momentum, C viscous terms) with the expressions of ns_trio.hip in the same
+// order, so that the result is the same bit for bit.
 // Three barriers in all: after the staging, after the in-plane gradients that
 // are differentiated along z, and before A and B take over C's values.
 //
 // Bound by latency: of 4.7 us a stage at 16^3 (14.2 us an RK3 step, the
-// march's best shape 21.8), 1.7 us are an empty launch of a chain; the round
+// march's best shape 21.1), 1.7 us are an empty launch of a chain; the round
 // of loads and its share of the conversions (1.8 us), the gradients (0.3 us)
 // and one thread's arithmetic (about 140 double operations, 1.5 us) are the
 // rest.  Rows of two fields side by side keep a wave's reads on distinct banks
@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
     // staged fields: rho, rho u_i, E, u, v, w, kinetic energy, e = T / (gamma (gamma - 1) M^2)
     enum { L_R, L_M0, L_M1, L_M2, L_E, L_U, L_V, L_W, L_K, L_T, NF };
     enum { G_A, G_B, G_C, NG };                      // D_x u + D_y v, D_x w, D_y w
-    enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_HEAT, H_PX, H_PY, H_PZ, NH };
+    enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_PX, H_PY, H_PZ, NH };
     // Two fields share a row of the array, side by side: with rows of 2 HX cells
     // the rows that a wave reads at once start in different banks.
     constexpr int RS = 2 * HX, PS = HY * RS;
@@ -151,12 +151,12 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
     // residuals of the own equations; what div u multiplies in them (group A rho
     // and E + p, B rho u_i); of B the terms with the planes above
     double R[3] = {0.0, 0.0, 0.0}, car[3] = {0.0, 0.0, 0.0}, up[3][2] = {};
-    // diagnostics of the point: group A mass and energy, B the momenta and
-    // kinetic energy, C enstrophy
+    // diagnostics of the point: group A mass, energy and kinetic energy, B the
+    // momenta, C enstrophy
     double dsum[4] = {0.0, 0.0, 0.0, 0.0};
     if (grp == 0) {
         // ------------------------------------------------------------ group A
-        const double r = LV(L_R, 0, 0, 0), E = LV(L_E, 0, 0, 0), w = LV(L_W, 0, 0, 0);
+        const double r = LV(L_R, 0, 0, 0), E = LV(L_E, 0, 0, 0), w = LV(L_W, 0, 0, 0), T = LV(L_T, 0, 0, 0);
         const double ke = LV(L_K, 0, 0, 0), u = LV(L_U, 0, 0, 0), v = LV(L_V, 0, 0, 0);
         double rm = 0.0, re = 0.0;
         {
@@ -164,6 +164,7 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
             TAPS_X(rt, L_R);
             TAPS_X(et, L_E);
             TAPS_X(kt, L_K);
+            TAPS_X(tt, L_T);
             HALF_SUMS(su, u, ut, k.x4, k.xh);
             double dE[4], dp[4];
             diffs(E, et, dE);
@@ -171,6 +172,7 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
             rm = conv(rm, r, rt, su);
             re = conv(re, dE, su);
             re = __builtin_fma(-k.gx, d1_prod(dp, ut), re);
+            re = __builtin_fma(k.kx, D2T(tt, T), re);
             vbuf[H_PX][pt] = k.gx * D1T(dp);
         }
         {
@@ -178,6 +180,7 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
             TAPS_Y(rt, L_R);
             TAPS_Y(et, L_E);
             TAPS_Y(kt, L_K);
+            TAPS_Y(tt, L_T);
             HALF_SUMS(sv, v, vt, k.y4, k.yh);
             double dE[4], dp[4];
             diffs(E, et, dE);
@@ -185,6 +188,7 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
             rm = conv(rm, r, rt, sv);
             re = conv(re, dE, sv);
             re = __builtin_fma(-k.gy, d1_prod(dp, vt), re);
+            re = __builtin_fma(k.ky, D2T(tt, T), re);
             vbuf[H_PY][pt] = k.gy * D1T(dp);
         }
         {
@@ -194,17 +198,19 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
             TAPS_Z(rt, L_R);
             TAPS_Z(et, L_E);
             TAPS_Z(kt, L_K);
+            TAPS_Z(tt, L_T);
             double mf[4], ef[4], pf[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const bool below = t < 2, near = t == 1 || t == 2;
                 const double st = (near ? k.z4 : k.zh) * (w + wt[t]);
                 // from the lower to the upper plane of the pair
-                const double dr = below ? r - rt[t] : rt[t] - r, dE = below ? E - et[t] : et[t] - E;
-                const double dK = below ? ke - kt[t] : kt[t] - ke;
-                mf[t] = dr * st;
+                const double dE = below ? E - et[t] : et[t] - E, dK = below ? ke - kt[t] : kt[t] - ke;
+                const double h = (near ? k.kz16 : k.kz) * (below ? T - tt[t] : tt[t] - T);
                 pf[t] = (near ? k.gz8 : k.gz) * (dE - dK);
-                ef[t] = __builtin_fma(pf[t], wt[t], dE * st);
+                const double e = dE * st;
+                mf[t] = (below ? r - rt[t] : rt[t] - r) * st;
+                ef[t] = below ? __builtin_fma(pf[t], wt[t], e) + h : __builtin_fma(pf[t], wt[t], e) - h;
             }
             rm = rm - (mf[1] - mf[0]);
             rm -= mf[2];
@@ -221,20 +227,18 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
         R[1] = re;
         car[0] = r;
         car[1] = __builtin_fma(c.gm1, E - ke, E);
+        if constexpr (DIAG) dsum[2] = ke;
     } else if (grp == 1) {
         // ------------------------------------------------------------ group B
         const double m[3] = {LV(L_M0, 0, 0, 0), LV(L_M1, 0, 0, 0), LV(L_M2, 0, 0, 0)};
         const double u = LV(L_U, 0, 0, 0), v = LV(L_V, 0, 0, 0), w = LV(L_W, 0, 0, 0);
-        const double T = LV(L_T, 0, 0, 0);
-        double he, rr[3];
+        double rr[3];
         {
             TAPS_X(ut, L_U);
             TAPS_X(m0t, L_M0);
             TAPS_X(m1t, L_M1);
             TAPS_X(m2t, L_M2);
-            TAPS_X(tt, L_T);
             HALF_SUMS(su, u, ut, k.x4, k.xh);
-            he = k.kx * D2T(tt, T);
             rr[0] = conv(0.0, m[0], m0t, su);
             rr[1] = conv(0.0, m[1], m1t, su);
             rr[2] = conv(0.0, m[2], m2t, su);
@@ -244,16 +248,13 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
             TAPS_Y(m0t, L_M0);
             TAPS_Y(m1t, L_M1);
             TAPS_Y(m2t, L_M2);
-            TAPS_Y(tt, L_T);
             HALF_SUMS(sv, v, vt, k.y4, k.yh);
-            he += k.ky * D2T(tt, T);
             rr[0] = conv(rr[0], m[0], m0t, sv);
             rr[1] = conv(rr[1], m[1], m1t, sv);
             rr[2] = conv(rr[2], m[2], m2t, sv);
         }
         {
             TAPS_Z(wt, L_W);
-            TAPS_Z(tt, L_T);
             double sz[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) sz[t] = (t == 1 || t == 2 ? k.z4 : k.zh) * (w + wt[t]);
@@ -268,17 +269,6 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
                 up[f][0] = fl[2];
                 up[f][1] = fl[3];
             }
-            double hf[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                // from the lower to the upper plane of the pair
-                const double dT = t < 2 ? T - tt[t] : tt[t] - T;
-                hf[t] = (t == 1 || t == 2 ? k.kz16 : k.kz) * dT;
-            }
-            double rh = he - (hf[1] - hf[0]);
-            rh += hf[2];
-            rh -= hf[3];
-            vbuf[H_HEAT][pt] = rh;
         }
     } else {
         // ------------------------------------------------------------ group C
@@ -340,7 +330,7 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
         const double div = vbuf[H_DIV][pt];
         if (grp == 0) {
             R[0] = __builtin_fma(-car[0], div, R[0]);
-            R[1] = __builtin_fma(-car[1], div, R[1] + (vbuf[H_EN][pt] + vbuf[H_HEAT][pt]));
+            R[1] = __builtin_fma(-car[1], div, R[1] + vbuf[H_EN][pt]);
         } else {
 #pragma unroll
             for (int f = 0; f < 3; ++f) {
@@ -365,11 +355,9 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
             }
         }
         if constexpr (DIAG) {
-#pragma unroll
-            for (int f = 0; f < 3; ++f) dsum[f] = acc[f];
-            if (grp == 1)
-                dsum[3] = 0.5 * (LV(L_M0, 0, 0, 0) * LV(L_U, 0, 0, 0) + LV(L_M1, 0, 0, 0) * LV(L_V, 0, 0, 0)
-                                 + LV(L_M2, 0, 0, 0) * LV(L_W, 0, 0, 0));
+            dsum[0] = acc[0];
+            dsum[1] = acc[1];
+            if (grp == 1) dsum[2] = acc[2];
         }
     }
 #undef AT
@@ -390,9 +378,9 @@ __global__ void __launch_bounds__(3 * BRX * BRY * BRZ) brick_stage_kernel(Consts
         }
         lds_barrier();
         if (tid < kDiag) {
-            // a record's slots by group: A 0 and 4, B 1, 2, 3 and 5, C 6 and 7 (zero)
-            const int g = (tid & 3) == 0 ? 0 : tid < 6 ? 1 : 2;
-            const int d = g == 0 ? tid >> 2 : g == 1 ? tid - 1 - (tid >> 2) : tid - 6;
+            // a record's slots by group: B 1 to 3, A 0, 4 and 5, C 6 and 7 (zero)
+            const int g = tid >= 1 && tid < 4 ? 1 : tid < 6 ? 0 : 2;
+            const int d = g == 1 ? tid - 1 : g == 0 ? (tid == 0 ? 0 : tid - 3) : tid - 6;
             const int64_t blin = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
             double t = 0.0;
 #pragma unroll

@@ -8,8 +8,8 @@
 // low-storage RK3 update of the generic-algorithm figure in the same pass),
 // but a block holds three threads per column of its tile:
 //  * group A (threads [0, NT)) loads and stages each plane and evaluates the
-//    energy equation and the pressure gradient;
-//  * group B evaluates the mass and momentum equations and heat conduction;
+//    energy equation with heat conduction, and the pressure gradient;
+//  * group B evaluates the mass and momentum equations;
 //  * group C evaluates div u, the viscous vector V_i = lap u_i + (1/3) d_i
 //    div u and the viscous work and dissipation.
 // The groups hand values over through vbuf, double buffered like the planes:
@@ -40,21 +40,23 @@
 // 3.0e-10 -> 1.6e-16 4.5e-16 3.4e-14; inviscid, p = 1 at M = 1e-3 1.8e-16 6.0e-15
 // 2.1e-16 -> 1.9e-16 2.1e-9 1.2e-10 -> 1.6e-16 1.6e-16 1.7e-16; mean flow 4.8e-15
 // 1.2e-14 5.7e-15 -> 4.6e-15 1.7e-14 1.1e-14 -> 3.3e-15 2.7e-15 3.3e-15.  Against
-// the deviations a step costs 0.7% (256^3) to 3.5% (101x77x53) more: one addition
-// per pressure tap, and div u times the point's own values.
+// the deviations a step costs 0 (256^3) to 2% (64^3, 101x77x53) more: one addition
+// per pressure tap, and div u times the point's own values.  (Heat conduction is
+// group A's, which needs it: in B and handed over, 512^3 took 13.24 ms instead of
+// 13.03, 101x77x53 79.9 us instead of 77.5.)
 //
-// What bounds it: at 512^3 a stage moves 19-26 GB (4.3 ms at the rate of a
-// plain kernel of the same access pattern for stage 2, 3.1 ms for stages 1
+// What bounds it: at 512^3 a stage moves 18-24 GB (4.2 ms at the rate of a
+// plain kernel of the same access pattern for stage 2, 3.2 ms for stages 1
 // and 3) and needs about 3.2 ms of LDS and vector issue when its planes come
-// from L2; a step takes 4.0-4.6 ms because one barrier per plane keeps the
+// from L2 (measured before the differences); a stage takes 4.2-4.6 ms because one barrier per plane keeps the
 // groups in step, so the three do not overlap fully.  Two groups (momentum |
 // the rest) at two waves per SIMD had 30 dependent LDS waits per plane in the
 // longer group; three groups of about equal length fit 168 registers, three
 // waves per SIMD, and hide them better.  Measured (ms per step without
-// diagnostics, two groups -> three): 512^3 13.99 -> 12.72, 256^3 1.739 ->
-// 1.595, 192^3 0.843 -> 0.754, 101x77x53 0.0884 -> 0.0774, 64^3 0.0552 ->
-// 0.0500, 32^3 0.0495 -> 0.0285 (there also because the march ends at its
-// last plane instead of at a multiple of five).
+// diagnostics, two groups -> three): 512^3 13.99 -> 12.97, 256^3 1.739 ->
+// 1.591, 192^3 0.843 -> 0.745, 101x77x53 0.0884 -> 0.0770, 64^3 0.0552 ->
+// 0.0489 (on small grids also because the march ends at its last plane instead
+// of at a multiple of five).
 #include <type_traits>
 
 #include "ns_common.hpp"
@@ -96,12 +98,12 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
     // staged fields: rho, rho u_i, E, u, v, w, kinetic energy, e = T / (gamma (gamma - 1) M^2)
     enum { L_R, L_M0, L_M1, L_M2, L_E, L_U, L_V, L_W, L_K, L_T, NF };
     // handed over: V, dissipative energy terms and div u of plane zp - 2 (C),
-    // heat conduction of plane zp - 2 (B), pressure gradient, in-plane of plane
-    // zp and along z of plane zp - 2 (A); with diagnostics omega_z of plane zp
-    // and omega_x, omega_y of plane zp - 2 (C)
-    enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_HEAT, H_PX, H_PY, H_PZ, H_OZ, H_OX, H_OY };
+    // pressure gradient, in-plane of plane zp and along z of plane zp - 2 (A);
+    // with diagnostics omega_z of plane zp and omega_x, omega_y of plane zp - 2
+    // (C)
+    enum { H_VX, H_VY, H_VZ, H_EN, H_DIV, H_PX, H_PY, H_PZ, H_OZ, H_OX, H_OY };
     __shared__ __attribute__((aligned(16))) double lds[2][NF][HP];
-    __shared__ double vbuf[2][DIAG ? 12 : 9][NT];
+    __shared__ double vbuf[2][DIAG ? 11 : 8][NT];
     __shared__ double red[NW][kDiag];
     __shared__ double sbuf[GRAD ? 2 : 1][GRAD ? HY : 1][BX];   // GRAD: D_x u + D_z w with two halo rows each side
 
@@ -193,9 +195,9 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
         // Group A alone loads: pairs of points with one 16-byte load each
         // (even nx).  Sharing the loads between A and B, one point per
         // thread, balances the arithmetic better but was 10% slower.
-        enum { Z_E, Z_K, Z_W, Z_R, NZ };
+        enum { Z_E, Z_K, Z_W, Z_T, Z_R, NZ };
         enum { R_EN, R_PZ, NR };
-        double qz[5][NZ];      // E, kinetic energy (with diagnostics rho) of planes zp .. zp - 3, w of zp .. zp - 2
+        double qz[5][NZ];      // E, kinetic energy (with diagnostics rho) of planes zp .. zp - 3, w and T of zp .. zp - 2
         double ra[5][NR];      // pending energy residual and pressure gradient along z
         double acc = 0.0, accn = 0.0;   // of this and the next step's point
 #pragma unroll
@@ -306,7 +308,7 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                 acc = accn;
                 accn = __builtin_nontemporal_load(accsrc + 4 * N + pn);
             }
-            const double E = LV(L_E, 0, 0), ke = LV(L_K, 0, 0), w = LV(L_W, 0, 0);
+            const double E = LV(L_E, 0, 0), ke = LV(L_K, 0, 0), w = LV(L_W, 0, 0), T = LV(L_T, 0, 0);
             double re = 0.0;
             if (do_plane) {
                 const double u = LV(L_U, 0, 0), v = LV(L_V, 0, 0);
@@ -314,24 +316,28 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                     TAPS_X(ut, L_U);
                     TAPS_X(et, L_E);
                     TAPS_X(kt, L_K);
+                    TAPS_X(tt, L_T);
                     HALF_SUMS(su, u, ut, k.x4, k.xh);
                     double dE[4], dp[4];
                     diffs(E, et, dE);
                     pressure_diffs(dE, ke, kt, dp);
                     re = conv(re, dE, su);
                     re = __builtin_fma(-k.gx, d1_prod(dp, ut), re);
+                    re = __builtin_fma(k.kx, D2T(tt, T), re);
                     vbuf[b][H_PX][pt] = k.gx * D1T(dp);
                 }
                 {
                     TAPS_Y(vt, L_V);
                     TAPS_Y(et, L_E);
                     TAPS_Y(kt, L_K);
+                    TAPS_Y(tt, L_T);
                     HALF_SUMS(sv, v, vt, k.y4, k.yh);
                     double dE[4], dp[4];
                     diffs(E, et, dE);
                     pressure_diffs(dE, ke, kt, dp);
                     re = conv(re, dE, sv);
                     re = __builtin_fma(-k.gy, d1_prod(dp, vt), re);
+                    re = __builtin_fma(k.ky, D2T(tt, T), re);
                     vbuf[b][H_PY][pt] = k.gy * D1T(dp);
                 }
                 if constexpr (DIAG) {
@@ -345,9 +351,12 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                 const double dE1 = E - qz[SM1][Z_E], dE2 = E - qz[SM2][Z_E];
                 const double p1 = k.gz8 * (dE1 - (ke - qz[SM1][Z_K])), p2 = k.gz * (dE2 - (ke - qz[SM2][Z_K]));
                 const double e1 = dE1 * s1, e2 = dE2 * s2;
-                ra[S0][R_EN] = re - (__builtin_fma(p1, w1, e1) - __builtin_fma(p2, w2, e2));
-                ra[SM1][R_EN] -= __builtin_fma(p1, w, e1);
-                ra[SM2][R_EN] += __builtin_fma(p2, w, e2);
+                const double h1 = k.kz16 * (T - qz[SM1][Z_T]), h2 = k.kz * (T - qz[SM2][Z_T]);
+                const double a1 = __builtin_fma(p1, w1, e1) + h1, a2 = __builtin_fma(p2, w2, e2) + h2;
+                const double b1 = __builtin_fma(p1, w, e1) - h1, b2 = __builtin_fma(p2, w, e2) - h2;
+                ra[S0][R_EN] = re - (a1 - a2);
+                ra[SM1][R_EN] -= b1;
+                ra[SM2][R_EN] += b2;
                 ra[S0][R_PZ] = p1 - p2;
                 ra[SM1][R_PZ] += p1;
                 ra[SM2][R_PZ] -= p2;
@@ -362,6 +371,7 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                 if constexpr (DIAG) qz[S0][Z_R] = LV(L_R, 0, 0);
                 qz[S0][Z_K] = ke;
                 qz[S0][Z_W] = w;
+                qz[S0][Z_T] = T;
             }
 
             // stage plane zp + 1 into the other buffer (last read in the
@@ -374,7 +384,7 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                 const double E3 = qz[SM3][Z_E];
                 const double H = __builtin_fma(c.gm1, E3 - qz[SM3][Z_K], E3);   // E + p
                 const double R = __builtin_fma(-H, vbuf[b ^ 1][H_DIV][pt],
-                                               ra[SM3][R_EN] + (vbuf[b ^ 1][H_EN][pt] + vbuf[b ^ 1][H_HEAT][pt]));
+                                               ra[SM3][R_EN] + vbuf[b ^ 1][H_EN][pt]);
                 if (active) {
                     if constexpr (MODE == 0) {
                         s.rout[4 * N + pidx] = R;
@@ -409,10 +419,9 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
     } else if (grp == 1) {
         // ------------------------------------------------------------ group B
         // the fields carried with the flow: density and momenta (the first four)
-        enum { Z_W = 4, Z_T, NZ };
-        double qz[5][NZ];      // rho and rho u_i of planes zp .. zp - 3, w and T of zp .. zp - 2
+        enum { Z_W = 4, NZ };
+        double qz[5][NZ];      // rho and rho u_i of planes zp .. zp - 3, w of zp .. zp - 2
         double ra[5][4];       // pending mass and momentum residuals
-        double rh[5] = {0.0, 0.0, 0.0, 0.0, 0.0};   // pending heat conduction
         double acc[4] = {0.0, 0.0, 0.0, 0.0}, accn[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
@@ -453,8 +462,7 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                 }
             }
             const double m[4] = {LV(L_R, 0, 0), LV(L_M0, 0, 0), LV(L_M1, 0, 0), LV(L_M2, 0, 0)};
-            const double w = LV(L_W, 0, 0), T = LV(L_T, 0, 0);
-            double he = 0.0;
+            const double w = LV(L_W, 0, 0);
             double rr[4] = {0.0, 0.0, 0.0, 0.0};
             if (do_plane) {
                 const double u = LV(L_U, 0, 0), v = LV(L_V, 0, 0);
@@ -464,9 +472,7 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                     TAPS_X(m0t, L_M0);
                     TAPS_X(m1t, L_M1);
                     TAPS_X(m2t, L_M2);
-                    TAPS_X(tt, L_T);
                     HALF_SUMS(su, u, ut, k.x4, k.xh);
-                    he = k.kx * D2T(tt, T);
                     rr[0] = conv(0.0, m[0], rt, su);
                     rr[1] = conv(0.0, m[1], m0t, su);
                     rr[2] = conv(0.0, m[2], m1t, su);
@@ -478,9 +484,7 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                     TAPS_Y(m0t, L_M0);
                     TAPS_Y(m1t, L_M1);
                     TAPS_Y(m2t, L_M2);
-                    TAPS_Y(tt, L_T);
                     HALF_SUMS(sv, v, vt, k.y4, k.yh);
-                    he += k.ky * D2T(tt, T);
                     rr[0] = conv(rr[0], m[0], rt, sv);
                     rr[1] = conv(rr[1], m[1], m0t, sv);
                     rr[2] = conv(rr[2], m[2], m1t, sv);
@@ -506,15 +510,7 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
                     KEEP(ra[SM2][f]);
                     qz[S0][f] = m[f];
                 }
-                const double h1 = k.kz16 * (T - qz[SM1][Z_T]), h2 = k.kz * (T - qz[SM2][Z_T]);
-                rh[S0] = he - (h1 - h2);
-                rh[SM1] += h1;
-                rh[SM2] -= h2;
-                KEEP(rh[S0]);
-                KEEP(rh[SM1]);
-                vbuf[b][H_HEAT][pt] = rh[SM2];
                 qz[S0][Z_W] = w;
-                qz[S0][Z_T] = T;
             }
             // RK update and output of plane zp - 3
             if (do_fin && active) {
@@ -544,8 +540,8 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
     } else if constexpr (GRAD) {
         // ---------------------------------------- group C, stored gradients
         // Reads 72 B per point more than the fused form (232 B in all in
-        // stage 2), which then bounds the stage: 0.83 ms at 256^3 in stage 2,
-        // 4.7 TB/s.  A step with the gradient sweep: 6.14 -> 3.46 ms against
+        // stage 2), which then bounds the stage: 0.89 ms at 256^3 in stage 2,
+        // 4.4 TB/s.  A step with the gradient sweep: 6.14 -> 3.48 ms against
         // one thread per point with thirteen divisions and every tap through
         // the caches.
         enum { Z_U, Z_V, Z_W, NZ };
