@@ -100,9 +100,9 @@ static int64_t compute_units()
 // 16x8 block takes about two thirds of the time of a plane of a 32x8 block,
 // so the narrow tile is faster where one block per compute unit and its longer
 // chunks still come to less.  Measured, 16x8 | 32x8, us per RK3 step: 48^3
-// 33.2 | 38.9, 56^3 43.3 | 46.9, 64^3 49.3 | 50.5, 80^3 77.0 | 81.2, 88^3
-// 116.9 | 98.5, 96^3 129.0 | 106.8, 101x77x53 83.1 | 77.0, 200x20x20 33.6 |
-// 36.0.  Both give the same bits.
+// 32.6 | 39.1, 56^3 43.6 | 46.4, 64^3 48.3 | 49.5, 80^3 75.0 | 75.7, 88^3
+// 119.1 | 96.1, 96^3 126.9 | 104.1, 101x77x53 95.5 | 75.8, 200x20x20 33.7 |
+// 36.1.  Both give the same bits.
 static int default_fp64_tile(const Consts &c, int *zchunk)
 {
     const int64_t cus = compute_units();
@@ -188,11 +188,11 @@ static int64_t max_partial_blocks(const Consts &c)
 // planes of a brick, 0 for the march.  Two planes where that gives at most one
 // brick per compute unit, else four planes as long as the device holds all
 // bricks at once: two (FP64) or four (FP32 storage) fit the LDS of a compute
-// unit.  Measured, us per RK3 step, bricks | best march: FP64 16^3 14.2 | 21.8,
-// 24^3 14.8 | 22.4, 32^3 17.1 | 23.7, 36^3 27.0 | 29.6, 40^3 27.7 | 30.2, 44^3
-// 37.5 | 32.7, 64x40x28 (560 bricks) 36.8 | 30.5; FP32 storage 16^3 13.8 | 21.9,
-// 32^3 16.1 | 22.9, 40^3 19.8 | 27.5, 48^3 28.9 | 30.4, 60^3 43.6 | 40.7, 64^3
-// 48.7 | 40.4.  Two planes against four: 16^3 FP64 14.6 | 16.3, 32^3 (512 of
+// unit.  Measured, us per RK3 step, bricks | best march: FP64 16^3 14.2 | 20.9,
+// 24^3 14.8 | 21.5, 32^3 16.9 | 23.2, 36^3 27.1 | 28.8, 40^3 27.8 | 30.4, 44^3
+// 37.5 | 32.4, 64x40x28 (560 bricks) 36.8 | 29.7; FP32 storage 16^3 13.5 | 21.9,
+// 32^3 15.5 | 22.9, 40^3 19.0 | 27.5, 48^3 27.9 | 29.7, 60^3 43.6 | 40.7, 64^3
+// 48.7 | 40.2.  Two planes against four: 16^3 FP64 14.6 | 16.3, 32^3 (512 of
 // two) 19.5 | 18.4.  The bricks may not outnumber the blocks that the workspace has
 // diagnostic partials for: those of a march of one-plane chunks, which are fewer
 // on some grids of an odd number of planes (16x165x5: 252 two-plane bricks, 210

@@ -12,7 +12,7 @@
 // are differentiated along z, and before A and B take over C's values.
 //
 // Bound by latency: of 4.7 us a stage at 16^3 (14.2 us an RK3 step, the
-// march's best shape 21.1), 1.7 us are an empty launch of a chain; the round
+// march's best shape 20.9), 1.7 us are an empty launch of a chain; the round
 // of loads and its share of the conversions (1.8 us), the gradients (0.3 us)
 // and one thread's arithmetic (about 140 double operations, 1.5 us) are the
 // rest.  Rows of two fields side by side keep a wave's reads on distinct banks

@@ -10,8 +10,8 @@
 //
 // Bound by latency like the FP64 kernel: 4.6 us a stage at 16^3, 1.7 us of it
 // an empty launch; at 48^3, 3.4 bricks a compute unit, by LDS and vector issue
-// (9.6 us).  us per RK3 step, march (its best tile) -> bricks: 16^3 21.9 -> 13.8,
-// 32^3 22.9 -> 16.1, 40^3 27.5 -> 19.8, 48^3 31.7 -> 28.9.  Rows of one field
+// (9.6 us).  us per RK3 step, march (its best tile) -> bricks: 16^3 21.9 -> 13.5,
+// 32^3 22.9 -> 15.5, 40^3 27.5 -> 19.0, 48^3 29.7 -> 27.9.  Rows of one field
 // instead of two: 32^3 16.5, 40^3 21.4, 48^3 30.8 (bank conflicts); one thread per
 // point for all equations: 16.0, 17.4, 22.1, 28.9 at 16^3 to 48^3, before that.
 #include "ns_common.hpp"

@@ -101,7 +101,7 @@ struct FusedPlan {
     double *state, *partial, *acc;
     void *b1, *b2;
 };
-// tile -1 / zchunk 0 take the process-wide or default launch shape.
+// tile -1 / zchunk 0 take the calling thread's or the default launch shape.
 // Validates everything (params, precision, shape, workspace) first.
 ns_status make_fused_plan(const ns_params *p, ns_precision prec, int tile, int zchunk,
                           double *state, void *work, size_t work_bytes, FusedPlan *out);

@@ -26,8 +26,8 @@ constexpr int RS_BX = 32, RS_BY = 8, RS_NT = RS_BX * RS_BY;
 // planes of the own column.  No corners: a gradient has taps in one direction
 // only.
 //
-// Bound by memory: 32 B read and 72 B written per point (0.45 ms at 256^3,
-// 3.9 TB/s; one thread per point, three divisions per tap: 0.75 ms).
+// Bound by memory: 32 B read and 72 B written per point (0.38 ms at 256^3,
+// 4.6 TB/s; one thread per point, three divisions per tap: 0.75 ms).
 __global__ void __launch_bounds__(RS_NT)
 rs_gradient_kernel(Consts c, const double *__restrict__ Q, double *__restrict__ G, int zchunk)
 {

@@ -53,9 +53,9 @@
 // the rest) at two waves per SIMD had 30 dependent LDS waits per plane in the
 // longer group; three groups of about equal length fit 168 registers, three
 // waves per SIMD, and hide them better.  Measured (ms per step without
-// diagnostics, two groups -> three): 512^3 13.99 -> 12.97, 256^3 1.739 ->
-// 1.591, 192^3 0.843 -> 0.745, 101x77x53 0.0884 -> 0.0770, 64^3 0.0552 ->
-// 0.0489 (on small grids also because the march ends at its last plane instead
+// diagnostics, two groups -> three): 512^3 13.99 -> 12.92, 256^3 1.739 ->
+// 1.571, 192^3 0.843 -> 0.735, 101x77x53 0.0884 -> 0.0753, 64^3 0.0552 ->
+// 0.0483 (on small grids also because the march ends at its last plane instead
 // of at a multiple of five).
 #include <type_traits>
 
@@ -540,8 +540,8 @@ trio_stage_kernel(Consts c, Coef64 k, StageArgs s)
     } else if constexpr (GRAD) {
         // ---------------------------------------- group C, stored gradients
         // Reads 72 B per point more than the fused form (232 B in all in
-        // stage 2), which then bounds the stage: 0.89 ms at 256^3 in stage 2,
-        // 4.4 TB/s.  A step with the gradient sweep: 6.14 -> 3.48 ms against
+        // stage 2), which then bounds the stage: 0.90 ms at 256^3 in stage 2,
+        // 4.3 TB/s.  A step with the gradient sweep: 6.14 -> 3.48 ms against
         // one thread per point with thirteen divisions and every tap through
         // the caches.
         enum { Z_U, Z_V, Z_W, NZ };

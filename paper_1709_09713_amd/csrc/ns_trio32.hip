@@ -16,8 +16,8 @@
 // one-thread kernel, whose single wave per SIMD waits for each of its
 // dependent reads, and whose second block hides that only where there are
 // blocks enough.  So it is the faster one on grids that give each compute unit
-// a block or two (us per RK3 step, one thread -> three groups: 56^3 40.9 -> 37.7,
-// 64^3 43.3 -> 40.4, 101x77x53 69.4 -> 64.9), and 4-8% slower on large ones, which
+// a block or two (us per RK3 step, one thread -> three groups: 56^3 40.1 -> 37.4,
+// 64^3 42.7 -> 40.2, 101x77x53 66.5 -> 63.0), and 4-8% slower on large ones, which
 // memory bounds.  Two blocks a compute unit would need 80 registers: 93-300
 // values spill.
 #include <type_traits>
